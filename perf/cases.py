@@ -1,0 +1,431 @@
+"""The work that users of this package have it do, as a list of timed cases.
+
+listed() names the cases, draw() makes more of the same ranges, prepare()
+builds what a program has in hand before the call (inputs on the GPU, the
+solver handle or engine it keeps), run() is one pass through the public entry
+points, work() what that pass cannot do without and exact() its result in
+64 bits without this package's code.
+
+Kinds:
+  poisson   Solver.solve of a Poisson problem (1D, 2D, 3D; FP64, or FP32 /
+            bfloat16-state cycles in FP64 refinement; V, W, F cycles, full
+            multigrid, red-black Gauss-Seidel or Jacobi smoothing)
+  diffusion Solver.solve of a 2D problem with a log-normal coefficient
+  learned   the same with the learned smoother on the finest level
+  batch     BatchSolver.solve of uneven 2D diffusion systems
+  train     learned.train: forward, loss, backward and Adam over patch pairs
+  jacobi5   the fixed-iteration five-point average of a 2D array
+  engine    a NumPy-style stencil program recorded and run by vector.Engine
+"""
+from __future__ import annotations
+
+import math
+
+import torch
+
+import paper_1210_7774_amd as M
+import paper_1210_7774_amd.learned as learned
+import paper_1210_7774_amd.vector as vector
+from paper_1210_7774_amd import inputs
+
+DEV = "cuda"
+
+
+# ---- the cases ------------------------------------------------------------------
+def _poisson(dim, n, precision="f64", nu=2, cycle="V", fmg=False, smoother="rbgs", rtol=1e-10):
+    return dict(kind="poisson", dim=dim, n=n, precision=precision, nu=nu, cycle=cycle, fmg=fmg, smoother=smoother,
+                rtol=rtol)
+
+
+def _diffusion(n, precision, nu=2, rtol=1e-10):
+    return dict(kind="diffusion", n=n, precision=precision, nu=nu, rtol=rtol)
+
+
+def listed():
+    return [
+        # a 1D two-point boundary value problem inside a larger program's loop:
+        # a few microseconds of arithmetic, so launches and latency are the call
+        dict(name="poisson1d_1023_f64", **_poisson(1, 1023)),
+        # a small 2D solve, as in a time-stepping code's pressure equation on a coarse mesh
+        dict(name="poisson2d_255_f64", **_poisson(2, 255)),
+        # nested iteration on an ordinary 2D grid
+        dict(name="poisson2d_2047_f64_fmg", **_poisson(2, 2047, fmg=True)),
+        # the 2D benchmark configuration
+        dict(name="poisson2d_4095_f64", **_poisson(2, 4095)),
+        # an ordinary 3D grid in mixed precision: the levels below the finest weigh as much as it does
+        dict(name="poisson3d_127_f32", **_poisson(3, 127, "f32")),
+        # the headline configuration: the largest 3D solve
+        dict(name="poisson3d_511_f64", **_poisson(3, 511)),
+        # porous-media style coefficients on the learned benchmark's grid, plain smoother
+        dict(name="diffusion2d_1023_f32", **_diffusion(1023, "f32")),
+        # the same problem with the learned smoother (inference inside the solve)
+        dict(name="learned2d_1023_f32", kind="learned", n=1023, precision="f32", rtol=1e-10),
+        # many independent systems of uneven size solved together (parameter sweeps, ensembles)
+        dict(name="batch48_f32", kind="batch", count=48, sizes_seed=40, precision="f32", rtol=1e-10),
+        # one short epoch of training the smoother (forward and backward)
+        dict(name="train_512x64", kind="train", pairs=512, batch=32, patch=64, epochs=1),
+        # the fixed-iteration Jacobi benchmark
+        dict(name="jacobi5_7168", kind="jacobi5", rows=7168, cols=7168, iters=4),
+        # the synthetic stencil program through the vector engine
+        dict(name="engine_mean_10240x1024", kind="engine", program="mean", rows=10240, cols=1024, steps=10),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choices(["poisson", "diffusion", "learned", "batch", "train", "jacobi5", "engine"],
+                       [40, 15, 8, 10, 8, 10, 9])[0]
+    rtol = float("%.2g" % 10 ** rng.uniform(-10, -8))
+    if kind == "poisson":
+        dim = rng.choice([1, 2, 2, 3, 3])
+        precision = rng.choice(["f64", "f64", "f32", "bf16"])
+        cycle = rng.choice(["V", "V", "V", "W", "F"])
+        fmg = precision == "f64" and rng.random() < 0.25
+        smoother = "jacobi" if rng.random() < 0.12 else "rbgs"
+        nu = rng.choice([1, 2, 2, 2, 3])
+        if dim == 1:
+            k = rng.randint(5, 12)
+            cycle = "V"
+        elif dim == 2:
+            k = rng.randint(5, 12 if smoother == "rbgs" and cycle == "V" else 10)
+        else:
+            plain = precision == "f64" and cycle == "V" and smoother == "rbgs" and nu == 2
+            k = rng.randint(4, 9 if plain else 8 if smoother == "rbgs" else 7)
+        if precision == "bf16":
+            rtol = 1e-10
+        return _poisson(dim, 2 ** k - 1, precision, nu, cycle, fmg, smoother, rtol)
+    if kind == "diffusion":
+        precision = rng.choice(["f64", "f32", "f32", "bf16"])
+        return _diffusion(2 ** rng.randint(7, 11) - 1, precision, rng.choice([2, 2, 3]),
+                          1e-10 if precision == "bf16" else rtol)
+    if kind == "learned":
+        return dict(kind="learned", n=2 ** rng.randint(7, 10) - 1, precision=rng.choice(["f32", "bf16"]),
+                    rtol=1e-10)
+    if kind == "batch":
+        return dict(kind="batch", count=_log_int(rng, 2, 48), sizes_seed=rng.randrange(10000),
+                    precision=rng.choice(["f64", "f32", "f32"]), rtol=rtol)
+    if kind == "train":
+        batch = _log_int(rng, 4, 48)
+        return dict(kind="train", pairs=batch * rng.randint(2, 12) + rng.randrange(batch), batch=batch,
+                    patch=rng.randint(24, 64), epochs=1)
+    if kind == "jacobi5":
+        return dict(kind="jacobi5", rows=_log_int(rng, 60, 7168), cols=_log_int(rng, 60, 7168),
+                    iters=rng.choice([1, 2, 3, 4, 4, 4, 5, 7, 8, 10, 16]))
+    return dict(kind="engine", program=rng.choice(["mean", "five_view"]), rows=_log_int(rng, 100, 10240),
+                cols=_log_int(rng, 100, 1100), steps=rng.randint(1, 10))
+
+
+# ---- inputs ---------------------------------------------------------------------
+def _gen(seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(int(seed) % (1 << 62))
+    return g
+
+
+def _normal(shape, g):
+    return torch.randn(shape, generator=g, dtype=torch.float64, device=DEV)
+
+
+def _lognormal(n, g, sigma=1.0, ell=1.0 / 16):
+    """exp of a Gaussian field with squared-exponential covariance on the
+    (n+2)^2 nodes of the unit square, by circulant embedding."""
+    h = 1.0 / (n + 1)
+    m = 1 << (n + 1 + int(math.ceil(6.0 * ell / h))).bit_length()
+    k = torch.arange(m, device=DEV, dtype=torch.float64)
+    d = torch.minimum(k, m - k) * h
+    c = sigma ** 2 * torch.exp(-(d[:, None] ** 2 + d[None, :] ** 2) / (2.0 * ell ** 2))
+    lam = torch.fft.fft2(c).real.clamp_min(0.0)
+    field = torch.fft.ifft2(lam.sqrt() * torch.fft.fft2(_normal((m, m), g))).real
+    return torch.exp(field[: n + 2, : n + 2]).contiguous()
+
+
+def _rhs(dim, n, g):
+    if dim > 1:
+        return _normal((n,) * dim, g)
+    x = torch.arange(1, n + 1, device=DEV, dtype=torch.float64) / (n + 1)
+    noise = torch.rand(n, generator=g, dtype=torch.float64, device=DEV) * 2 - 1
+    return math.pi ** 2 * torch.sin(math.pi * x) + 1e-3 * noise
+
+
+def _batch_sizes(case):
+    return [int(n) for n in inputs.batch_sizes(case["count"], case["sizes_seed"])]
+
+
+def _faces(a):
+    """Harmonic face means of a nodal coefficient, along x and along y."""
+    return (2 * a[..., :, :-1] * a[..., :, 1:] / (a[..., :, :-1] + a[..., :, 1:]),
+            2 * a[..., :-1, :] * a[..., 1:, :] / (a[..., :-1, :] + a[..., 1:, :]))
+
+
+def _pairs(case, g):
+    """Training pairs as a cycle leaves them: errors with smooth and rough
+    parts, s = D^-1 A e on a log-normal coefficient."""
+    count, p = case["pairs"], case["patch"]
+    field = _lognormal(1023, g)
+    ys = torch.randint(0, 1025 - p - 2, (count,), generator=g, device=DEV)
+    xs = torch.randint(0, 1025 - p - 2, (count,), generator=g, device=DEV)
+    r = torch.arange(p + 2, device=DEV)
+    a = field[ys[:, None, None] + r[None, :, None], xs[:, None, None] + r[None, None, :]]
+    e = _normal((count, p + 2, p + 2), g)
+    smooth = e
+    for _ in range(4):
+        smooth = (smooth + smooth.roll(1, 1) + smooth.roll(-1, 1) + smooth.roll(1, 2) + smooth.roll(-1, 2)) / 5
+    e = 1e-3 * (smooth + 0.2 * e)
+    fx, fy = _faces(a)
+    c = e[:, 1:-1, 1:-1]
+    w, ea, so, no = fx[:, 1:-1, :-1], fx[:, 1:-1, 1:], fy[:, :-1, 1:-1], fy[:, 1:, 1:-1]
+    ae = (w * (c - e[:, 1:-1, :-2]) + ea * (c - e[:, 1:-1, 2:]) + so * (c - e[:, :-2, 1:-1]) + no * (c - e[:, 2:, 1:-1]))
+    s = ae / (w + ea + so + no)
+    return [t.to(torch.float32).contiguous() for t in (s, c, a[:, 1:-1, 1:-1])]
+
+
+def prepare(case, seed):
+    g = _gen(seed)
+    kind = case["kind"]
+    if kind == "poisson":
+        shape = (case["n"],) * case["dim"]
+        solver = M.Solver(case["n"], case["dim"], nu1=case["nu"], nu2=case["nu"], smoother=case["smoother"],
+                          precision=case["precision"], cycle=case["cycle"], fmg=case["fmg"], zero_start=True)
+        return dict(case=case, solver=solver, f=_rhs(case["dim"], case["n"], g),
+                    u=torch.zeros(shape, dtype=torch.float64, device=DEV))
+    if kind in ("diffusion", "learned"):
+        n = case["n"]
+        a = _lognormal(n, g)
+        if kind == "learned":
+            solver = M.Solver(n, 2, a=a, smoother="learned", precision=case["precision"], zero_start=True,
+                              learned=learned.jacobi_start())
+        else:
+            solver = M.Solver(n, 2, a=a, nu1=case["nu"], nu2=case["nu"], precision=case["precision"], zero_start=True)
+        return dict(case=case, solver=solver, f=_normal((n, n), g),
+                    u=torch.zeros(n, n, dtype=torch.float64, device=DEV))
+    if kind == "batch":
+        ns = _batch_sizes(case)
+        coefs = [_lognormal(n, g) for n in ns]
+        fs = [_normal((n, n), g) for n in ns]
+        us = [torch.zeros(n, n, dtype=torch.float64, device=DEV) for n in ns]
+        return dict(case=case, solver=M.BatchSolver(ns, coefs=coefs, precision=case["precision"]), us=us, fs=fs)
+    if kind == "train":
+        s, e, a = _pairs(case, g)
+        return dict(case=case, pairs=(s, e, a), start=learned.jacobi_start(),
+                    work=learned.scratch(case["batch"], case["patch"]))
+    if kind == "jacobi5":
+        x = torch.rand(case["rows"], case["cols"], generator=g, dtype=torch.float64, device=DEV)
+        return dict(case=case, x=x, out=torch.empty_like(x), work=torch.empty_like(x) if case["iters"] > 4 else None)
+    x = torch.rand(case["rows"], case["cols"], generator=g, dtype=torch.float64, device=DEV)
+    ta, tb = x.clone(), x.clone()
+    eng = vector.Engine()
+    return dict(case=case, eng=eng, x=eng.asarray(x), a=eng.asarray(ta), b=eng.asarray(tb), tensors=(x, ta, tb))
+
+
+# ---- one pass ---------------------------------------------------------------------
+def _run_mean(state):
+    """steps x the 3 x 3 mean into the other of two arrays, from x."""
+    eng, steps = state["eng"], state["case"]["steps"]
+    R, C = state["case"]["rows"], state["case"]["cols"]
+    src, dst, other = state["x"], state["a"], state["b"]
+    for _ in range(steps):
+        views = [src[1 + di:R - 1 + di, 1 + dj:C - 1 + dj] for di in (-1, 0, 1) for dj in (-1, 0, 1)]
+        acc = views[0] + views[1]
+        for v in views[2:]:
+            acc = acc + v
+        dst[1:-1, 1:-1] = acc / 9.0
+        del acc, views
+        src, dst, other = dst, other, dst
+    eng.flush()
+    return state["tensors"][1 if steps % 2 else 2]
+
+
+def _run_five_view(state):
+    """steps x the five-view loop in place on a copy of x."""
+    eng = state["eng"]
+    A = state["a"]
+    A[...] = state["x"]
+    center, up, down = A[1:-1, 1:-1], A[:-2, 1:-1], A[2:, 1:-1]
+    left, right = A[1:-1, :-2], A[1:-1, 2:]
+    for _ in range(state["case"]["steps"]):
+        work = (((center + up) + down) + left) + right
+        work *= 0.2
+        center[...] = work
+        del work
+    eng.flush()
+    return state["tensors"][1]
+
+
+def run(state):
+    case = state["case"]
+    kind = case["kind"]
+    if kind in ("poisson", "diffusion", "learned"):
+        status, _ = state["solver"].solve(state["u"], state["f"], rtol=case["rtol"])
+        return {"u": state["u"], "status": status}
+    if kind == "batch":
+        for u in state["us"]:
+            u.zero_()
+        status, _ = state["solver"].solve(state["us"], state["fs"], rtol=case["rtol"])
+        return {"u": list(state["us"]), "status": status}
+    if kind == "train":
+        w = state["start"].clone()
+        res = learned.train(*state["pairs"], w, epochs=case["epochs"], batch=case["batch"], border=5, lr=1e-4,
+                            work=state["work"])
+        return {"w": w, "loss": list(res.loss_hist)}
+    if kind == "jacobi5":
+        return M.jacobi5(state["x"], iters=case["iters"], out=state["out"], work=state["work"])
+    return _run_mean(state) if case["program"] == "mean" else _run_five_view(state)
+
+
+# ---- what a pass cannot do without --------------------------------------------------
+def work(case):
+    """Bytes: the inputs read once, the outputs written once.  Operations: of
+    the solves, the cycles a solve of this tolerance takes at the convergence
+    factors of these problems (about 0.1 for Poisson, 0.2 with log-normal
+    coefficients) times the smoothing, residual and transfer operations of a
+    cycle; of the rest, the arithmetic of the definition."""
+    kind = case["kind"]
+    if kind in ("poisson", "diffusion", "learned"):
+        d, n, nu = case.get("dim", 2), case["n"], case.get("nu", 2)
+        pts = n ** d
+        cycles = math.log(case["rtol"]) / math.log(0.1 if kind == "poisson" else 0.2)
+        per = (2 * nu + 2) * (2 * d + 3) * (1 if kind == "poisson" else 2)
+        flops = cycles * pts * per
+        if kind == "learned":
+            flops += cycles * pts * 4 * 9792.0
+        return {"bytes": (16.0 if kind == "poisson" else 24.0) * pts, "flops": flops}
+    if kind == "batch":
+        pts = sum(n * n for n in _batch_sizes(case))
+        return {"bytes": 24.0 * pts, "flops": math.log(case["rtol"]) / math.log(0.3) * pts * 6 * 14}
+    if kind == "train":
+        px = case["epochs"] * (case["pairs"] // case["batch"]) * case["batch"] * case["patch"] ** 2
+        return {"bytes": 12.0 * px, "flops": 3 * 9792.0 * px}
+    pts = case["rows"] * case["cols"]
+    steps = case["iters"] if kind == "jacobi5" else case["steps"]
+    return {"bytes": 16.0 * pts, "flops": 9.0 * pts * steps}
+
+
+# ---- the results in 64 bits -----------------------------------------------------------
+def _dst(x, axis):
+    """Type-I sine transform along one axis (odd extension, real FFT)."""
+    x = x.movedim(axis, -1)
+    z = torch.zeros(x.shape[:-1] + (1,), dtype=x.dtype, device=x.device)
+    n = x.shape[-1]
+    return (torch.fft.rfft(torch.cat([z, x, z, -x.flip(-1)], -1)).imag[..., 1:n + 1] * -0.5).movedim(-1, axis)
+
+
+def _poisson_solve(f):
+    """The discrete Poisson solution by sine transforms."""
+    n, d = f.shape[0], f.dim()
+    k = torch.arange(1, n + 1, device=f.device, dtype=torch.float64)
+    lam = 4.0 * (n + 1) ** 2 * torch.sin(k * math.pi / (2 * (n + 1))) ** 2
+    x = f
+    for ax in range(d):
+        x = _dst(x, ax)
+    tot = 0
+    for ax in range(d):
+        tot = tot + lam.reshape([-1 if q == ax else 1 for q in range(d)])
+    x = x / tot
+    for ax in range(d):
+        x = _dst(x, ax) * (2.0 / (n + 1))
+    return x
+
+
+def _diffusion_solve(a, f):
+    """The discrete diffusion solution by conjugate gradients, preconditioned
+    with the sine-transform solve scaled by the root of the coefficient."""
+    n = f.shape[0]
+    fx, fy = _faces(a)
+    w, e, s, no = fx[1:-1, :-1], fx[1:-1, 1:], fy[:-1, 1:-1], fy[1:, 1:-1]
+    diag, ih2 = w + e + s + no, float((n + 1) ** 2)
+    root = a[1:-1, 1:-1].sqrt()
+
+    def op(u):
+        p = torch.nn.functional.pad(u, (1, 1, 1, 1))
+        return (diag * u - w * p[1:-1, :-2] - e * p[1:-1, 2:] - s * p[:-2, 1:-1] - no * p[2:, 1:-1]) * ih2
+
+    u = torch.zeros_like(f)
+    r = f.clone()
+    z = _poisson_solve(r / root) / root
+    p, rz, stop = z, (r * z).sum(), 1e-26 * (f * f).sum()
+    for it in range(600):
+        q = op(p)
+        al = rz / (p * q).sum()
+        u = u + al * p
+        r = r - al * q
+        if it % 8 == 7 and bool((r * r).sum() < stop):
+            break
+        z = _poisson_solve(r / root) / root
+        new = (r * z).sum()
+        p, rz = z + (new / rz) * p, new
+    return u
+
+
+def _train_exact(case, seed):
+    s, e, a = (t.double() for t in _pairs(case, _gen(seed)))
+    shapes = inputs.LEARNED_SHAPES
+    w = learned.jacobi_start().double()
+    npairs, B, P, bd = case["pairs"], case["batch"], case["patch"], 5
+    order = torch.from_numpy(inputs.epoch_orders(npairs, case["epochs"], 7100)).long().to(DEV)
+    m, v = torch.zeros_like(w), torch.zeros_like(w)
+
+    def net(x, w):
+        at = 0
+        for i, (co, ci) in enumerate(shapes):
+            k = w[at:at + co * ci * 9].reshape(co, ci * 9)
+            at += co * ci * 9
+            cols = torch.nn.functional.pad(x, (1, 1, 1, 1))
+            cols = torch.stack([cols[:, :, dy:dy + P, dx:dx + P] for dy in range(3) for dx in range(3)], 2)
+            x = torch.matmul(k, cols.reshape(x.shape[0], ci * 9, P * P)).reshape(x.shape[0], co, P, P)
+            if i < 3:
+                x = torch.relu(x)
+        return x[:, 0]
+
+    def energy(x, fx, fy):
+        x = x[:, bd:P - bd, bd:P - bd]
+        return (fx * (x[:, :, 1:] - x[:, :, :-1]) ** 2).sum((1, 2)) + (fy * (x[:, 1:] - x[:, :-1]) ** 2).sum((1, 2))
+
+    hist, step, b1, b2 = [], 0, 0.9, 0.999
+    for ep in range(case["epochs"]):
+        tot = 0.0
+        for bi in range(npairs // B):
+            idx = order[ep * npairs + bi * B: ep * npairs + (bi + 1) * B]
+            fx, fy = _faces(a[idx][:, bd:P - bd, bd:P - bd])
+            wt = w.clone().requires_grad_(True)
+            loss = energy(e[idx] - net(s[idx][:, None], wt), fx, fy) / energy(e[idx], fx, fy)
+            loss.mean().backward()
+            tot += float(loss.detach().sum())
+            step += 1
+            m = b1 * m + (1 - b1) * wt.grad
+            v = b2 * v + (1 - b2) * wt.grad ** 2
+            w = w - 1e-4 * (m / (1 - b1 ** step)) / ((v / (1 - b2 ** step)).sqrt() + 1e-8)
+        hist.append(tot / (npairs // B * B))
+    return {"w": w, "loss": hist}
+
+
+def exact(case, seed):
+    g = _gen(seed)
+    kind = case["kind"]
+    if kind == "poisson":
+        return {"u": _poisson_solve(_rhs(case["dim"], case["n"], g)), "status": None}
+    if kind in ("diffusion", "learned"):
+        a = _lognormal(case["n"], g)
+        return {"u": _diffusion_solve(a, _normal((case["n"],) * 2, g)), "status": None}
+    if kind == "batch":
+        ns = _batch_sizes(case)
+        coefs = [_lognormal(n, g) for n in ns]
+        return {"u": [_diffusion_solve(a, _normal((n, n), g)) for n, a in zip(ns, coefs)], "status": None}
+    if kind == "train":
+        return _train_exact(case, seed)
+    x = torch.rand(case["rows"], case["cols"], generator=g, dtype=torch.float64, device=DEV)
+    R, C = case["rows"], case["cols"]
+    for _ in range(case["iters"] if kind == "jacobi5" else case["steps"]):
+        y = x.clone()
+        if kind == "jacobi5" or case["program"] == "five_view":
+            y[1:-1, 1:-1] = 0.2 * (x[1:-1, 1:-1] + x[:-2, 1:-1] + x[2:, 1:-1] + x[1:-1, :-2] + x[1:-1, 2:])
+        else:
+            acc = 0.0
+            for di in (-1, 0, 1):
+                for dj in (-1, 0, 1):
+                    acc = acc + x[1 + di:R - 1 + di, 1 + dj:C - 1 + dj]
+            y[1:-1, 1:-1] = acc / 9.0
+        x = y
+    return x
