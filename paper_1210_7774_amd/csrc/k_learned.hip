@@ -106,45 +106,67 @@ __global__ __launch_bounds__(256) void k_lconv_in(const float *s, const int *idx
 }
 
 // ---- 16 -> 16 layers on MFMA --------------------------------------------------
-// One wavefront computes 16 consecutive pixels of one row x 16 channels.
+// One wavefront computes a column of kConvRows rows of 16 consecutive pixels x
+// 16 channels.
 // mode 0 (forward):  out[p][co] = bf16(relu(sum_t sum_ci WF[t][co][ci] in[p + t][ci]))
 // mode 1 (data gradient): out[p][ci] = bf16(mask(p, ci) * sum_t sum_co WD[t][ci][co] in[p - t][co]),
 //   mask = act[p][ci] > 0 (the forward activation of this layer's input), so
 //   the result is the gradient with respect to the previous pre-activation.
+// Latency bound at training sizes (32 patches of 64 x 64: 8 MB, 8192 row
+// tiles): a wave per row tile loaded its nine weight blocks and nine input
+// blocks for nine products; four rows per wave load the weights once and each
+// input row once for the three output rows that read it: 8.2 -> 6.5 us
+// (forward), 8.8 -> 8.2 us (data gradient).
+static constexpr int kConvRows = 4;
 template <int MODE>
 __global__ __launch_bounds__(256) void k_lconv16(const bf16_t *in, bf16_t *out, const bf16_t *wt, const bf16_t *act,
                                                   int B, int H, int W)
 {
     const int lane = threadIdx.x & 63;
-    const int tiles_x = (W + 15) / 16;
-    const long long ntiles = (long long)B * H * tiles_x;
-    const long long tile = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (tile >= ntiles) return;
-    const int tx = (int)(tile % tiles_x), y = (int)((tile / tiles_x) % H), b = (int)(tile / ((long long)tiles_x * H));
+    const int tiles_x = (W + 15) / 16, segs = (H + kConvRows - 1) / kConvRows;
+    const long long nunits = (long long)B * tiles_x * segs;
+    const long long unit = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    if (unit >= nunits) return;
+    const int y0 = (int)(unit % segs) * kConvRows, tx = (int)((unit / segs) % tiles_x);
+    const int b = (int)(unit / ((long long)segs * tiles_x));
     const int i = lane & 15, kq = (lane >> 4) * 4;
     const int x0 = tx * 16;
-    v4f acc = {0.f, 0.f, 0.f, 0.f};
+    v4s bw[9];
 #pragma unroll
-    for (int t = 0; t < 9; ++t) {
-        const int ky = t / 3, kx = t % 3;
-        const int yy = MODE == 0 ? y + ky - 1 : y - ky + 1;
-        const int xx = MODE == 0 ? x0 + i + kx - 1 : x0 + i - kx + 1;
-        v4s a = {0, 0, 0, 0};
-        if (yy >= 0 && yy < H && xx >= 0 && xx < W)
-            a = *(const v4s *)(in + (((long long)b * H + yy) * W + xx) * 16 + kq);
-        const v4s bw = *(const v4s *)(wt + (t * 16 + i) * 16 + kq);
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bw, acc, 0, 0, 0);
+    for (int t = 0; t < 9; ++t) bw[t] = *(const v4s *)(wt + (t * 16 + i) * 16 + kq);
+    // the three x-shifted blocks of input row y0 - 1 + r, in tap order
+    v4s rows[kConvRows + 2][3];
+#pragma unroll
+    for (int r = 0; r < kConvRows + 2; ++r) {
+        const int yy = y0 - 1 + r;
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) {
+            const int xx = MODE == 0 ? x0 + i + kx - 1 : x0 + i - kx + 1;
+            rows[r][kx] = (v4s){0, 0, 0, 0};
+            if (yy >= 0 && yy < H && xx >= 0 && xx < W)
+                rows[r][kx] = *(const v4s *)(in + (((long long)b * H + yy) * W + xx) * 16 + kq);
+        }
     }
-    // lane holds pixels x0 + kq + q, channel i
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int x = x0 + kq + q;
-        if (x >= W) continue;
-        const long long o = (((long long)b * H + y) * W + x) * 16 + i;
-        float v = acc[q];
-        if (MODE == 0) v = relu(v);
-        else v = (bf16_to_f32(act[o]) > 0.f) ? v : 0.f;
-        out[o] = f32_to_bf16(v);
+    for (int ry = 0; ry < kConvRows; ++ry) {
+        const int y = y0 + ry;
+        if (y >= H) break;
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(rows[MODE == 0 ? ry + t / 3 : ry + 2 - t / 3][t % 3], bw[t],
+                                                            acc, 0, 0, 0);
+        // lane holds pixels x0 + kq + q, channel i
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int x = x0 + kq + q;
+            if (x >= W) continue;
+            const long long o = (((long long)b * H + y) * W + x) * 16 + i;
+            float v = acc[q];
+            if (MODE == 0) v = relu(v);
+            else v = (bf16_to_f32(act[o]) > 0.f) ? v : 0.f;
+            out[o] = f32_to_bf16(v);
+        }
     }
 }
 
@@ -222,77 +244,85 @@ __global__ __launch_bounds__(256) void k_lscaled(const S *e, const float *f, con
 
 // ---- energy-norm loss and its gradient with respect to the network output ---
 // Per patch b (one block each): w = e - y on the window V = [border, P-border)^2,
-// E = sum_faces_in_V a_f (w_p - w_q)^2, E0 = the same for e (precomputed),
+// E = sum_faces_in_V a_f (w_p - w_q)^2, E0 = the same for e,
 // dy = -(2 / B) (A_V w) / E0, loss_b = E / E0.
-__global__ __launch_bounds__(256) void k_lloss(const float *y, const float *e, const float *a, const float *E0,
-                                               const int *idx, int B, int P, int border, float *dy, float *loss_b)
+// Latency bound (a patch per workgroup): the first 256 threads sum E0 while
+// the other 256 sum E and leave A_V w in dy, which all of them scale once E0
+// is known; four pixels' loads are in flight per thread (32 patches of
+// 64 x 64: 12.8 + 17.8 us as two launches, now 16.2 us).
+__global__ __launch_bounds__(512) void k_lloss(const float *y, const float *e, const float *a, const int *idx, int B,
+                                               int P, int border, float *dy, float *loss_b)
 {
     const int b = blockIdx.x;
     const long long pb = (long long)(idx ? idx[b] : b) * P * P;
-    const float inv = -2.f / ((float)B * E0[b]);
-    __shared__ float red[256];
+    const float *eb = e + pb, *ab = a + pb, *yb = y + (long long)b * P * P;
+    float *dyb = dy + (long long)b * P * P;
+    const int lo = border, hi = P - border, np = P * P;
+    __shared__ float red[512];
+    const int half = threadIdx.x >> 8, tid = threadIdx.x & 255;
     float part = 0.f;
-    for (int p = threadIdx.x; p < P * P; p += blockDim.x) {
-        const int x = p % P, yy = p / P;
-        const bool in = x >= border && x < P - border && yy >= border && yy < P - border;
-        float g = 0.f;
-        const float wc = e[pb + p] - y[(long long)b * P * P + p];
-        const float ac = a[pb + p];
-        auto nb = [&](int xx, int yq) -> float {
-            return e[pb + (long long)yq * P + xx] - y[(long long)b * P * P + (long long)yq * P + xx];
-        };
-        auto hm = [&](int xx, int yq) { const float q = a[pb + (long long)yq * P + xx]; return 2.f * ac * q / (ac + q); };
-        if (in) {
-            const int dxs[4] = {-1, 1, 0, 0}, dys[4] = {0, 0, -1, 1};
+    constexpr int U = 4;
+    for (int p0 = tid; p0 < np; p0 += 256 * U) {
+        // values at the pixel and its neighbours (0: centre, 1 .. 4: left, right, up, down)
+        float ev[U][5], av[U][5], yv[U][5];
 #pragma unroll
-            for (int f = 0; f < 4; ++f) {
-                const int xx = x + dxs[f], yq = yy + dys[f];
-                if (xx < border || xx >= P - border || yq < border || yq >= P - border) continue;
-                const float d = wc - nb(xx, yq);
-                const float af = hm(xx, yq);
-                g += af * d;
-                if (f == 1 || f == 3) part += af * d * d;  // each face once: right and down
+        for (int u = 0; u < U; ++u) {
+            const int p = min(p0 + 256 * u, np - 1), x = p % P, yy = p / P;
+            const int q[5] = {p, x > 0 ? p - 1 : p, x + 1 < P ? p + 1 : p, yy > 0 ? p - P : p, yy + 1 < P ? p + P : p};
+#pragma unroll
+            for (int k = 0; k < 5; ++k) {
+                ev[u][k] = eb[q[k]];
+                av[u][k] = ab[q[k]];
+                yv[u][k] = half ? yb[q[k]] : 0.f;
             }
         }
-        dy[(long long)b * P * P + p] = inv * g;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int p = p0 + 256 * u, x = p % P, yy = p / P;
+            if (p >= np) break;
+            const bool in = x >= lo && x < hi && yy >= lo && yy < hi;
+            const float ac = av[u][0];
+            if (half == 0) {
+                if (!in) continue;
+                const float ec = ev[u][0];
+                if (x + 1 < hi) {
+                    const float q2 = av[u][2], d = ec - ev[u][2];
+                    part += 2.f * ac * q2 / (ac + q2) * d * d;
+                }
+                if (yy + 1 < hi) {
+                    const float q2 = av[u][4], d = ec - ev[u][4];
+                    part += 2.f * ac * q2 / (ac + q2) * d * d;
+                }
+                continue;
+            }
+            float g = 0.f;
+            const float wc = ev[u][0] - yv[u][0];
+            if (in) {
+                const int dxs[4] = {-1, 1, 0, 0}, dys[4] = {0, 0, -1, 1};
+#pragma unroll
+                for (int f = 0; f < 4; ++f) {
+                    const int xx = x + dxs[f], yq = yy + dys[f];
+                    if (xx < lo || xx >= hi || yq < lo || yq >= hi) continue;
+                    const float d = wc - (ev[u][f + 1] - yv[u][f + 1]);
+                    const float q = av[u][f + 1];
+                    const float af = 2.f * ac * q / (ac + q);
+                    g += af * d;
+                    if (f == 1 || f == 3) part += af * d * d;  // each face once: right and down
+                }
+            }
+            dyb[p] = g;
+        }
     }
     red[threadIdx.x] = part;
     __syncthreads();
-    for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    for (int o = 128; o > 0; o >>= 1) {
+        if (tid < o) red[threadIdx.x] += red[threadIdx.x + o];
         __syncthreads();
     }
-    if (threadIdx.x == 0) loss_b[b] = red[0] / E0[b];
-}
-
-// E0[b] = E_V(e) of the b-th patch of the batch
-__global__ __launch_bounds__(256) void k_lenergy(const float *e, const float *a, const int *idx, int P, int border,
-                                                 float *E0)
-{
-    const int q = blockIdx.x;
-    const long long pb = (long long)(idx ? idx[q] : q) * P * P;
-    __shared__ float red[256];
-    float part = 0.f;
-    for (int p = threadIdx.x; p < P * P; p += blockDim.x) {
-        const int x = p % P, y = p / P;
-        if (x < border || x >= P - border || y < border || y >= P - border) continue;
-        const float ac = a[pb + p], ec = e[pb + p];
-        if (x + 1 < P - border) {
-            const float q2 = a[pb + p + 1], d = ec - e[pb + p + 1];
-            part += 2.f * ac * q2 / (ac + q2) * d * d;
-        }
-        if (y + 1 < P - border) {
-            const float q2 = a[pb + p + P], d = ec - e[pb + p + P];
-            part += 2.f * ac * q2 / (ac + q2) * d * d;
-        }
-    }
-    red[threadIdx.x] = part;
-    __syncthreads();
-    for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) E0[q] = red[0];
+    const float E0 = red[0];
+    const float inv = -2.f / ((float)B * E0);
+    for (int p = threadIdx.x; p < np; p += 512) dyb[p] = inv * dyb[p];
+    if (threadIdx.x == 0) loss_b[b] = red[256] / E0;
 }
 
 // ---- backward through layer 4 (16 -> 1) ---------------------------------------
@@ -328,121 +358,179 @@ __global__ __launch_bounds__(256) void k_lbwd_out(const float *dy, const bf16_t 
 }
 
 // ---- weight gradients: per-block partials, reduced in block order -----------
-// 16->16 layer (MFMA, K = pixels): for tap t, G_t[ci][co] = sum_p in[p + t][ci] dz[p][co].
-// Each wavefront takes a run of 16-pixel row tiles; a block's 4 wavefronts add
-// in a fixed order; the block writes partial[block][t][ci][co] (FP32).
-__global__ __launch_bounds__(256) void k_lwgrad16(const bf16_t *in, const bf16_t *dz, int B, int H, int W,
-                                                  int tiles_per_wave, float *partial)
+// All four layers in one launch (blockIdx.y), the pixels as the contraction:
+//   layers 2, 3: G_t[ci][co] = sum_p in[p + t][ci] dz[p][co]  (bf16 MFMA, K = 16 pixels)
+//   layer 1:     G[co][t] = sum_p dz1[p][co] bf16(s[p + t])   (bf16 MFMA)
+//   layer 4:     G[ci][t] = sum_q x3[q][ci] dy[q - t]         (FP32 MFMA: dy is FP32)
+// A wavefront takes units of kWgRows rows of 16 pixels and marches down them:
+// in layers 2 and 3 the input row is loaded once (six pixels a lane) for the
+// nine taps of the three output rows that read it.  A block's four wavefronts
+// add in a fixed order and the block writes its partial in the order of the
+// flat gradient, partial[block][kNW].  What bounds it: load latency (at 32
+// patches of 64 x 64, 8 MB of maps); the layers' gradients only need the
+// finished data gradients, so one launch holds four times the waves.  The
+// VALU kernel this replaces ran the 1-channel layers in 32 blocks with 144
+// accumulators a thread (483 + 209 us; layers 2 and 3 28 us each, their serial
+// reductions 60 us each); now 22 us and one reduction of 4 us.
+static constexpr int kWgRows = 8;
+static constexpr int kWgMaxBlocks = 512;  // per layer: bounds the partials (10 MB)
+static int wgrad_blocks(int B, int H, int W)
+{
+    const long long units = (long long)B * ((W + 15) / 16) * ((H + kWgRows - 1) / kWgRows);
+    return (int)std::min<long long>((units + 3) / 4, kWgMaxBlocks);
+}
+
+struct WgArgs {
+    const float *s;        // layer-1 input (FP32, read as bf16-rounded), gathered through idx
+    const int *idx;
+    const bf16_t *x1, *x2, *x3, *dz1, *dz2, *dz3;
+    const float *dy;
+    int B, H, W;
+    float *partial;        // [blocks][kNW]
+};
+
+__global__ __launch_bounds__(256) void k_lwgrad(WgArgs a)
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int tiles_x = (W + 15) / 16;
-    const long long ntiles = (long long)B * H * tiles_x;
-    const int ci = lane & 15, kq = (lane >> 4) * 4;  // A row = ci; B col = co = lane & 15
-    v4f acc[9];
+    const int H = a.H, W = a.W;
+    const int tiles_x = (W + 15) / 16, segs = (H + kWgRows - 1) / kWgRows;
+    const long long nunits = (long long)a.B * tiles_x * segs;
+    const int c = lane & 15, kq = (lane >> 4) * 4;  // operand row / column, first of the lane's four pixels
+    const int layer = blockIdx.y + 1;
+    __shared__ float sh[4][9][256];
+    const long long stride = (long long)gridDim.x * 4;
+    float *dst = a.partial + (long long)blockIdx.x * kNW;
+
+    if (layer == 2 || layer == 3) {
+        const bf16_t *in = layer == 2 ? a.x1 : a.x2, *dz = layer == 2 ? a.dz2 : a.dz3;
+        v4f acc[9];
 #pragma unroll
-    for (int t = 0; t < 9; ++t) acc[t] = (v4f){0.f, 0.f, 0.f, 0.f};
-    const long long first = ((long long)blockIdx.x * 4 + wv) * tiles_per_wave;
-    for (int k = 0; k < tiles_per_wave; ++k) {
-        const long long tile = first + k;
-        if (tile >= ntiles) break;
-        const int tx = (int)(tile % tiles_x), y = (int)((tile / tiles_x) % H), b = (int)(tile / ((long long)tiles_x * H));
-        const int x0 = tx * 16;
-        // B operand: dz at pixels x0 + kq + q, channel co = lane & 15
-        v4s bz;
+        for (int t = 0; t < 9; ++t) acc[t] = (v4f){0.f, 0.f, 0.f, 0.f};
+        for (long long u = (long long)blockIdx.x * 4 + wv; u < nunits; u += stride) {
+            const int y0 = (int)(u % segs) * kWgRows, tx = (int)((u / segs) % tiles_x);
+            const int b = (int)(u / ((long long)segs * tiles_x));
+            const int x0 = tx * 16, y1 = min(y0 + kWgRows, H);
+            const bf16_t *inb = in + (long long)b * H * W * 16, *dzb = dz + (long long)b * H * W * 16;
+            // input row yy at pixels x0 + kq - 1 .. x0 + kq + 4, channel c
+            auto row = [&](int yy, short (&r)[6]) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int x = x0 + kq + q;
-            bz[q] = (x < W) ? (short)dz[(((long long)b * H + y) * W + x) * 16 + (lane & 15)] : (short)0;
+                for (int k = 0; k < 6; ++k) {
+                    const int xx = x0 + kq + k - 1;
+                    const bool ok = yy >= 0 && yy < H && xx >= 0 && xx < W;
+                    r[k] = ok ? (short)inb[((long long)yy * W + xx) * 16 + c] : (short)0;
+                }
+            };
+            auto zrow = [&](int yy, v4s &z) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int xx = x0 + kq + q;
+                    z[q] = (yy < y1 && xx < W) ? (short)dzb[((long long)yy * W + xx) * 16 + c] : (short)0;
+                }
+            };
+            short r0[6], r1[6], r2[6];
+            v4s z, zn;
+            row(y0 - 1, r0);
+            row(y0, r1);
+            row(y0 + 1, r2);
+            zrow(y0, z);
+            for (int y = y0; y < y1; ++y) {
+                short rn[6];
+                row(y + 2, rn);  // the next row's loads are in flight during the products
+                zrow(y + 1, zn);
+#pragma unroll
+                for (int t = 0; t < 9; ++t) {
+                    const short *r = t < 3 ? r0 : t < 6 ? r1 : r2;
+                    v4s ax;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) ax[q] = r[q + t % 3];
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ax, z, acc[t], 0, 0, 0);
+                }
+#pragma unroll
+                for (int k = 0; k < 6; ++k) {
+                    r0[k] = r1[k];
+                    r1[k] = r2[k];
+                    r2[k] = rn[k];
+                }
+                z = zn;
+            }
         }
+        // lane holds G_t[ci = kq + q][co = c]; add the four wavefronts in order
 #pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            const int yy = y + t / 3 - 1;
-            v4s ax;
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) sh[wv][t][(kq + q) * 16 + c] = acc[t][q];
+        __syncthreads();
+        float *d = dst + (layer == 2 ? kW2 : kW3);
+        for (int e = threadIdx.x; e < 2304; e += blockDim.x) {
+            const int t = e % 9, ci = (e / 9) % 16, co = e / 144, r = ci * 16 + co;
+            d[e] = ((sh[0][t][r] + sh[1][t][r]) + sh[2][t][r]) + sh[3][t][r];
+        }
+        return;
+    }
+    // 1-channel layers: rows = channels, columns = taps (9 .. 15 zero)
+    const int ty = c / 3 - 1, tx_ = c % 3 - 1;
+    v4f acc = {0.f, 0.f, 0.f, 0.f};
+    for (long long u = (long long)blockIdx.x * 4 + wv; u < nunits; u += stride) {
+        const int y0 = (int)(u % segs) * kWgRows, tx = (int)((u / segs) % tiles_x);
+        const int b = (int)(u / ((long long)segs * tiles_x));
+        const int x0 = tx * 16, y1 = min(y0 + kWgRows, H);
+        const bf16_t *ch = (layer == 1 ? a.dz1 : a.x3) + (long long)b * H * W * 16;
+        const float *one = layer == 1 ? a.s + (long long)(a.idx ? a.idx[b] : b) * H * W : a.dy + (long long)b * H * W;
+        const int sy = layer == 1 ? ty : -ty, sx = layer == 1 ? tx_ : -tx_;
+#pragma unroll 4
+        for (int y = y0; y < y1; ++y) {
+            bf16_t cv[4];
+            float ov[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int x = x0 + kq + q;  // output pixel p
-                const int xx = x + t % 3 - 1;
-                const bool ok = x < W && yy >= 0 && yy < H && xx >= 0 && xx < W;
-                ax[q] = ok ? (short)in[(((long long)b * H + yy) * W + xx) * 16 + ci] : (short)0;
+                const int x = x0 + kq + q, yy = y + sy, xx = x + sx;
+                cv[q] = x < W ? ch[((long long)y * W + x) * 16 + c] : (bf16_t)0;
+                ov[q] = (c < 9 && x < W && yy >= 0 && yy < H && xx >= 0 && xx < W) ? one[(long long)yy * W + xx] : 0.f;
             }
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ax, bz, acc[t], 0, 0, 0);
-        }
-    }
-    // lane holds G_t[ci = kq + q][co = lane & 15]; add the 4 wavefronts in order
-    __shared__ float sh[4][9][256];
+            if (layer == 1) {
+                v4s av, bv;
 #pragma unroll
-    for (int t = 0; t < 9; ++t)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) sh[wv][t][(kq + q) * 16 + (lane & 15)] = acc[t][q];
-    __syncthreads();
-    for (int e = threadIdx.x; e < 9 * 256; e += blockDim.x) {
-        const int t = e / 256, r = e % 256;
-        const float v = ((sh[0][t][r] + sh[1][t][r]) + sh[2][t][r]) + sh[3][t][r];
-        partial[(long long)blockIdx.x * 2304 + e] = v;  // [t][ci][co]
-    }
-}
-
-// 1-channel layers (VALU): layer 1 G[co][t] = sum_p dz1[p][co] s[p + t];
-// layer 4 G[ci][t] = sum_p dy[p] x3[p + t][ci].  Each block: a run of pixels,
-// fixed-order tree reduction, partial[block][16][9].
-template <int LAYER>
-__global__ __launch_bounds__(256) void k_lwgrad1(const float *s, const int *idx, const bf16_t *act16,
-                                                 const float *dy, int B, int H, int W, int px_per_block,
-                                                 float *partial)
-{
-    __shared__ float red[256];
-    const long long npx = (long long)B * H * W;
-    const long long p0 = (long long)blockIdx.x * px_per_block;
-    float acc[144];
-#pragma unroll
-    for (int k = 0; k < 144; ++k) acc[k] = 0.f;
-    for (long long p = p0 + threadIdx.x; p < min(npx, p0 + px_per_block); p += blockDim.x) {
-        const int x = (int)(p % W), y = (int)((p / W) % H), b = (int)(p / ((long long)W * H));
-#pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            const int yy = y + t / 3 - 1, xx = x + t % 3 - 1;
-            const bool ok = yy >= 0 && yy < H && xx >= 0 && xx < W;
-            if (LAYER == 1) {
-                const long long sb = (long long)(idx ? idx[b] : b) * H * W;
-                const float sv = ok ? bfr(s[sb + (long long)yy * W + xx]) : 0.f;
-#pragma unroll
-                for (int co = 0; co < 16; ++co) acc[co * 9 + t] += bf16_to_f32(act16[p * 16 + co]) * sv;
-            } else {
-                const float d = dy[p];
-#pragma unroll
-                for (int ci = 0; ci < 16; ++ci) {
-                    const float xv = ok ? bf16_to_f32(act16[(((long long)b * H + yy) * W + xx) * 16 + ci]) : 0.f;
-                    acc[ci * 9 + t] += d * xv;
+                for (int q = 0; q < 4; ++q) {
+                    av[q] = (short)cv[q];
+                    bv[q] = bfs(ov[q]);
                 }
+                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc, 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(bf16_to_f32(cv[q]), ov[q], acc, 0, 0, 0);
             }
         }
     }
-    for (int k = 0; k < 144; ++k) {
-        red[threadIdx.x] = acc[k];
-        __syncthreads();
-        for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-            if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) partial[(long long)blockIdx.x * 144 + k] = red[0];
-        __syncthreads();
+    // lane holds G[channel kq + q][tap c]
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sh[wv][0][(kq + q) * 16 + c] = acc[q];
+    __syncthreads();
+    if (threadIdx.x < 144) {
+        const int r = ((int)threadIdx.x / 9) * 16 + (int)threadIdx.x % 9;
+        dst[(layer == 1 ? kW1 : kW4) + threadIdx.x] = ((sh[0][0][r] + sh[1][0][r]) + sh[2][0][r]) + sh[3][0][r];
     }
 }
 
-// Sum partials over blocks (in block order) into the flat FP32 gradient:
-// g[off + map(e)] = sum_b partial[b][e].  For 16->16 layers partial entries are
-// [t][ci][co] and the flat order is [co][ci][t].
-__global__ void k_lreduce(const float *partial, int nblocks, int nper, int layout16, float *g)
+// g[e] = sum_b partial[b][e]: 32 entries a block, eight threads an entry (each
+// adds every eighth block's partial), their sums added in order.
+__global__ __launch_bounds__(256) void k_lreduce(const float *partial, int nblocks, float *g)
 {
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < nper; e += blockDim.x * gridDim.x) {
-        float acc = 0.f;
-        for (int b = 0; b < nblocks; ++b) acc += partial[(long long)b * nper + e];
-        int dst = e;
-        if (layout16) {
-            const int t = e / 256, ci = (e / 16) % 16, co = e % 16;
-            dst = (co * 16 + ci) * 9 + t;
-        }
-        g[dst] = acc;
+    __shared__ float sh[8][32];
+    const int col = threadIdx.x & 31, grp = threadIdx.x >> 5;
+    const int e = blockIdx.x * 32 + col;
+    float acc = 0.f;
+    if (e < kNW) {
+#pragma unroll 8
+        for (int b = grp; b < nblocks; b += 8) acc += partial[(long long)b * kNW + e];
+    }
+    sh[grp][col] = acc;
+    __syncthreads();
+    if (threadIdx.x < 32 && e < kNW) {
+        float v = sh[0][col];
+#pragma unroll
+        for (int k = 1; k < 8; ++k) v += sh[k][col];
+        g[e] = v;
     }
 }
 
@@ -1052,6 +1140,12 @@ static int lgrid(long long work, int block = 256)
     return (int)std::min<long long>(std::max<long long>(g, 1), 65536);
 }
 
+// blocks of four wavefronts, kConvRows rows of 16 pixels each
+static int conv16_grid(int B, int H, int W)
+{
+    return (int)(((long long)B * ((W + 15) / 16) * ((H + kConvRows - 1) / kConvRows) + 3) / 4);
+}
+
 hipError_t learned_prep(const float *w, const LearnedW &d, hipStream_t s)
 {
     hipLaunchKernelGGL(k_lprep, dim3(lgrid(kNW)), dim3(256), 0, s, w, d);
@@ -1065,8 +1159,7 @@ hipError_t learned_forward(const float *s, const int *idx, int B, int H, int W, 
 {
     const long long npx = (long long)B * H * W;
     hipLaunchKernelGGL(k_lconv_in, dim3(lgrid(npx)), dim3(256), 0, st, s, idx, B, H, W, d.w1, x1);
-    const long long tiles = (long long)B * H * ((W + 15) / 16);
-    const int g16 = (int)((tiles + 3) / 4);
+    const int g16 = conv16_grid(B, H, W);
     hipLaunchKernelGGL((k_lconv16<0>), dim3(g16), dim3(256), 0, st, x1, x2, d.wf2, (const bf16_t *)nullptr, B, H, W);
     hipLaunchKernelGGL((k_lconv16<0>), dim3(g16), dim3(256), 0, st, x2, x3, d.wf3, (const bf16_t *)nullptr, B, H, W);
     if (y) hipLaunchKernelGGL(k_lconv_out, dim3(lgrid(npx)), dim3(256), 0, st, x3, d.w4, B, H, W, y);
@@ -1093,14 +1186,11 @@ hipError_t learned_step(int st, void *e, const float *f, const float *a, int n, 
 size_t learned_train_scratch(int B, int P)
 {
     const size_t px = (size_t)B * P * P;
-    const size_t tiles = (size_t)B * P * ((P + 15) / 16);
-    const size_t blk16 = (tiles + 4 * 8 - 1) / (4 * 8);
-    const size_t blk1 = (px + 4095) / 4096;
     size_t b = 0;
     b += 6 * px * 16 * sizeof(bf16_t);                 // x1 x2 x3 dz3 dz2 dz1
     b += 2 * px * sizeof(float);                       // y, dy
-    b += 2 * (size_t)B * sizeof(float);                // loss and E0 per patch
-    b += std::max(blk16 * 2304, blk1 * 144) * sizeof(float) * 2;  // partials
+    b += (size_t)B * sizeof(float);                    // loss per patch
+    b += (size_t)wgrad_blocks(B, P, P) * kNW * sizeof(float);  // partials
     b += 3 * kNW * sizeof(float) + 256;                // g, m, v, loss accumulator
     b += 2 * 144 * sizeof(float) + 4 * 2304 * sizeof(bf16_t) + (256 + 3 * 2560) * sizeof(bf16_t);  // copies
     b += 64 * 1024;                                    // alignment slack
@@ -1118,9 +1208,6 @@ static char *carve_up(char *&p, size_t bytes)
 TrainBufs learned_carve(void *scratch, int B, int P)
 {
     const size_t px = (size_t)B * P * P;
-    const size_t tiles = (size_t)B * P * ((P + 15) / 16);
-    const size_t blk16 = (tiles + 4 * 8 - 1) / (4 * 8);
-    const size_t blk1 = (px + 4095) / 4096;
     char *p = (char *)scratch;
     TrainBufs t;
     t.x1 = (bf16_t *)carve_up(p, px * 16 * 2);
@@ -1132,8 +1219,7 @@ TrainBufs learned_carve(void *scratch, int B, int P)
     t.y = (float *)carve_up(p, px * 4);
     t.dy = (float *)carve_up(p, px * 4);
     t.lossb = (float *)carve_up(p, (size_t)B * 4);
-    t.E0 = (float *)carve_up(p, (size_t)B * 4);
-    t.part = (float *)carve_up(p, std::max(blk16 * 2304, blk1 * 144) * 4 * 2);
+    t.part = (float *)carve_up(p, (size_t)wgrad_blocks(B, P, P) * kNW * 4);
     t.g = (float *)carve_up(p, kNW * 4);
     t.m = (float *)carve_up(p, kNW * 4);
     t.v = (float *)carve_up(p, kNW * 4);
@@ -1159,37 +1245,17 @@ hipError_t learned_loss_grad(const float *S, const float *E, const float *A, con
     const long long px = (long long)B * P * P;
     hipError_t r = learned_forward(S, idx, B, P, P, t.d, t.x1, t.x2, t.x3, t.y, st);
     if (r != hipSuccess) return r;
-    hipLaunchKernelGGL(k_lenergy, dim3(B), dim3(256), 0, st, E, A, idx, P, border, t.E0);
-    hipLaunchKernelGGL(k_lloss, dim3(B), dim3(256), 0, st, t.y, E, A, t.E0, idx, B, P, border, t.dy, t.lossb);
-    // layer 4
-    const int blk1 = (int)((px + 4095) / 4096);
-    hipLaunchKernelGGL((k_lwgrad1<4>), dim3(blk1), dim3(256), 0, st, (const float *)nullptr, idx, t.x3, t.dy, B, P, P,
-                       4096, t.part);
-    hipLaunchKernelGGL(k_lreduce, dim3(1), dim3(256), 0, st, t.part, blk1, 144, 0, g + kW4);
+    hipLaunchKernelGGL(k_lloss, dim3(B), dim3(512), 0, st, t.y, E, A, idx, B, P, border, t.dy, t.lossb);
+    // data gradients, last layer first: dz3 = mask(x3) * conv4^T(dy), dz2 = mask(x2) * conv3^T(dz3), dz1 likewise
+    const int g16 = conv16_grid(B, P, P);
     hipLaunchKernelGGL(k_lbwd_out, dim3(lgrid(px)), dim3(256), 0, st, t.dy, t.x3, t.d.w4, B, P, P, t.dz3);
-    const long long tiles = (long long)B * P * ((P + 15) / 16);
-    const int tpw = 8;
-    const int blk16 = (int)((tiles + 4 * tpw - 1) / (4 * tpw));
-    const int g16 = (int)((tiles + 3) / 4);
-    // layer 3: weights from (x2, dz3); data gradient dz2 = mask(x2) * conv^T(dz3)
-    hipLaunchKernelGGL(k_lwgrad16, dim3(blk16), dim3(256), 0, st, t.x2, t.dz3, B, P, P, tpw, t.part);
-    hipLaunchKernelGGL(k_lreduce, dim3(lgrid(2304)), dim3(256), 0, st, t.part, blk16, 2304, 1, g + kW3);
     hipLaunchKernelGGL((k_lconv16<1>), dim3(g16), dim3(256), 0, st, t.dz3, t.dz2, t.d.wd3, t.x2, B, P, P);
-    // layer 2
-    hipLaunchKernelGGL(k_lwgrad16, dim3(blk16), dim3(256), 0, st, t.x1, t.dz2, B, P, P, tpw, t.part);
-    hipLaunchKernelGGL(k_lreduce, dim3(lgrid(2304)), dim3(256), 0, st, t.part, blk16, 2304, 1, g + kW2);
     hipLaunchKernelGGL((k_lconv16<1>), dim3(g16), dim3(256), 0, st, t.dz2, t.dz1, t.d.wd2, t.x1, B, P, P);
-    // layer 1
-    hipLaunchKernelGGL((k_lwgrad1<1>), dim3(blk1), dim3(256), 0, st, S, idx, t.dz1, (const float *)nullptr, B, P, P,
-                       4096, t.part);
-    hipLaunchKernelGGL(k_lreduce, dim3(1), dim3(256), 0, st, t.part, blk1, 144, 0, g + kW1);
-    return hipGetLastError();
-}
-
-hipError_t learned_energy(const float *E, const float *A, const int *idx, int B, int P, int border, float *E0,
-                          hipStream_t st)
-{
-    hipLaunchKernelGGL(k_lenergy, dim3(B), dim3(256), 0, st, E, A, idx, P, border, E0);
+    // the four layers' weight gradients
+    const int nblk = wgrad_blocks(B, P, P);
+    const WgArgs wa{S, idx, t.x1, t.x2, t.x3, t.dz1, t.dz2, t.dz3, t.dy, B, P, P, t.part};
+    hipLaunchKernelGGL(k_lwgrad, dim3(nblk, 4), dim3(256), 0, st, wa);
+    hipLaunchKernelGGL(k_lreduce, dim3((kNW + 31) / 32), dim3(256), 0, st, t.part, nblk, g);
     return hipGetLastError();
 }
 

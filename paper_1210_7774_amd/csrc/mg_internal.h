@@ -276,7 +276,7 @@ struct LearnedW {       // device weight copies (bf16 / bf16-rounded)
 };
 struct TrainBufs {
     bf16_t *x1, *x2, *x3, *dz3, *dz2, *dz1;
-    float *y, *dy, *lossb, *E0, *part, *g, *m, *v;
+    float *y, *dy, *lossb, *part, *g, *m, *v;
     double *lacc;
     LearnedW d;
 };
