@@ -262,7 +262,8 @@ mg_status mg_jacobi5_static(const double *in, double *out, int rows, int cols, i
  * measures launch shapes on the device.  For every 2D level size that runs
  * the fused PRE/POST kernels, mg_autotune times the PRE launch with block
  * heights 4 .. 256 and, on sizes that hold no system's finest level, LDS
- * tiles, on the bound arrays (u[s], f[s]: nsys device pointers, as for a
+ * tiles (a finest level of up to 1023 points an edge always runs tiles and is
+ * listed untimed), on the bound arrays (u[s], f[s]: nsys device pointers, as for a
  * solve), `reps` (1 .. 50) timed launches per candidate, and keeps the
  * fastest; the choice lasts for the handle's life.  The finest level's
  * smoother runs in place, so u[s] comes back smoothed (a better iterate of
@@ -272,8 +273,9 @@ mg_status mg_jacobi5_static(const double *in, double *out, int rows, int cols, i
  * 0/1; count = how many there are, of which min(count, max) are written to
  * the caller's arrays); mg_tune_set applies one (e.g. read back from a
  * cache): MG_ERR_ARG for n < 1 or hb outside 2 .. 256; odd hb is rounded
- * down; a tile request on a size that holds a finest level, or on a 3D
- * handle, is kept but that size marches. */
+ * down; a size that holds a finest level keeps the form the library gives it
+ * (tiles up to 1023 points an edge, marching with this block height above),
+ * and 3D handles keep the entry without using it. */
 mg_status mg_autotune(mg_handle h, double *const *u, const double *const *f, int reps);
 mg_status mg_tune_get(mg_handle h, int *n, int *hb, int *tiled, int max, int *count);
 mg_status mg_tune_set(mg_handle h, int n, int hb, int tiled);

@@ -1,30 +1,40 @@
-// LDS-tiled fused level kernels for the small 2D levels of the cycle.
+// LDS-tiled fused level kernels for the 2D levels of the cycle that do not
+// fill the chip by marching.
 //
-// The row-marching kernels walk a chain of row steps whose length is set by
-// the block height plus the halo; on a level of a few hundred rows that chain
-// is pure memory latency.  Here one workgroup owns a 32 x 32 tile: it loads
-// the tile plus a halo of R = 2 nu + 2 points into LDS in one round, runs the
-// fused stages there with a barrier between stages, and writes its owned
-// points back.  The stages and their arithmetic are those of the marching
-// kernels (same update, residual, full weighting and bilinear correction
-// formulas); the halo shrinks by one ring per stage, so every value kept
-// depends only on data the workgroup loaded itself (the fusion that the
-// paper's blockable rule, "Vector Engine" section, forbids for elementwise
-// kernels is legal through the recomputed halo).
+// The row-marching kernels walk a chain of row steps (about a microsecond
+// each) whose length is set by the block height plus the halo; on a level of
+// a few hundred rows that chain, not the bytes, is the launch.  Here one
+// workgroup owns a T x T tile and holds the tile plus a halo of R points in
+// registers: every thread owns a pair of x-adjacent points, one of each colour
+// (first column odd), with their right-hand side and face weights, for the
+// whole launch.  Only the values of neighbours go through LDS, stored by
+// colour class (all red points row by row, then all black ones), so the three
+// neighbours a point does not own (its partner is in the thread) are reads of
+// consecutive elements over a wavefront, without bank conflicts and without
+// index arithmetic inside a stage.  A stage is one masked update, one LDS
+// store and one barrier.  The halo shrinks by one ring per stage, so every
+// value kept depends only on data the workgroup loaded itself (the fusion
+// that the paper's blockable rule, "Vector Engine" section, forbids for
+// elementwise kernels is legal through the recomputed halo).
 //
 // PRE  (mode 0): from u (or zero), nu red-black sweeps, residual, full
 //   weighting onto the coarse points the tile owns; writes A and f_c.
-// POST (mode 1): A + P u_c (bilinear), nu red-black sweeps; writes B.
-// Levels that hold a system's finest level keep the marching kernels (they
-// add into the FP64 iterate and measure the residual norm).
+// POST (mode 1): A + P u_c (bilinear), nu red-black sweeps; writes B, or adds
+//   into the FP64 iterate (refinement), or also measures the squared residual
+//   (the FP64 finest level).
+//
+// Tile edge (tile2d_edge): 32 points (28 for three sweeps, whose region would
+// need more than 1024 threads), 16 where 32 would leave CUs idle: there the
+// launch is load latency plus barriers, and 7 waves pass a barrier sooner than
+// 16.  Measured (nu = 2, PRE / POST): 255 FP64 finest 15.4 / 16.6 us marching,
+// 4.6 / 4.2 us here (T = 16); 511 FP64 8.4 / 8.8 us in the first tiled form (two
+// strided passes over the region per stage, all values in LDS), 5.0 / 4.8 us
+// here; 1023 FP64 18.8 / 20.7 -> 10.0 / 11.2 us; 1023 FP32 diffusion finest
+// 36.1 / 49.8 us marching, 11.2 / 14.0 us here.  At 2047 marching is level with
+// it and above that ahead (no halo rows to recompute).
 #include "dev_common.h"
 
 namespace mgx {
-
-constexpr int kTile = 32;                            // owned points per side
-constexpr int kTileRMax = 8;                         // halo for nu <= 3
-constexpr int kTileNR = kTile + 2 * kTileRMax;       // largest region side
-constexpr int kTileThreads = 1024;
 
 template <class C>
 __device__ __forceinline__ C tharmonic(C a, C b)
@@ -32,213 +42,344 @@ __device__ __forceinline__ C tharmonic(C a, C b)
     return (C)2 * a * b / (a + b);
 }
 
-template <class S, class F, bool VC, int MODE, int NS>
-__global__ __launch_bounds__(kTileThreads) void k_tile2d(MarchArgs args)
+// two x-adjacent values (aligned to one element)
+template <class S>
+__device__ __forceinline__ void ld2(const S *p, S &x, S &y)
 {
-    using T = Traits<S>;
-    using C = typename T::C;
-    constexpr int NIT = (kTileNR * kTileNR + kTileThreads - 1) / kTileThreads;  // region passes
-    constexpr int NA = NIT * kTileThreads;
-    constexpr int kCN = kTileNR / 2 + 2;                                         // coarse region side
-    constexpr int NCIT = (kCN * kCN + kTileThreads - 1) / kTileThreads;
-    __shared__ C U[NA];
-    __shared__ C Fv[NA];  // rhs, then (PRE) the residual
-    __shared__ C WE[VC ? NA : 1], WN[VC ? NA : 1], ID[VC ? NA : 1];
-    __shared__ C CV[MODE == 1 ? NCIT * kTileThreads : 1];  // coarse correction values
-    constexpr int R = 2 * NS + 2, NR = kTile + 2 * R, NP = NR * NR;  // compile-time: index math by constants
-    // items == null: one level (args.levels[0]) whose tiles follow the
-    // workgroup index, which saves the dependent load of a work-item record
-    const bool direct = args.items == nullptr;
-    for (int item = blockIdx.x; item < args.nitems; item += gridDim.x) {
-        MarchItem wi;
-        LevelDesc L;
-        if (direct) {
-            L = args.levels[0];
-            const int tiles_x = (L.n + kTile - 1) / kTile;
-            wi.lvl = 0;
-            wi.ia = 1 + kTile * (item % tiles_x);
-            wi.ja = 1 + kTile * (item / tiles_x);
-            wi.part = 0;
-        } else {
-            wi = args.items[item];
-            L = args.levels[wi.lvl];
+    typedef S v2 __attribute__((ext_vector_type(2), aligned(sizeof(S))));
+    const v2 v = *(const __attribute__((address_space(1))) v2 *)p;
+    x = v.x;
+    y = v.y;
+}
+template <class S>
+__device__ __forceinline__ void st2(S *p, S x, S y)
+{
+    typedef S v2 __attribute__((ext_vector_type(2), aligned(sizeof(S))));
+    *(__attribute__((address_space(1))) v2 *)p = (v2){x, y};
+}
+__device__ __forceinline__ double tval(double v) { return v; }
+__device__ __forceinline__ float tval(float v) { return v; }
+__device__ __forceinline__ float tval(bf16_t v) { return bf16_to_f32(v); }
+__device__ __forceinline__ void tput(double &d, double v) { d = v; }
+__device__ __forceinline__ void tput(float &d, float v) { d = v; }
+// (values are rounded to bfloat16 when computed)
+__device__ __forceinline__ void tput(bf16_t &d, float v) { d = (bf16_t)(__float_as_uint(v) >> 16); }
+
+// FIN: the level may hold a system's finest level (POST: FP64 norm, or the add
+// into the FP64 iterate).
+template <class S, int MODE, int NS, int T, int FIN>
+struct TileGeo {
+    // halo: one ring per half sweep, and 2 more for residual + restriction, 1
+    // (kept even: 2) for the norm
+    static constexpr bool NORM = MODE == 1 && FIN && sizeof(S) == 8;
+    static constexpr bool ACC = MODE == 1 && FIN && sizeof(S) < 8;
+    static constexpr int R = 2 * NS + ((MODE == 0 || NORM) ? 2 : 0);
+    static constexpr int LX = T + 2 * R, PX = LX / 2, NP = PX * LX;
+    static constexpr int NT = (NP + 63) / 64 * 64;
+};
+
+template <class S, class F, bool VC, int MODE, int NS, int T, int FIN>
+__global__ __launch_bounds__((TileGeo<S, MODE, NS, T, FIN>::NT)) void k_tile2d(MarchArgs args, LevelDesc L1)
+{
+    using G = TileGeo<S, MODE, NS, T, FIN>;
+    using Tr = Traits<S>;
+    using C = typename Tr::C;
+    constexpr int R = G::R, LX = G::LX, PX = G::PX, NP = G::NP, NT = G::NT;
+    static_assert(NT <= 1024 && R % 2 == 0 && T % 2 == 0, "tile geometry");
+    __shared__ C U[2 * NP + 2];                            // red points, black points, a spare pair
+    __shared__ C RP[MODE == 0 ? NP : 1], R0[MODE == 0 ? NP : 1];
+    __shared__ C FE[VC ? NP : 1], FN0[VC ? NP : 1], FN1[VC ? NP : 1];
+    __shared__ double wsum[G::NORM ? NT / 64 : 1];
+
+    // Workgroups are dealt round-robin to the 8 XCDs; each gets a contiguous
+    // range of tiles (neighbouring tiles' halos meet in one L2)
+    const int per = (args.nitems + 7) / 8;
+    const int item = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+    if (item >= args.nitems) return;
+    // items == null: one level, its descriptor in the arguments and its tiles
+    // from the workgroup index (no dependent loads before the data)
+    MarchItem wi;
+    LevelDesc L;
+    if (args.items == nullptr) {
+        L = L1;
+        const int tiles_x = (L.n + T - 1) / T;
+        wi.ia = 1 + T * (item % tiles_x);
+        wi.ja = 1 + T * (item / tiles_x);
+        wi.part = item;
+    } else {
+        wi = args.items[item];
+        L = args.levels[wi.lvl];
+    }
+    // the stop flag is tested once the region's loads are issued (the same
+    // value for the whole workgroup)
+    const int done = args.states[L.sys].done;
+    const int n = L.n, nc = L.nc;
+    const int tid = threadIdx.x;
+    const bool act = NP == NT || tid < NP;
+    const int y = act ? tid / PX : 0, kp = act ? tid % PX : 0;
+    const int gi = wi.ia - R + 2 * kp, gj = wi.ja - R + y;  // the pair: columns gi (odd), gi + 1
+    const bool rin = act && gj >= 1 && gj <= n && gi >= 1;
+    const bool in0 = rin && gi <= n, in1 = rin && gi + 1 <= n;
+    const C h2 = (C)L.h2, ih2 = (C)L.inv_h2;
+    const int gic = min(max(gi, 1), n - 1), gjc = min(max(gj, 1), n);  // (n >= 3)
+    const long long go = (long long)(gjc - 1) * L.pitch + (gic - 1);
+    const bool edge = gi == n;                                         // the pair's first column is the last one
+    const bool own = act && y >= R && y < R + T && kp >= R / 2 && kp < R / 2 + T / 2;
+
+    // ---- load the region: clamped addresses, values selected afterwards, so
+    // all of a thread's loads are in flight together
+    const bool uzero = MODE == 0 && L.uzero;
+    C ux[2] = {(C)0, (C)0}, fx[2];
+    {
+        F a, b;
+        ld2((const F *)L.f + go, a, b);
+        fx[0] = (C)(edge ? b : a);
+        fx[1] = (C)b;
+    }
+    if (!uzero) {
+        S a, b;
+        ld2((const S *)(MODE == 0 ? L.B : L.A) + go, a, b);
+        ux[0] = in0 ? tval(edge ? b : a) : (C)0;
+        ux[1] = in1 ? tval(b) : (C)0;
+    }
+    double acc[2] = {0.0, 0.0};
+    long long ao = 0;
+    if constexpr (G::ACC) {
+        ao = (long long)(gjc - 1) * L.acc_pitch + (gic - 1);
+        if (L.acc && own && in0) {
+            ld2(L.acc + ao, acc[0], acc[1]);
+            if (edge) acc[0] = acc[1];
         }
-        // the stop flag is tested after the region's loads are issued (the
-        // same value for the whole workgroup)
-        const int done = args.states[L.sys].done;
-        const int n = L.n, nc = L.nc;
-        const long long pitch = L.pitch, cpitch = L.cpitch;
-        const int i0 = wi.ia - R, j0 = wi.ja - R;  // region origin (1-based)
-        const int ia1 = wi.ia + kTile - 1, ja1 = wi.ja + kTile - 1;
-        const C h2 = (C)L.h2, ih2 = (C)L.inv_h2;
-        const S *uin = (MODE == 0) ? (L.uzero ? nullptr : (const S *)L.B) : (const S *)L.A;
-        const F *fin = (const F *)L.f;
-        const C *acoef = (const C *)L.a;
-        // ---- load the region (and the faces touching it).  Fixed trip
-        // count and clamped addresses, values selected afterwards: every
-        // thread has all its loads in flight at once.
+    }
+    C mid = (C)1, fe = (C)1, fn0 = (C)1, fn1 = (C)1;
+    if constexpr (VC) {
+        // the faces right of and above the pair's points (the boundary nodes
+        // 0 and n + 1 have coefficients too); those left and below come from
+        // the neighbours through LDS
+        const C *ac = (const C *)L.a;
+        auto node = [&](int i, int j) -> C {
+            return gld(ac + (long long)min(max(j, 0), n + 1) * (n + 2) + min(max(i, 0), n + 1));
+        };
+        const C a0 = node(gi, gj), a1 = node(gi + 1, gj), a2 = node(gi + 2, gj);
+        const C b0 = node(gi, gj + 1), b1 = node(gi + 1, gj + 1);
+        mid = tharmonic(a0, a1);
+        fe = tharmonic(a1, a2);
+        fn0 = tharmonic(a0, b0);
+        fn1 = tharmonic(a1, b1);
+    }
+    if constexpr (MODE == 1) {
+        // bilinear coarse-grid correction: coarse (I, J) sits on fine (2I, 2J),
+        // index 0 and nc + 1 are the zero boundary
+        const S *bc = (const S *)L.Bc;
+        const int I = (gi + 1) / 2;
+        const int Ja = (gj & 1) ? (gj - 1) / 2 : gj / 2, Jb = (gj & 1) ? (gj + 1) / 2 : gj / 2;
+        auto cv = [&](int i, int j) -> C {
+            const bool ok = i >= 1 && i <= nc && j >= 1 && j <= nc;
+            const C v = tval(gld(bc + (long long)(min(max(j, 1), nc) - 1) * L.cpitch + (min(max(i, 1), nc) - 1)));
+            return ok ? v : (C)0;
+        };
+        const C l0 = cv(I - 1, Ja), r0 = cv(I, Ja), l1 = cv(I - 1, Jb), r1 = cv(I, Jb);
+        const C x0a = (l0 + r0) * (C)0.5, x0b = (l1 + r1) * (C)0.5;
+        const C c0 = (gj & 1) ? (x0a + x0b) * (C)0.5 : x0a;
+        const C c1 = (gj & 1) ? (r0 + r1) * (C)0.5 : r0;
+        ux[0] = in0 ? Tr::rnd(ux[0] + c0) : (C)0;
+        ux[1] = in1 ? Tr::rnd(ux[1] + c1) : (C)0;
+    }
+    if (done) return;
+
+    // ---- by colour class (0: red, 1-based index sum even) -----------------------
+    const bool x1red = (gj & 1) == 0;  // which of the pair is red in this row
+    const int q = y * PX + kp;
+    const int dy = min(y, LX - 1 - y);
+    const int dm0 = in0 ? min(min(2 * kp, LX - 1 - 2 * kp), dy) : -1;
+    const int dm1 = in1 ? min(min(2 * kp + 1, LX - 2 - 2 * kp), dy) : -1;
+    // distance of the class's point to the region's edge (stage test)
+    const int dm[2] = {x1red ? dm1 : dm0, x1red ? dm0 : dm1};
+    C u[2] = {x1red ? ux[1] : ux[0], x1red ? ux[0] : ux[1]};
+    const C f[2] = {x1red ? fx[1] : fx[0], x1red ? fx[0] : fx[1]};
+    int me[2], xn[2], yb[2];
 #pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-            const int p = threadIdx.x + it * kTileThreads;
-            const int gi = i0 + p % NR, gj = j0 + p / NR;
-            const bool inside = p < NP && gi >= 1 && gi <= n && gj >= 1 && gj <= n;
-            const long long o = inside ? (long long)(gj - 1) * pitch + (gi - 1) : 0;
-            const C uv = uin ? (C)T::ld(uin + o) : (C)0;
-            const C fv = (C)gld(fin + o);
-            U[p] = inside ? uv : (C)0;
-            Fv[p] = inside ? fv : (C)0;
-            if constexpr (VC) {
-                // east / north face of node (gi, gj) for nodes 0 .. n (faces
-                // against boundary nodes use the boundary's coefficient)
-                const bool fe = p < NP && gi >= 0 && gi <= n && gj >= 0 && gj <= n + 1;
-                const bool fn = p < NP && gi >= 0 && gi <= n + 1 && gj >= 0 && gj <= n;
-                const long long an = (fe || fn) ? (long long)gj * (n + 2) + gi : 0;
-                const C ac = gld(acoef + an);
-                const C ae = gld(acoef + (fe ? an + 1 : an));
-                const C anb = gld(acoef + (fn ? an + (n + 2) : an));
-                WE[p] = fe ? tharmonic(ac, ae) : (C)1;
-                WN[p] = fn ? tharmonic(ac, anb) : (C)1;
-            }
+    for (int c = 0; c < 2; ++c) {
+        me[c] = act ? c * NP + q : 2 * NP + c;
+        // the x neighbour that is not the partner: left of the first column,
+        // right of the second (margins keep the clamped ones unused)
+        const bool sec = (c == 0) == x1red;
+        xn[c] = (1 - c) * NP + y * PX + min(max(kp + (sec ? 1 : -1), 0), PX - 1);
+        yb[c] = (1 - c) * NP + min(max(y - 1, 0), LX - 3) * PX + kp;
+    }
+    // the point's west neighbour is its partner when it is the pair's second,
+    // its east neighbour when it is the first (sums add west, east, south,
+    // north: the order of the marching kernels, whose values these are)
+    const bool second[2] = {x1red, !x1red};
+    // face weights: west, east, south (row j - 1), north
+    C fw[2], fE[2], fs[2], fn[2], id[2];
+    if constexpr (VC) {
+        if (act) {
+            FE[q] = fe;
+            FN0[q] = fn0;
+            FN1[q] = fn1;
         }
-        // ---- POST: the coarse values under the region, staged in LDS
-        // (coarse I covers fine 2I; index 0 and nc + 1 are the zero boundary)
-        const int ci0 = (i0 >= 1 ? (i0 - 1) / 2 : -((1 - i0 + 1) / 2)), cj0 = (j0 >= 1 ? (j0 - 1) / 2 : -((1 - j0 + 1) / 2));
-        if constexpr (MODE == 1) {
-            const S *bc = (const S *)L.Bc;
+        if (!uzero) {
+            U[me[0]] = u[0];
+            U[me[1]] = u[1];
+        }
+        __syncthreads();
+        const C w = FE[max(q - 1, 0)], s0 = FN0[max(q - PX, 0)], s1 = FN1[max(q - PX, 0)];
+        const C i0 = (C)1 / (((w + mid) + s0) + fn0), i1 = (C)1 / (((mid + fe) + s1) + fn1);
 #pragma unroll
-            for (int it = 0; it < NCIT; ++it) {
-                const int q = threadIdx.x + it * kTileThreads;
-                const int I = ci0 + q % kCN, J = cj0 + q / kCN;
-                const bool ok = q < kCN * kCN && I >= 1 && I <= nc && J >= 1 && J <= nc;
-                const C v = (C)T::ld(bc + (ok ? (long long)(J - 1) * cpitch + (I - 1) : 0));
-                CV[q] = ok ? v : (C)0;
-            }
+        for (int c = 0; c < 2; ++c) {
+            fw[c] = second[c] ? mid : w;
+            fE[c] = second[c] ? fe : mid;
+            fs[c] = second[c] ? s1 : s0;
+            fn[c] = second[c] ? fn1 : fn0;
+            id[c] = second[c] ? i1 : i0;
         }
-        if (done) continue;  // before the first barrier of the item
+    }
+    int m0 = 1;
+    if (uzero) {
+        // a zero state: the first red half sweep has no neighbours to read
+        C v;
+        if constexpr (VC) v = (h2 * f[0]) * id[0];
+        else v = (h2 * f[0]) * (C)0.25;
+        u[0] = dm[0] >= 1 ? Tr::rnd(v) : (C)0;
+        m0 = 2;
+    }
+    if (!VC || uzero) {
+        U[me[0]] = u[0];
+        U[me[1]] = u[1];
         __syncthreads();
-        if constexpr (VC) {
-            for (int p = threadIdx.x; p < NP; p += kTileThreads) {
-                const int x = p % NR, y = p / NR;
-                C v = (C)0.25;
-                if (x >= 1 && y >= 1) v = (C)1 / (((WE[p - 1] + WE[p]) + WN[p - NR]) + WN[p]);
-                ID[p] = v;
+    }
+    // ---- the red-black stages; stage m updates the points at least m from
+    // the region's edge
+#pragma unroll
+    for (int m = 1; m <= 2 * NS; ++m) {
+        if (m < m0) continue;
+        const int c = (m & 1) ? 0 : 1;
+        const C xo = U[xn[c]], up = U[yb[c]], dn = U[yb[c] + 2 * PX];
+        const C w = second[c] ? u[1 - c] : xo, e = second[c] ? xo : u[1 - c];
+        C v;
+        if constexpr (!VC) v = ((((h2 * f[c] + w) + e) + up) + dn) * (C)0.25;
+        else v = ((((h2 * f[c] + fw[c] * w) + fE[c] * e) + fs[c] * up) + fn[c] * dn) * id[c];
+        if (dm[c] >= m) {
+            u[c] = Tr::rnd(v);
+            U[me[c]] = u[c];
+        }
+        if (m < 2 * NS || MODE == 0 || G::NORM) __syncthreads();
+    }
+    auto resid = [&](int c) -> C {
+        const C xo = U[xn[c]], up = U[yb[c]], dn = U[yb[c] + 2 * PX];
+        const C w = second[c] ? u[1 - c] : xo, e = second[c] ? xo : u[1 - c];
+        C Au;
+        if constexpr (!VC)
+            Au = ((((u[c] - w) + (u[c] - e)) + (u[c] - up)) + (u[c] - dn)) * ih2;
+        else
+            Au = (((fw[c] * (u[c] - w) + fE[c] * (u[c] - e)) + fs[c] * (u[c] - up)) + fn[c] * (u[c] - dn)) * ih2;
+        return f[c] - Au;
+    };
+    ux[0] = x1red ? u[1] : u[0];
+    ux[1] = x1red ? u[0] : u[1];
+    // ---- store the owned points
+    if (own && in0) {
+        if constexpr (G::ACC) {
+            if (L.acc) {
+                double *p = L.acc + ao;
+                if (in1) st2(p, acc[0] + (double)ux[0], acc[1] + (double)ux[1]);
+                else p[edge ? 1 : 0] = acc[0] + (double)ux[0];
             }
         }
-        // ---- POST: bilinear coarse-grid correction on the region
-        if constexpr (MODE == 1) {
-            auto cv = [&](int I, int J) -> C { return CV[(J - cj0) * kCN + (I - ci0)]; };
-            for (int p = threadIdx.x; p < NP; p += kTileThreads) {
-                const int gi = i0 + p % NR, gj = j0 + p / NR;
-                if (!(gi >= 1 && gi <= n && gj >= 1 && gj <= n)) continue;
-                auto hx = [&](int J) -> C {
-                    if ((gi & 1) == 0) return cv(gi / 2, J);
-                    return (cv((gi - 1) / 2, J) + cv((gi + 1) / 2, J)) * (C)0.5;
-                };
-                const C corr = ((gj & 1) == 0) ? hx(gj / 2) : (hx((gj - 1) / 2) + hx((gj + 1) / 2)) * (C)0.5;
-                U[p] = T::rnd(U[p] + corr);
-            }
+        if (!G::ACC || !L.acc) {
+            S *p = (S *)(MODE == 0 ? L.A : L.B) + go;
+            S a, b;
+            tput(a, ux[0]);
+            tput(b, ux[1]);
+            if (in1) st2(p, a, b);
+            else gst(p + (edge ? 1 : 0), a);
+        }
+    }
+    if constexpr (MODE == 0) {
+        // ---- residual on the tile + 1, summed 1-2-1 along x, then along y
+        const C rr[2] = {dm[0] >= R - 1 ? resid(0) : (C)0, dm[1] >= R - 1 ? resid(1) : (C)0};
+        const C r0 = x1red ? rr[1] : rr[0], r1 = x1red ? rr[0] : rr[1];
+        if (act) {
+            RP[q] = r0 + (C)2 * r1;
+            R0[q] = r0;
         }
         __syncthreads();
-        // ---- the red-black stages; stage m updates the points within R - m
-        // of the tile (red: 1-based index sum even)
-        for (int m = 1; m <= 2 * NS; ++m) {
-            const int colour = (m & 1) ? 0 : 1;
-            const int lim = R - m;
-            for (int p = threadIdx.x; p < NP; p += kTileThreads) {
-                const int x = p % NR, y = p / NR;
-                const int gi = i0 + x, gj = j0 + y;
-                const int d = max(max(wi.ia - gi, gi - ia1), max(wi.ja - gj, gj - ja1));
-                if (!(gi >= 1 && gi <= n && gj >= 1 && gj <= n) || ((gi + gj) & 1) != colour || d > lim) continue;
-                const C w = U[p - 1], e = U[p + 1], up = U[p - NR], dn = U[p + NR];
-                C v;
-                if constexpr (!VC) {
-                    v = ((((h2 * Fv[p] + w) + e) + up) + dn) * (C)0.25;
-                } else {
-                    v = ((((h2 * Fv[p] + WE[p - 1] * w) + WE[p] * e) + WN[p - NR] * up) + WN[p] * dn) * ID[p];
+        // coarse (I, J) sits on fine (2I, 2J): the second point of a pair of an even row
+        const int I = (gi + 1) / 2, J = gj / 2;
+        if (own && in1 && (gj & 1) == 0 && I <= nc && J <= nc) {
+            auto rx = [&](int p) { return RP[p] + R0[p + 1]; };
+            const C v = ((rx(q - PX) + (C)2 * rx(q)) + rx(q + PX)) * (C)0.0625;
+            gst((F *)L.fc + (long long)(J - 1) * L.cpitch + (I - 1), (F)v);
+        }
+    }
+    if constexpr (G::NORM) {
+        if (L.norm) {
+            double s = 0.0;
+            if (own) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const double r = dm[c] >= 0 ? (double)resid(c) : 0.0;
+                    s += r * r;
                 }
-                U[p] = T::rnd(v);
             }
+            s = wave_sum(s);
+            if ((tid & 63) == 0) wsum[tid >> 6] = s;
             __syncthreads();
-        }
-        if constexpr (MODE == 0) {
-            // ---- residual on the tile + 1 (into Fv), then full weighting
-            for (int p = threadIdx.x; p < NP; p += kTileThreads) {
-                const int x = p % NR, y = p / NR;
-                const int gi = i0 + x, gj = j0 + y;
-                const int d = max(max(wi.ia - gi, gi - ia1), max(wi.ja - gj, gj - ja1));
-                if (d > 1) continue;
-                C r = (C)0;
-                if (gi >= 1 && gi <= n && gj >= 1 && gj <= n) {
-                    const C u = U[p], w = U[p - 1], e = U[p + 1], up = U[p - NR], dn = U[p + NR];
-                    C Au;
-                    if constexpr (!VC) {
-                        Au = ((((u - w) + (u - e)) + (u - up)) + (u - dn)) * ih2;
-                    } else {
-                        Au = (((WE[p - 1] * (u - w) + WE[p] * (u - e)) + WN[p - NR] * (u - up)) + WN[p] * (u - dn)) *
-                             ih2;
-                    }
-                    r = Fv[p] - Au;
-                }
-                Fv[p] = r;
-            }
-            __syncthreads();
-            F *fc = (F *)L.fc;
-            for (int q = threadIdx.x; q < (kTile / 2) * (kTile / 2); q += kTileThreads) {
-                // coarse (I, J) sits on fine (2I, 2J); the tile owns it when that
-                // fine point is owned (ia, ja odd, so 2I = ia + 1 + 2 qx)
-                const int fi = wi.ia + 1 + 2 * (q % (kTile / 2)), fj = wi.ja + 1 + 2 * (q / (kTile / 2));
-                const int I = fi / 2, J = fj / 2;
-                if (I > nc || J > nc) continue;
-                const int x = fi - i0, y = fj - j0;
-                auto rx = [&](int yy) {
-                    const int b = yy * NR + x;
-                    return (Fv[b - 1] + (C)2 * Fv[b]) + Fv[b + 1];
-                };
-                const C v = ((rx(y - 1) + (C)2 * rx(y)) + rx(y + 1)) * (C)0.0625;
-                fc[(long long)(J - 1) * cpitch + (I - 1)] = (F)v;
+            if (tid < 64) {
+                double tot = 0.0;
+                for (int k = 0; k < NT / 64; ++k) tot += wsum[k];
+                put_partial(args.partials, wi.part, tot, 0.0);
             }
         }
-        // ---- store the owned points
-        S *uout = (MODE == 0) ? (S *)L.A : (S *)L.B;
-        for (int q = threadIdx.x; q < kTile * kTile; q += kTileThreads) {
-            const int gi = wi.ia + q % kTile, gj = wi.ja + q / kTile;
-            if (gi > n || gj > n) continue;
-            const int p = (gj - j0) * NR + (gi - i0);
-            T::st(uout + (long long)(gj - 1) * pitch + (gi - 1), U[p]);
-        }
-        __syncthreads();  // the next item reuses the LDS arrays
     }
 }
 
-template <class S, class F, bool VC, int NS>
-static hipError_t tile_ns(int mode, const MarchArgs &a, int grid, hipStream_t s)
+template <class S, class F, bool VC, int NS, int T>
+static hipError_t tile_go(int mode, int fin, const MarchArgs &a, const LevelDesc &L, hipStream_t s)
 {
-    if (mode == 0) hipLaunchKernelGGL((k_tile2d<S, F, VC, 0, NS>), dim3(grid), dim3(kTileThreads), 0, s, a);
-    else hipLaunchKernelGGL((k_tile2d<S, F, VC, 1, NS>), dim3(grid), dim3(kTileThreads), 0, s, a);
+    const dim3 grid((unsigned)((a.nitems + 7) / 8 * 8));
+    if (mode == 0)
+        hipLaunchKernelGGL((k_tile2d<S, F, VC, 0, NS, T, 0>), grid, dim3(TileGeo<S, 0, NS, T, 0>::NT), 0, s, a, L);
+    else if (!fin)
+        hipLaunchKernelGGL((k_tile2d<S, F, VC, 1, NS, T, 0>), grid, dim3(TileGeo<S, 1, NS, T, 0>::NT), 0, s, a, L);
+    else
+        hipLaunchKernelGGL((k_tile2d<S, F, VC, 1, NS, T, 1>), grid, dim3(TileGeo<S, 1, NS, T, 1>::NT), 0, s, a, L);
     return hipGetLastError();
 }
 
 template <class S, class F, bool VC>
-static hipError_t tile_typed(int mode, const MarchArgs &a, int NS, int grid, hipStream_t s)
+static hipError_t tile_typed(int mode, int fin, int NS, const MarchArgs &a, const LevelDesc &L, hipStream_t s)
 {
+    const bool small = a.W == 16;
     switch (NS) {
-    case 1: return tile_ns<S, F, VC, 1>(mode, a, grid, s);
-    case 2: return tile_ns<S, F, VC, 2>(mode, a, grid, s);
-    default: return tile_ns<S, F, VC, 3>(mode, a, grid, s);
+    case 1: return small ? tile_go<S, F, VC, 1, 16>(mode, fin, a, L, s) : tile_go<S, F, VC, 1, 32>(mode, fin, a, L, s);
+    case 2: return small ? tile_go<S, F, VC, 2, 16>(mode, fin, a, L, s) : tile_go<S, F, VC, 2, 32>(mode, fin, a, L, s);
+    case 3: return small ? tile_go<S, F, VC, 3, 16>(mode, fin, a, L, s) : tile_go<S, F, VC, 3, 28>(mode, fin, a, L, s);
     }
+    return hipErrorInvalidValue;
 }
 
-hipError_t launch_tile2d(int mode, int st, bool vc, int nsweeps, const MarchArgs &a, hipStream_t s)
+// tiles of count levels of n x n points: the large edge when that gives every
+// one of the 256 CUs a tile, else 16
+int tile2d_edge(int n, int count, int nsweeps)
 {
-    if (a.W != kTile || a.Hb != kTile || nsweeps < 1 || 2 * nsweeps + 2 > kTileRMax) return hipErrorInvalidValue;
-    const int grid = std::max(1, std::min(a.nitems, 65535));
+    const int T = nsweeps == 3 ? 28 : 32, nt = (n + T - 1) / T;
+    return (long long)nt * nt * count >= 256 ? T : 16;
+}
+
+hipError_t launch_tile2d(int mode, int st, bool vc, int nsweeps, bool finest, const MarchArgs &a, const LevelDesc &L,
+                         hipStream_t s)
+{
+    if (a.nitems < 1 || a.W != a.Hb || (a.W != 16 && a.W != (nsweeps == 3 ? 28 : 32))) return hipErrorInvalidValue;
+    const int fin = finest ? 1 : 0;
     switch (st) {
-    case ST_F64: return vc ? tile_typed<double, double, true>(mode, a, nsweeps, grid, s)
-                           : tile_typed<double, double, false>(mode, a, nsweeps, grid, s);
-    case ST_F32: return vc ? tile_typed<float, float, true>(mode, a, nsweeps, grid, s)
-                           : tile_typed<float, float, false>(mode, a, nsweeps, grid, s);
-    default: return vc ? tile_typed<bf16_t, float, true>(mode, a, nsweeps, grid, s)
-                       : tile_typed<bf16_t, float, false>(mode, a, nsweeps, grid, s);
+    case ST_F64: return vc ? tile_typed<double, double, true>(mode, fin, nsweeps, a, L, s)
+                           : tile_typed<double, double, false>(mode, fin, nsweeps, a, L, s);
+    case ST_F32: return vc ? tile_typed<float, float, true>(mode, fin, nsweeps, a, L, s)
+                           : tile_typed<float, float, false>(mode, fin, nsweeps, a, L, s);
+    default: return vc ? tile_typed<bf16_t, float, true>(mode, fin, nsweeps, a, L, s)
+                       : tile_typed<bf16_t, float, false>(mode, fin, nsweeps, a, L, s);
     }
 }
 

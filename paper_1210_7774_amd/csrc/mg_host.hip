@@ -873,14 +873,12 @@ mg_status enqueue_march(mg_handle_s *h, const Group &g, bool post, hipStream_t s
     a.part0 = h->d_part0;
     a.nparts = h->d_nparts;
     if (g.tiled) {
-        if (g.nitems > 0 && h->nsys == 1) {
-            // one level: tiles from the workgroup index, the level's descriptor alone
-            a.levels = (keep ? h->d_descs_keep : h->d_descs) + h->items[g.item0].lvl;
-            a.items = nullptr;
-        }
+        // one level: tiles from the workgroup index, the descriptor in the arguments
+        if (h->nsys == 1) a.items = nullptr;
+        const LevelDesc &L = (keep ? h->descs_keep : h->descs)[h->items[g.item0].lvl];
         const int pi = prof_begin(h, lvname(post ? "post_tile" : "pre_tile", g.n), post ? g.bytes_post : g.bytes_pre,
                                   st);
-        HIPCHK(h, launch_tile2d(post ? 1 : 0, h->st, h->vc, post ? h->opt.nu2 : h->opt.nu1, a, st));
+        HIPCHK(h, launch_tile2d(post ? 1 : 0, h->st, h->vc, post ? h->opt.nu2 : h->opt.nu1, g.finest, a, L, st));
         prof_end(h, pi, st);
         return MG_OK;
     }
@@ -1466,18 +1464,18 @@ mg_status build_schedule(mg_handle_s *h)
         g.G = env_int("MGX_G", 1);
         if (h->vc) g.G = 1;
         g.W = march_strip_width(g.G, nsweep);
-        // small levels that hold no system's finest level: LDS tiles
         bool has_finest = false;
         for (auto &S : h->sys)
             if (S.lt > 0 && S.lv[0].march && S.lv[0].n == n) has_finest = true;
-        g.tiled = !has_finest && n <= env_int("MGX_TILE_MAX", 1023);
-        if (g.tiled) g.W = 32;
-        const int strips = (n + g.W - 1) / g.W;
-        // block height: enough work items to fill the device, even, 8..256
         int count = 0;
         for (auto &S : h->sys)
             for (int l = 0; l < S.lt; ++l)
                 if (S.lv[l].march && S.lv[l].n == n) ++count;
+        g.tiled = n <= env_int("MGX_TILE_MAX", 1023);
+        const int edge = tile2d_edge(n, count, nsweep);
+        if (g.tiled) g.W = edge;
+        const int strips = (n + g.W - 1) / g.W;
+        // block height: enough work items to fill the device, even, 8..256
         bool any_finest = false;
         for (auto &S : h->sys)
             if (S.lt > 0 && S.lv[0].n == n) any_finest = true;
@@ -1489,15 +1487,16 @@ mg_status build_schedule(mg_handle_s *h)
         hb = env_int("MGX_HB", hb);
         if (hb < 2) hb = 2;
         hb &= ~1;
-        if (g.tiled) hb = 32;
-        // an autotuned (or caller-set) shape for this size replaces the heuristic
+        if (g.tiled) hb = edge;
+        // an autotuned (or caller-set) shape for this size replaces the
+        // heuristic (a size that holds a finest level keeps its form, and
+        // takes the block height when it marches)
         for (auto &t : h->tune) {
             if (t.first != n) continue;
-            const bool can_tile = !has_finest && h->dim == 2;
-            g.tiled = t.second.second != 0 && can_tile;
+            if (!has_finest) g.tiled = t.second.second != 0;
             if (g.tiled) {
-                g.W = 32;
-                hb = 32;
+                g.W = edge;
+                hb = edge;
             } else {
                 g.W = march_strip_width(g.G, nsweep);
                 hb = std::max(2, std::min(256, t.second.first)) & ~1;
@@ -1992,6 +1991,25 @@ extern "C" mg_status mg_solve(mg_handle h, double *u, const double *f, double rt
 
 // ---- level operations on the finest level (FP64 handles) ------------------
 
+namespace {
+
+// A tiled finest level's PRE / POST on the caller's arrays (single systems).
+mg_status tiled_level_op(mg_handle_s *h, const Group &g, int mode, int nsweeps, const LevelDesc &d)
+{
+    MarchArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.nitems = g.nitems;
+    a.W = g.W;
+    a.Hb = g.Hb;
+    a.states = h->d_states;
+    a.partials = h->d_partials;
+    HIPCHK(h, launch_tile2d(mode, h->st, h->vc, nsweeps, true, a, d, h->stream));
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    return MG_OK;
+}
+
+}  // namespace
+
 extern "C" mg_status mg_smooth_restrict(mg_handle h, const double *u, const double *f, double *u_out, double *fc)
 {
     if (!h || h->batch || !u || !f || !u_out || !fc) return MG_ERR_ARG;
@@ -2014,12 +2032,13 @@ extern "C" mg_status mg_smooth_restrict(mg_handle h, const double *u, const doub
         d.A = u_out;
         d.B = (void *)u;
         d.uzero = 0;
-        LevelDesc *dd = nullptr;
-        HIPCHK(h, hipMalloc((void **)&dd, sizeof(LevelDesc)));
-        HIPCHK(h, hipMemcpy(dd, &d, sizeof(d), hipMemcpyHostToDevice));
         const Group *grp = nullptr;
         for (auto &g : h->groups)
             if (g.n == S.n) grp = &g;
+        if (grp->tiled) return tiled_level_op(h, *grp, 0, h->opt.nu1, d);
+        LevelDesc *dd = nullptr;
+        HIPCHK(h, hipMalloc((void **)&dd, sizeof(LevelDesc)));
+        HIPCHK(h, hipMemcpy(dd, &d, sizeof(d), hipMemcpyHostToDevice));
         MarchArgs a;
         std::memset(&a, 0, sizeof(a));
         std::vector<MarchItem> its(h->items.begin() + grp->item0, h->items.begin() + grp->item0 + grp->nitems);
@@ -2091,12 +2110,13 @@ extern "C" mg_status mg_correct_smooth(mg_handle h, const double *u, const doubl
     if (S.lv[0].march) {
         d.A = (void *)u;
         d.B = u_out;
-        LevelDesc *dd = nullptr;
-        HIPCHK(h, hipMalloc((void **)&dd, sizeof(LevelDesc)));
-        HIPCHK(h, hipMemcpy(dd, &d, sizeof(d), hipMemcpyHostToDevice));
         const Group *grp = nullptr;
         for (auto &g : h->groups)
             if (g.n == S.n) grp = &g;
+        if (grp->tiled) return tiled_level_op(h, *grp, 1, h->opt.nu2, d);
+        LevelDesc *dd = nullptr;
+        HIPCHK(h, hipMalloc((void **)&dd, sizeof(LevelDesc)));
+        HIPCHK(h, hipMemcpy(dd, &d, sizeof(d), hipMemcpyHostToDevice));
         std::vector<MarchItem> its(h->items.begin() + grp->item0, h->items.begin() + grp->item0 + grp->nitems);
         for (auto &it : its) it.lvl = 0;
         MarchItem *di = nullptr;
@@ -2341,7 +2361,12 @@ mg_status autotune_impl(mg_handle_s *h, int reps)
     const bool prof = h->prof;
     h->prof = false;
     std::vector<std::pair<int, bool>> sizes;  // (n, holds a finest level)
-    for (auto &g : h->groups) sizes.push_back({g.n, g.finest});
+    std::vector<int> fixed;                   // finest levels on tiles: one shape, nothing to time
+    for (auto &g : h->groups) {
+        if (g.finest && g.tiled) fixed.push_back(g.n);
+        else sizes.push_back({g.n, g.finest});
+    }
+    for (int n : fixed) tune_put(h, n, 32, 0);
     for (auto &sz : sizes) {
         const int n = sz.first;
         std::vector<std::pair<int, int>> cands;
