@@ -1094,6 +1094,14 @@ mg_status enqueue_tail(mg_handle_s *h, hipStream_t st, int list)
     }
     const double tb = (double)h->nsys * level_points(h->tail_top, h->dim) * (h->fs + state_bytes(h->st));
     const int pi = prof_begin(h, "tail", tb, st);
+    // the 2D red-black V-cycle has a register-resident form (the others --
+    // W / F schedules, Jacobi, a 1-point coarsest grid -- run level by level
+    // in LDS: 11.8 us against 29 for 63 .. 3 in FP64)
+    if (list < 0 && h->dim == 2 && t.smoother == 0 && tail2d_supported(h->st, h->vc, h->tail_top, h->tail_m)) {
+        HIPCHK(h, launch_tail2d(h->st, h->vc, t, h->tail_descs[0], st));
+        prof_end(h, pi, st);
+        return MG_OK;
+    }
     HIPCHK(h, launch_tail_sized(h->st, h->vc, h->dim, t, h->tail_lds, h->tail_threads, st));
     prof_end(h, pi, st);
     return MG_OK;

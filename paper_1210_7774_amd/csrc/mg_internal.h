@@ -238,6 +238,10 @@ enum TailOp {
     TAIL_OP_RESTRICT_RHS = 5,  // f_{l+1} = R f_l, u_{l+1} = 0 (full multigrid)
     TAIL_OP_INTERP = 6,        // u_l = P u_{l+1} (full multigrid)
 };
+// The 2D red-black V-cycle tail (k_tail2d.hip) for the given top level and m
+// coarsest unknowns; L: the top level's descriptor (used when a.nsys == 1).
+bool tail2d_supported(int st, bool vc, int n_top, int m);
+hipError_t launch_tail2d(int st, bool vc, const TailArgs &a, const LevelDesc &L, hipStream_t s);
 hipError_t tail_prepare(int st, bool vc, int dim);
 hipError_t launch_tail_sized(int st, bool vc, int dim, const TailArgs &a, size_t lds, int threads, hipStream_t s);
 // Dynamic LDS of the tail (levels n_top and below); faces adds the face tables.
