@@ -1,5 +1,6 @@
 // Wavefront 3D level passes: one or two red-black Gauss-Seidel sweeps of the
-// 7-point Poisson operator per pass over a 32 x 32 column tile, with the
+// 7-point Poisson operator per pass over a column tile (32 x 32, smaller on the
+// small levels), with the
 // operations next to them in the cycle fused in front (zero start, trilinear
 // coarse-grid correction) and behind (residual + full-weighting restriction,
 // or the residual's squared norm, or adding the result into an FP64 iterate).
@@ -38,18 +39,6 @@
 #include "dev_common.h"
 #include "mg_m3.h"
 
-#ifndef MGX_W3_PD
-#define MGX_W3_PD 1
-#endif
-#ifndef MGX_W3_PD_CORR
-#define MGX_W3_PD_CORR 1
-#endif
-#ifndef MGX_W3_ONEBAR
-#define MGX_W3_ONEBAR 1  // one barrier per step (every stage's LDS inputs come from earlier steps)
-#endif
-#ifndef MGX_W3_RESREG
-#define MGX_W3_RESREG 1  // two sweeps: the residual's plane and the one below from registers (1) or LDS (0)
-#endif
 
 namespace mgx {
 
@@ -64,10 +53,11 @@ __device__ __forceinline__ void w3_static_for(Fn &&fn)
     w3_static_for_impl(std::make_integer_sequence<int, N>{}, fn);
 }
 
-// Geometry of a pass with NS sweeps and the given tail.
-template <int NS, int TAIL>
+// Geometry of a pass with NS sweeps and the given tail over tiles of T x T
+// owned columns.
+template <int NS, int TAIL, int T_>
 struct W3Geo {
-    static constexpr int T = 32;  // owned tile edge (columns)
+    static constexpr int T = T_;
     // halo: 2 per sweep, + 2 for residual + restriction (the restriction reads
     // the residual one point around the tile), + 1 for the norm
     static constexpr int R = 2 * NS + (TAIL == M3_TAIL_RR ? 2 : TAIL == M3_TAIL_NORM ? 1 : 0);
@@ -79,10 +69,10 @@ struct W3Geo {
     static_assert(LX % 2 == 0, "pairs of columns");
 };
 
-template <class S, class F, int NS, int HEAD, int TAIL>
-__global__ __launch_bounds__((W3Geo<NS, TAIL>::NT)) void k_march3dw(M3Args a)
+template <class S, class F, int NS, int HEAD, int TAIL, int T, bool ACC>
+__global__ __launch_bounds__((W3Geo<NS, TAIL, T>::NT)) void k_march3dw(M3Args a)
 {
-    using G = W3Geo<NS, TAIL>;
+    using G = W3Geo<NS, TAIL, T>;
     using Tr = Traits<S>;
     using C = typename Tr::C;
     constexpr int TT = G::T, R = G::R, LX = G::LX, LY = G::LY, PX = G::PX, NP = G::NP, NT = G::NT;
@@ -92,8 +82,12 @@ __global__ __launch_bounds__((W3Geo<NS, TAIL>::NT)) void k_march3dw(M3Args a)
     constexpr int NRP = TAIL == M3_TAIL_RR ? RX * RX + 1 : 1;  // + a spare element
     constexpr int KCX = LX / 2 + 3, NKC = HEAD == M3_HEAD_CORR ? KCX * KCX : 1;
     constexpr int QC = (NKC + NT - 1) / NT;
-    // planes of loads in flight (one with the correction's registers)
-    constexpr int PD = HEAD == M3_HEAD_CORR ? MGX_W3_PD_CORR : MGX_W3_PD;
+    // registers to spare (FP64 values at 1024 threads fill the 128 a thread has)
+    constexpr bool ROOMY = T < 32 || sizeof(C) == 4;
+    // planes of loads in flight (more where the registers allow; a second one
+    // in FP64 at edge 32 spills, and the small levels' steps are bound by LDS
+    // round trips, not by these loads)
+    constexpr int PD = ROOMY ? 2 : 1;
     constexpr int CN = TT / 2;                      // coarse points per tile edge (RR)
     constexpr uint32_t SB = sizeof(S), FB = sizeof(F);
     // residual margin: the tile + 1 (RR) or the tile (NORM)
@@ -101,7 +95,7 @@ __global__ __launch_bounds__((W3Geo<NS, TAIL>::NT)) void k_march3dw(M3Args a)
     static_assert(TAIL != M3_TAIL_RR || CN * CN <= NT, "one coarse point per thread");
 
     __shared__ C U[DL * PLN];
-    __shared__ C Rp[MGX_W3_ONEBAR ? 2 : 1][NRP];  // (two planes: written and read in one phase)
+    __shared__ C Rp[2][NRP];  // (two planes: one written, one read per step)
     __shared__ C Kc[HEAD == M3_HEAD_CORR ? 3 * NKC : 1];
     __shared__ double wsum[NT / 64];
 
@@ -148,8 +142,8 @@ __global__ __launch_bounds__((W3Geo<NS, TAIL>::NT)) void k_march3dw(M3Args a)
         return ok ? (uint32_t)((long long)(i - 1) + (long long)(j - 1) * pitch) * es : kOOB;
     };
     // (adding into an FP64 iterate is the refinement's, whose inner cycles
-    // keep a 4- or 2-byte state; the launcher rejects it for an FP64 state)
-    const bool use_acc = sizeof(S) < 8 && a.acc != nullptr;
+    // keep a 4- or 2-byte state)
+    constexpr bool use_acc = ACC;
     const uint32_t OB = use_acc ? 8u : SB;
     const long long opitch = use_acc ? a.accp : a.op, oppitch = use_acc ? a.accpp : a.opp;
     uint32_t uo[2], fo[2], so[2];
@@ -326,28 +320,29 @@ __global__ __launch_bounds__((W3Geo<NS, TAIL>::NT)) void k_march3dw(M3Args a)
         load_f(z0 + 1 + d, pf[(1 + d) % PD]);
     }
 
-    // one Gauss-Seidel update of the class-c point of the plane in LDS slot
-    // `pl`, its vertical neighbours zm / zp and partner from the registers
-    // (in x the partner is added first: the order of the two x neighbours
-    // then differs from the unfused kernels' by the point's side in the pair,
-    // a rounding-level difference)
-    auto gs = [&](const C *pl, int c, C fv, C partner, C zm, C zp) -> C {
-        const C xo = pl[xn[c]];
-        const C ym = pl[yb[c]], yp = pl[yb[c] + 2 * PX];
+    // the three in-plane neighbours of the class-c point that the thread does
+    // not own, from the plane in LDS slot `pl`
+    struct Nb {
+        C x, m, p;
+    };
+    auto nbr = [&](const C *pl, int c) { return Nb{pl[xn[c]], pl[yb[c]], pl[yb[c] + 2 * PX]}; };
+    // one Gauss-Seidel update: partner and vertical neighbours zm / zp from the
+    // registers (in x the partner is added first: the order of the two x
+    // neighbours then differs from the unfused kernels' by the point's side in
+    // the pair, a rounding-level difference)
+    auto gs = [&](const Nb &q, C fv, C partner, C zm, C zp) -> C {
         C s = h2 * fv;
         s = s + partner;
-        s = s + xo;
-        s = s + ym;
-        s = s + yp;
+        s = s + q.x;
+        s = s + q.m;
+        s = s + q.p;
         s = s + zm;
         s = s + zp;
         return Tr::rnd(s * (C)(1.0 / 6.0));
     };
-    auto resid = [&](const C *pl, int c, C fv, C cen, C partner, C zm, C zp) -> C {
-        const C xo = pl[xn[c]];
-        const C ym = pl[yb[c]], yp = pl[yb[c] + 2 * PX];
-        C sa = (cen - partner) + (cen - xo);
-        sa = (sa + (cen - ym)) + (cen - yp);
+    auto resid = [&](const Nb &q, C fv, C cen, C partner, C zm, C zp) -> C {
+        C sa = (cen - partner) + (cen - q.x);
+        sa = (sa + (cen - q.m)) + (cen - q.p);
         sa = (sa + (cen - zm)) + (cen - zp);
         return fv - sa * ih2;
     };
@@ -419,26 +414,18 @@ __global__ __launch_bounds__((W3Geo<NS, TAIL>::NT)) void k_march3dw(M3Args a)
             }
         }
         __syncthreads();
-        // ---- A: red stages; restriction of the residual plane of the last step
-        {
-            constexpr int c = d & 1;  // the red class of plane z (z0 is even)
-            const int ok = z >= lo(1) && z <= hi(1) ? 1 : LX;  // (a margin no point has)
-            C *pl = U + ls(0) * PLN;
-            const C v = gs(pl, c, fr[ri(0)][c], ur[ri(0)][1 - c], ur[ri(-1)][c], ur[ri(1)][c]);
-            ur[ri(0)][c] = dm[c] >= ok ? v : ur[ri(0)][c];
-            pl[me[c]] = ur[ri(0)][c];
-        }
-        if constexpr (NS == 2) {
-            constexpr int c = (d + 1) & 1;  // the red class of plane z - 3
-            const int q = z - 3;
-            const int ok = q >= lo(3) && q <= hi(3) ? 3 : LX;
-            C *pl = U + ls(-3) * PLN;
-            const C zm = U[ls(-4) * PLN + me[c]];  // (plane z - 4 from LDS: fewer live registers)
-            const C v = gs(pl, c, fr[ri(-3)][c], ur[ri(-3)][1 - c], zm, ur[ri(-2)][c]);
-            ur[ri(-3)][c] = dm[c] >= ok ? v : ur[ri(-3)][c];
-            pl[me[c]] = ur[ri(-3)][c];
-        }
-        if constexpr (TAIL == M3_TAIL_RR) {
+        // Every LDS read of the step is of a value from an earlier step.  With
+        // registers to spare (ROOMY) all of them are issued here and the step's
+        // own LDS writes come at its end, so the stages' round trips overlap
+        // (a read cannot be moved above a write the compiler cannot tell apart
+        // from it); FP64 values at 1024 threads keep each stage's reads and
+        // writes together (hoisted they spill 17 to 60 registers: 838 -> 1718 us
+        // for a 511^3 pass).
+        constexpr int ca = d & 1;        // red class of plane z, black class of plane z - 1
+        constexpr int cb = (d + 1) & 1;  // red class of plane z - 3, black class of plane z - 4
+        constexpr bool TWO = NS == 2;
+        // ---- restriction of the residual plane of the last step
+        auto restriction = [&]() {
             const int zr = z - LR - 1;
             if (has_coarse && zr >= rlo && zr <= rhi) {
                 // residual plane zr is oz = 0 of coarse plane zr / 2 (even zr), or
@@ -453,7 +440,7 @@ __global__ __launch_bounds__((W3Geo<NS, TAIL>::NT)) void k_march3dw(M3Args a)
 #pragma unroll
                         for (int ox = -1; ox <= 1; ++ox) {
                             const int wt = (2 - (ox < 0 ? -ox : ox)) * (2 - (oy < 0 ? -oy : oy));
-                            s = s + ((C)wt * wz) * Rp[MGX_W3_ONEBAR ? (d + 1) & 1 : 0][rp_index(rx + ox, ry + oy)];
+                            s = s + ((C)wt * wz) * Rp[(d + 1) & 1][rp_index(rx + ox, ry + oy)];
                         }
                     return s;
                 };
@@ -477,27 +464,54 @@ __global__ __launch_bounds__((W3Geo<NS, TAIL>::NT)) void k_march3dw(M3Args a)
                     else cacc1 = tz;
                 }
             }
+        };
+        Nb a1, b1, a2{}, b2{}, rn[2] = {};
+        if constexpr (ROOMY) {
+            a1 = nbr(U + ls(0) * PLN, ca);
+            if constexpr (TWO) a2 = nbr(U + ls(-3) * PLN, cb);
+            b1 = nbr(U + ls(-1) * PLN, ca);
+            if constexpr (TWO) b2 = nbr(U + ls(-4) * PLN, cb);
+            if constexpr (TAIL != M3_TAIL_NONE) {
+                rn[0] = nbr(U + ls(-LR) * PLN, 0);
+                rn[1] = nbr(U + ls(-LR) * PLN, 1);
+            }
         }
-        if constexpr (!MGX_W3_ONEBAR) __syncthreads();
-        // ---- B: black stages, the store of the final plane, the residual
+        // ---- red of sweep 1 on plane z, of sweep 2 on plane z - 3
         {
-            constexpr int c = d & 1;  // the black class of plane z - 1
+            const int ok = z >= lo(1) && z <= hi(1) ? 1 : LX;  // (a margin no point has)
+            if constexpr (!ROOMY) a1 = nbr(U + ls(0) * PLN, ca);
+            const C v = gs(a1, fr[ri(0)][ca], ur[ri(0)][1 - ca], ur[ri(-1)][ca], ur[ri(1)][ca]);
+            ur[ri(0)][ca] = dm[ca] >= ok ? v : ur[ri(0)][ca];
+            if constexpr (!ROOMY) U[ls(0) * PLN + me[ca]] = ur[ri(0)][ca];
+        }
+        if constexpr (TWO) {
+            const int q = z - 3;
+            const int ok = q >= lo(3) && q <= hi(3) ? 3 : LX;
+            if constexpr (!ROOMY) a2 = nbr(U + ls(-3) * PLN, cb);
+            // (FP64 at 1024 threads: the plane below from LDS, fewer live registers)
+            const C zm = ROOMY ? ur[ri(-4)][cb] : U[ls(-4) * PLN + me[cb]];
+            const C v = gs(a2, fr[ri(-3)][cb], ur[ri(-3)][1 - cb], zm, ur[ri(-2)][cb]);
+            ur[ri(-3)][cb] = dm[cb] >= ok ? v : ur[ri(-3)][cb];
+            if constexpr (!ROOMY) U[ls(-3) * PLN + me[cb]] = ur[ri(-3)][cb];
+        }
+        if constexpr (TAIL == M3_TAIL_RR && !ROOMY) restriction();
+        // ---- black of sweep 1 on plane z - 1, of sweep 2 on plane z - 4
+        {
             const int q = z - 1;
             const int ok = q >= lo(2) && q <= hi(2) ? 2 : LX;
-            C *pl = U + ls(-1) * PLN;
-            const C v = gs(pl, c, fr[ri(-1)][c], ur[ri(-1)][1 - c], ur[ri(-2)][c], ur[ri(0)][c]);
-            ur[ri(-1)][c] = dm[c] >= ok ? v : ur[ri(-1)][c];
-            pl[me[c]] = ur[ri(-1)][c];
+            if constexpr (!ROOMY) b1 = nbr(U + ls(-1) * PLN, ca);
+            const C v = gs(b1, fr[ri(-1)][ca], ur[ri(-1)][1 - ca], ur[ri(-2)][ca], ur[ri(0)][ca]);
+            ur[ri(-1)][ca] = dm[ca] >= ok ? v : ur[ri(-1)][ca];
+            if constexpr (!ROOMY) U[ls(-1) * PLN + me[ca]] = ur[ri(-1)][ca];
         }
-        if constexpr (NS == 2) {
-            constexpr int c = (d + 1) & 1;  // the black class of plane z - 4
+        if constexpr (TWO) {
             const int q = z - 4;
             const int ok = q >= lo(4) && q <= hi(4) ? 4 : LX;
-            C *pl = U + ls(-4) * PLN;
-            const C zm = U[ls(-5) * PLN + me[c]];
-            const C v = gs(pl, c, fr[ri(-4)][c], ur[ri(-4)][1 - c], zm, ur[ri(-3)][c]);
-            ur[ri(-4)][c] = dm[c] >= ok ? v : ur[ri(-4)][c];
-            pl[me[c]] = ur[ri(-4)][c];
+            if constexpr (!ROOMY) b2 = nbr(U + ls(-4) * PLN, cb);
+            const C zm = ROOMY ? ur[ri(-5)][cb] : U[ls(-5) * PLN + me[cb]];
+            const C v = gs(b2, fr[ri(-4)][cb], ur[ri(-4)][1 - cb], zm, ur[ri(-3)][cb]);
+            ur[ri(-4)][cb] = dm[cb] >= ok ? v : ur[ri(-4)][cb];
+            if constexpr (!ROOMY) U[ls(-4) * PLN + me[cb]] = ur[ri(-4)][cb];
         }
         {
             // plane z - LB is final: store the owned points
@@ -508,41 +522,50 @@ __global__ __launch_bounds__((W3Geo<NS, TAIL>::NT)) void k_march3dw(M3Args a)
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
                 const C v = ur[ri(-LB)][c];
-                if (use_acc) bst(ro, so[c], ap[c] + (double)v);
+                if constexpr (use_acc) bst(ro, so[c], ap[c] + (double)v);
                 else Tr::bstore(ro, so[c], v);
             }
             onext += opb;
-            if (use_acc) {
+            if constexpr (use_acc) {
                 const bool ok1 = q + 1 >= k0 && q + 1 < k1 && q + 1 >= 1 && q + 1 <= n;
                 const rsrc_t r1 = make_rsrc(onext, ok1 ? ext_o : 0u);
                 ap[0] = bld<double>(r1, so[0]);
                 ap[1] = bld<double>(r1, so[1]);
             }
         }
+        // ---- residual of plane z - LR
+        C res[2] = {(C)0, (C)0};
         if constexpr (TAIL != M3_TAIL_NONE) {
             const int q = z - LR;
             const int ok = q >= rlo && q <= rhi ? MRES : LX;
-            {
-                const C *pl = U + ls(-LR) * PLN;
 #pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    // two sweeps: the plane and the one below from LDS, or the
-                    // one below only (the correction pass: fewest spilled
-                    // registers), or neither (from the registers)
-                    constexpr bool lds = NS == 2 && !MGX_W3_RESREG;
-                    constexpr bool lzm = NS == 2 && (lds || HEAD == M3_HEAD_CORR);
-                    const C cen = lds ? pl[me[c]] : ur[ri(-LR)][c];
-                    const C prt = lds ? pl[me[1 - c]] : ur[ri(-LR)][1 - c];
-                    const C zm = lzm ? U[ls(-LR - 1) * PLN + me[c]] : ur[ri(-LR - 1)][c];
-                    const C r = resid(pl, c, fr[ri(-LR)][c], cen, prt, zm, ur[ri(-LR + 1)][c]);
-                    if constexpr (TAIL == M3_TAIL_RR) {
-                        Rp[MGX_W3_ONEBAR ? d & 1 : 0][rpi[c]] = dm[c] >= ok ? r : (C)0;
-                    } else {
-                        const double rd = (double)r;
-                        nacc += dm[c] >= ok ? rd * rd : 0.0;
-                    }
+            for (int c = 0; c < 2; ++c) {
+                if constexpr (!ROOMY) rn[c] = nbr(U + ls(-LR) * PLN, c);
+                // (the FP64 correction pass: the plane below from LDS, fewest spilled registers)
+                constexpr bool lzm = TWO && !ROOMY && HEAD == M3_HEAD_CORR;
+                const C zm = lzm ? U[ls(-LR - 1) * PLN + me[c]] : ur[ri(-LR - 1)][c];
+                const C r = resid(rn[c], fr[ri(-LR)][c], ur[ri(-LR)][c], ur[ri(-LR)][1 - c], zm, ur[ri(-LR + 1)][c]);
+                if constexpr (TAIL == M3_TAIL_RR) {
+                    if constexpr (ROOMY) res[c] = dm[c] >= ok ? r : (C)0;
+                    else Rp[d & 1][rpi[c]] = dm[c] >= ok ? r : (C)0;
+                } else {
+                    const double rd = (double)r;
+                    nacc += dm[c] >= ok ? rd * rd : 0.0;
                 }
             }
+        }
+        if constexpr (ROOMY) {
+            U[ls(0) * PLN + me[ca]] = ur[ri(0)][ca];
+            U[ls(-1) * PLN + me[ca]] = ur[ri(-1)][ca];
+            if constexpr (TWO) {
+                U[ls(-3) * PLN + me[cb]] = ur[ri(-3)][cb];
+                U[ls(-4) * PLN + me[cb]] = ur[ri(-4)][cb];
+            }
+            if constexpr (TAIL == M3_TAIL_RR) {
+                Rp[d & 1][rpi[0]] = res[0];
+                Rp[d & 1][rpi[1]] = res[1];
+            }
+            if constexpr (TAIL == M3_TAIL_RR) restriction();
         }
       });
     }
@@ -559,13 +582,27 @@ __global__ __launch_bounds__((W3Geo<NS, TAIL>::NT)) void k_march3dw(M3Args a)
     }
 }
 
+// Tile edge of a level: 32, and smaller where 32 x 32 columns leave the chip
+// mostly idle: there a pass is a chain of steps (planes plus twice the halo
+// plus the stage lags) whose length hardly depends on the tile, and a step is
+// the shorter the fewer wavefronts share a CU's issue slots and barrier (16 at
+// edge 32, 7 at 16, 4 at 8), although the halo is recomputed more often.  PRE /
+// POST, edge 32 with the stages' LDS reads one after another, then as here:
+// 31^3 FP32 16.1 / 14.2 -> 10.1 / 9.0 us, FP64 19.6 / 15.5 -> 13.0 / 10.3 us;
+// 63^3 FP32 16.4 / 15.0 -> 12.7 / 11.5 us, FP64 20.0 / 16.8 -> 17.2 / 13.9 us.
+// (127^3 FP32, edge 32 both times: 24.6 / 27.3 -> 24.0 / 24.8 us.)
+static int w3_edge(int n)
+{
+    return n <= 31 ? 8 : n <= 63 ? 16 : 32;
+}
+
 // planes per run: one run per tile column when the level has at least 256
 // tiles (one workgroup per CU), else shorter runs so that a launch has about
 // 256 workgroups; runs are an even number of planes (coarse planes then never
 // straddle two runs' restriction ownership)
 static int w3_kz(int n)
 {
-    const int nt = (n + 31) / 32;
+    const int nt = (n + w3_edge(n) - 1) / w3_edge(n);
     const int tiles = nt * nt;
     const int runs = std::max(1, 256 / tiles);
     int kz = (n + runs - 1) / runs;
@@ -575,38 +612,46 @@ static int w3_kz(int n)
 
 int march3dw_blocks(int n)
 {
-    const int nt = (n + 31) / 32;
+    const int nt = (n + w3_edge(n) - 1) / w3_edge(n);
     const int kz = w3_kz(n);
     return nt * nt * ((n + kz - 1) / kz);
 }
 
-template <class S, class F, int NS, int HEAD, int TAIL>
-static void w3_go(const M3Args &a, dim3 grid, hipStream_t s)
+template <class S, class F, int NS, int HEAD, int TAIL, bool ACC = false>
+static hipError_t w3_go(const M3Args &a, dim3 grid, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_march3dw<S, F, NS, HEAD, TAIL>), grid, dim3(W3Geo<NS, TAIL>::NT), 0, s, a);
+    switch (w3_edge(a.n)) {
+    case 8:
+        hipLaunchKernelGGL((k_march3dw<S, F, NS, HEAD, TAIL, 8, ACC>), grid, dim3(W3Geo<NS, TAIL, 8>::NT), 0, s, a);
+        break;
+    case 16:
+        hipLaunchKernelGGL((k_march3dw<S, F, NS, HEAD, TAIL, 16, ACC>), grid, dim3(W3Geo<NS, TAIL, 16>::NT), 0, s, a);
+        break;
+    default:
+        hipLaunchKernelGGL((k_march3dw<S, F, NS, HEAD, TAIL, 32, ACC>), grid, dim3(W3Geo<NS, TAIL, 32>::NT), 0, s, a);
+    }
+    return hipGetLastError();
 }
 
 template <class S, class F, int NS, int HEAD>
 static hipError_t w3_tail(int tail, const M3Args &a, dim3 grid, hipStream_t s)
 {
     switch (tail) {
-    case M3_TAIL_NONE: w3_go<S, F, NS, HEAD, M3_TAIL_NONE>(a, grid, s); break;
+    case M3_TAIL_NONE:
+        if constexpr (sizeof(S) < 8 && HEAD != M3_HEAD_ZERO) {
+            if (a.acc) return w3_go<S, F, NS, HEAD, M3_TAIL_NONE, true>(a, grid, s);
+        }
+        if (a.acc) return hipErrorInvalidValue;
+        return w3_go<S, F, NS, HEAD, M3_TAIL_NONE>(a, grid, s);
     case M3_TAIL_RR:
         // (the cycle never restricts right after a correction)
-        if constexpr (HEAD != M3_HEAD_CORR) {
-            w3_go<S, F, NS, HEAD, M3_TAIL_RR>(a, grid, s);
-            break;
-        }
+        if constexpr (HEAD != M3_HEAD_CORR) return w3_go<S, F, NS, HEAD, M3_TAIL_RR>(a, grid, s);
         return hipErrorInvalidValue;
     case M3_TAIL_NORM:
-        if constexpr (sizeof(S) == 8) {
-            w3_go<S, F, NS, HEAD, M3_TAIL_NORM>(a, grid, s);
-            break;
-        }
+        if constexpr (sizeof(S) == 8) return w3_go<S, F, NS, HEAD, M3_TAIL_NORM>(a, grid, s);
         return hipErrorInvalidValue;
-    default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 template <class S, class F, int NS>
@@ -631,9 +676,9 @@ static hipError_t w3_ns(int ns, int head, int tail, const M3Args &a, dim3 grid, 
 hipError_t launch_march3dw(int st, int ns, int head, int tail, const M3Args &in, hipStream_t s)
 {
     M3Args a = in;
-    if (st == ST_F64 && a.acc) return hipErrorInvalidValue;
+    if (a.acc && (st == ST_F64 || tail != M3_TAIL_NONE)) return hipErrorInvalidValue;
     a.kz = w3_kz(a.n);
-    a.ntx = a.nty = (a.n + 31) / 32;
+    a.ntx = a.nty = (a.n + w3_edge(a.n) - 1) / w3_edge(a.n);
     a.ntz = (a.n + a.kz - 1) / a.kz;
     const long long nb = (long long)a.ntx * a.nty * a.ntz;
     if (nb < 1 || nb > 0x7fffffffLL - 8) return hipErrorInvalidValue;
