@@ -1102,6 +1102,12 @@ mg_status enqueue_tail(mg_handle_s *h, hipStream_t st, int list)
         prof_end(h, pi, st);
         return MG_OK;
     }
+    // and so has the 3D one (15 .. 3, FP64: 14.1 us against 35)
+    if (list < 0 && h->dim == 3 && t.smoother == 0 && tail3d_supported(h->tail_top, h->tail_m)) {
+        HIPCHK(h, launch_tail3d(h->st, t, h->tail_descs[0], st));
+        prof_end(h, pi, st);
+        return MG_OK;
+    }
     HIPCHK(h, launch_tail_sized(h->st, h->vc, h->dim, t, h->tail_lds, h->tail_threads, st));
     prof_end(h, pi, st);
     return MG_OK;

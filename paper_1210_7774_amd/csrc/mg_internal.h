@@ -242,6 +242,9 @@ enum TailOp {
 // coarsest unknowns; L: the top level's descriptor (used when a.nsys == 1).
 bool tail2d_supported(int st, bool vc, int n_top, int m);
 hipError_t launch_tail2d(int st, bool vc, const TailArgs &a, const LevelDesc &L, hipStream_t s);
+// The 3D one (k_tail3d.hip).
+bool tail3d_supported(int n_top, int m);
+hipError_t launch_tail3d(int st, const TailArgs &a, const LevelDesc &L, hipStream_t s);
 hipError_t tail_prepare(int st, bool vc, int dim);
 hipError_t launch_tail_sized(int st, bool vc, int dim, const TailArgs &a, size_t lds, int threads, hipStream_t s);
 // Dynamic LDS of the tail (levels n_top and below); faces adds the face tables.
