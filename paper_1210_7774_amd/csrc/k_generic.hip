@@ -491,27 +491,11 @@ __global__ __launch_bounds__(256) void k_copy_state(GenArgs g, const S *src, S *
     }
 }
 
-// ---- FP64 residual norm (+ optional r32 / r64 output) and stop test ------------
-template <int DIM, bool VC>
-__global__ __launch_bounds__(256) void k_norm(NormArgs g)
+// ---- FP64 residual norm (+ optional r32 / r64 output) -----------------------------
+// (the finish kernel that follows reduces the block partials)
+// The block's sums of a 256-thread workgroup into its partial slot.
+__device__ __forceinline__ void norm_block_sum(double rr, double ff, double *partials, int slot)
 {
-    if (!g.first && g.state->done) return;
-    Idx<DIM> x{g.n, g.pitch, g.ppitch};
-    // (the finish kernel that follows reduces the block partials)
-    const long long m = npts(g.n, DIM);
-    double rr = 0.0, ff = 0.0;
-    for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < m; p += (long long)gridDim.x * blockDim.x) {
-        int i, j, k;
-        coords(p, g.n, DIM, i, j, k);
-        const long long o = x.off(i, j, k);
-        const double fv = g.f[o];
-        const double r = fv - apply_pt<double, DIM, VC>(g.u, g.a, x, g.inv_h2, i, j, k);
-        rr += r * r;
-        ff += fv * fv;
-        // contiguous interior outputs
-        if (g.r32) g.r32[p] = (float)r;
-        if (g.r64) g.r64[p] = r;
-    }
     __shared__ double srr[4], sff[4];
     rr = wave_sum(rr);
     ff = wave_sum(ff);
@@ -521,21 +505,147 @@ __global__ __launch_bounds__(256) void k_norm(NormArgs g)
         sff[w] = ff;
     }
     __syncthreads();
-    if (threadIdx.x < 64) {
-        double a = 0.0, b = 0.0;
-        for (int q = 0; q < (int)(blockDim.x >> 6); ++q) {
-            a += srr[q];
-            b += sff[q];
-        }
-        put_partial(g.partials, blockIdx.x, a, b);
+    if (threadIdx.x < 64) put_partial(partials, slot, ((srr[0] + srr[1]) + srr[2]) + srr[3],
+                                      ((sff[0] + sff[1]) + sff[2]) + sff[3]);
+}
+
+__global__ __launch_bounds__(256) void k_norm1(NormArgs g)
+{
+    if (!g.first && g.state->done) return;
+    Idx<1> x{g.n, g.pitch, g.ppitch};
+    double rr = 0.0, ff = 0.0;
+    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < g.n; p += gridDim.x * blockDim.x) {
+        const double fv = g.f[p];
+        const double r = fv - apply_pt<double, 1, false>(g.u, g.a, x, g.inv_h2, p + 1, 1, 1);
+        rr += r * r;
+        ff += fv * fv;
+        if (g.r32) g.r32[p] = (float)r;
+        if (g.r64) g.r64[p] = r;
     }
+    norm_block_sum(rr, ff, g.partials, blockIdx.x);
+}
+
+// 2D: one wavefront takes kNormRows rows of 64 columns and marches down them.
+// u, f and the coefficient are loaded once per point (the x neighbours are the
+// adjacent lanes', the y neighbours the rows before and after; lanes 0 and 63
+// also load the column beside the strip), and a face mean is computed once:
+// the west face is the left lane's east face, the south face the previous
+// row's north face.  Bandwidth bound for many systems; the thread-per-point
+// form it replaces spent itself on four FP64 divisions and ten cache loads a
+// point: 1023^2 diffusion 11.2 -> 9.9 us, 48 systems of 13.7 M unknowns
+// 155 -> 88 us (all active).
+// HASU false: the zero iterate (r = f), the same sums in the same order.
+constexpr int kNormRows = 8;
+template <bool VC, bool HASU>
+__device__ __forceinline__ void norm2_unit(const double *u, const double *f, const double *a, int n, long long pitch,
+                                           double ih2, int ic, int j0, float *r32, double *r64, double &rr, double &ff)
+{
+    constexpr int B = 4;  // rows per round of loads
+    const int lane = threadIdx.x & 63;
+    const int i = ic + lane;                                   // this lane's column
+    const bool cin = i <= n;
+    const int ie = lane == 0 ? ic - 1 : ic + 64;               // the column beside the strip (lanes 0, 63)
+    const bool ein = (lane == 0 || lane == 63) && ie >= 1 && ie <= n;
+    const int j1 = min(j0 + kNormRows, n + 1);
+    auto row = [&](int j, double &c, double &e) {
+        const bool ok = HASU && j >= 1 && j <= n;
+        c = ok && cin ? gld(u + (long long)(j - 1) * pitch + (i - 1)) : 0.0;
+        e = ok && ein ? gld(u + (long long)(j - 1) * pitch + (ie - 1)) : 0.0;
+    };
+    const int ia = min(i, n + 1), iae = min(ic + 64, n + 1);
+    auto arow = [&](int j, double &c, double &e) {
+        const long long o = (long long)min(j, n + 1) * (n + 2);
+        c = gld(a + o + ia);
+        e = lane == 63 ? gld(a + o + iae) : 0.0;
+    };
+    double us = 0.0, uc = 0.0, ue = 0.0, t = 0.0;  // the row before, the row, its side column
+    row(j0 - 1, us, t);
+    row(j0, uc, ue);
+    double ac = 1.0, ae = 0.0, ws = 0.0;
+    if constexpr (VC && HASU) {
+        double as, ase;
+        arow(j0 - 1, as, ase);
+        arow(j0, ac, ae);
+        ws = harm(as, ac);
+    }
+    for (int j = j0; j < j1; j += B) {
+        double un[B], une[B], fv[B], an[B], ane[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            row(j + k + 1, un[k], une[k]);
+            fv[k] = cin && j + k <= n ? gld(f + (long long)(j + k - 1) * pitch + (i - 1)) : 0.0;
+            if constexpr (VC && HASU) arow(j + k + 1, an[k], ane[k]);
+        }
+        // the strip's west faces of the round's rows, one a lane
+        double wl = 0.0;
+        if constexpr (VC && HASU) {
+            const long long o = (long long)min(j + (lane & (B - 1)), n + 1) * (n + 2) + ic;
+            wl = harm(gld(a + o - 1), gld(a + o));
+        }
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            if (j + k >= j1) break;
+            const double w = from_prev(uc, ue), e = from_next(uc, ue);
+            double s = 0.0;
+            if constexpr (!HASU) {
+            } else if constexpr (!VC) {
+                s = (uc - w) + (uc - e);
+                s = (s + (uc - us)) + (uc - un[k]);
+            } else {
+                const double we = harm(ac, from_next(ac, ae)), ww = from_prev(we, lane_value(wl, k));
+                const double wn = harm(ac, an[k]);
+                s = ((ww * (uc - w) + we * (uc - e)) + ws * (uc - us)) + wn * (uc - un[k]);
+                ws = wn;
+                ac = an[k];
+                ae = ane[k];
+            }
+            const double r = cin ? fv[k] - s * ih2 : 0.0;
+            rr += r * r;
+            ff += fv[k] * fv[k];
+            // contiguous interior outputs
+            const long long p = (long long)(j + k - 1) * n + (i - 1);
+            if (cin && r32) gst(r32 + p, (float)r);
+            if (cin && r64) gst(r64 + p, r);
+            us = uc;
+            uc = un[k];
+            ue = une[k];
+        }
+    }
+}
+
+template <bool VC, bool HASU>
+__global__ __launch_bounds__(256) void k_norm2(NormArgs g)
+{
+    if (!g.first && g.state->done) return;
+    const int nsx = (g.n + 63) / 64, nunits = nsx * ((g.n + kNormRows - 1) / kNormRows);
+    double rr = 0.0, ff = 0.0;
+    for (int t = blockIdx.x * 4 + (threadIdx.x >> 6); t < nunits; t += gridDim.x * 4)
+        norm2_unit<VC, HASU>(g.u, g.f, g.a, g.n, g.pitch, g.inv_h2, 1 + 64 * (t % nsx), 1 + kNormRows * (t / nsx), g.r32,
+                       g.r64, rr, ff);
+    norm_block_sum(rr, ff, g.partials, blockIdx.x);
+}
+
+// Work items of the batched norm: four strips of kNormRows rows of a system.
+int norm_batch_items(int n) { return ((n + 255) / 256) * ((n + kNormRows - 1) / kNormRows); }
+void norm_batch_item(int n, int q, NormItem &it)
+{
+    const int nx = (n + 255) / 256;
+    it.i0 = 1 + 256 * (q % nx);
+    it.j0 = 1 + kNormRows * (q / nx);
+}
+int norm2_blocks(int n)
+{
+    const long long units = (long long)((n + 63) / 64) * ((n + kNormRows - 1) / kNormRows);
+    return (int)std::min<long long>((units + 3) / 4, 2048);
 }
 
 // ---- 3D FP64 residual norm: each thread marches one column up a run of 32
 // planes keeping u(k - 1), u(k), u(k + 1) in registers, so every array is
 // streamed once (the in-plane neighbours come from the cache); work units of
-// 64 x 4 columns x 32 planes are dealt to the blocks in a fixed order
-template <int RUN>
+// 64 x 4 columns x RUN planes are dealt to the blocks in a fixed order.  32
+// planes a unit, 8 up to 255 points an edge, where longer runs leave the chip
+// waiting on a few columns (127^3 with the FP32 rhs written: 22.8 -> 13.4 us)
+template <int RUN, bool HASU>
 __global__ __launch_bounds__(256) void k_norm3(NormArgs g)
 {
     if (!g.first && g.state->done) return;
@@ -548,7 +658,7 @@ __global__ __launch_bounds__(256) void k_norm3(NormArgs g)
     const double *u = g.u;
     double rr = 0.0, ff = 0.0;
     auto U = [&](int i, int j, int k) -> double {
-        return (u && i >= 1 && i <= n && j >= 1 && j <= n && k >= 1 && k <= n) ? u[x.off(i, j, k)] : 0.0;
+        return (HASU && i >= 1 && i <= n && j >= 1 && j <= n && k >= 1 && k <= n) ? u[x.off(i, j, k)] : 0.0;
     };
     for (long long un = blockIdx.x; un < nunits; un += gridDim.x) {
         const int i = (int)(un % ntx) * 64 + tx + 1, j = (int)((un / ntx) % nty) * 4 + ty + 1;
@@ -573,64 +683,24 @@ __global__ __launch_bounds__(256) void k_norm3(NormArgs g)
             c = up;
         }
     }
-    __shared__ double srr[4], sff[4];
-    rr = wave_sum(rr);
-    ff = wave_sum(ff);
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        srr[w] = rr;
-        sff[w] = ff;
-    }
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        double a = 0.0, b = 0.0;
-        for (int q = 0; q < (int)(blockDim.x >> 6); ++q) {
-            a += srr[q];
-            b += sff[q];
-        }
-        put_partial(g.partials, blockIdx.x, a, b);
-    }
+    norm_block_sum(rr, ff, g.partials, blockIdx.x);
 }
 
-// ---- batched FP64 residual (2D), one block per chunk of rows of one system ----
+// ---- batched FP64 residual (2D): a block per item, a wavefront per strip ------
 __global__ __launch_bounds__(256) void k_norm_batch(const NormItem *items, const NormSys *sys, SolveState *states,
                                                     double *partials, int flags)
 {
     const NormItem it = items[blockIdx.x];
     const NormSys S = sys[it.sys];
-    const int first = flags & 1;
-    if (!first && states[it.sys].done) return;
-    Idx<2> x{S.n, S.pitch, 0};
+    if (!(flags & 1) && states[it.sys].done) return;
     double rr = 0.0, ff = 0.0;
-    const long long cnt = (long long)(it.j1 - it.j0) * S.n;
-    for (long long q = threadIdx.x; q < cnt; q += blockDim.x) {
-        const int i = (int)(q % S.n) + 1, j = it.j0 + (int)(q / S.n);
-        const long long o = x.off(i, j, 1);
-        const double fv = S.f[o];
-        const double au = S.a ? apply_pt<double, 2, true>(S.u, S.a, x, S.inv_h2, i, j, 1)
-                              : apply_pt<double, 2, false>(S.u, S.a, x, S.inv_h2, i, j, 1);
-        const double r = fv - au;
-        rr += r * r;
-        ff += fv * fv;
-        if (flags & 2) S.r32[(long long)(j - 1) * S.n + (i - 1)] = (float)r;
+    const int ic = it.i0 + 64 * (int)(threadIdx.x >> 6);
+    float *r32 = (flags & 2) ? S.r32 : nullptr;
+    if (ic <= S.n) {
+        if (S.a) norm2_unit<true, true>(S.u, S.f, S.a, S.n, S.pitch, S.inv_h2, ic, it.j0, r32, nullptr, rr, ff);
+        else norm2_unit<false, true>(S.u, S.f, S.a, S.n, S.pitch, S.inv_h2, ic, it.j0, r32, nullptr, rr, ff);
     }
-    __shared__ double srr[4], sff[4];
-    rr = wave_sum(rr);
-    ff = wave_sum(ff);
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        srr[w] = rr;
-        sff[w] = ff;
-    }
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        double a = 0.0, b = 0.0;
-        for (int q = 0; q < (int)(blockDim.x >> 6); ++q) {
-            a += srr[q];
-            b += sff[q];
-        }
-        put_partial(partials, it.slot, a, b);
-    }
+    norm_block_sum(rr, ff, partials, it.slot);
 }
 
 hipError_t launch_norm_batch(const NormItem *items, int nitems, const NormSys *sys, SolveState *states,
@@ -641,66 +711,83 @@ hipError_t launch_norm_batch(const NormItem *items, int nitems, const NormSys *s
     return hipGetLastError();
 }
 
-// ---- reduction of the partial sums + stop test: one wavefront per system ----
+// ---- reduction of the partial sums + stop test: one workgroup per system ----
 // part0 / nparts: per-system slot ranges (device), or null for one system
 // whose slots are [slot0, slot0 + nslots).
-__global__ __launch_bounds__(64) void k_norm_finish(SolveState *states, const double *partials, const int *part0,
-                                                    const int *nparts, int slot0, int nslots, int first)
+// A few hundred numbers: the launch and one round of loads.  Everything the
+// kernel reads (partials, state, the whole history) is loaded at once, one
+// value a thread; a single wavefront that walked the history in a loop took 4.5
+// to 6.4 us of every cycle, this form 3.8 to 4.8.
+__global__ __launch_bounds__(256) void k_norm_finish(SolveState *states, const double *partials, const int *part0,
+                                                     const int *nparts, int slot0, int nslots, int first)
 {
-    const int sys = blockIdx.x;
+    __shared__ double srr[4], sff[4], smn[4], shist[256];
+    const int sys = blockIdx.x, tid = threadIdx.x;
     SolveState *st = states + sys;
-    if (!first && st->done) return;
-    const int lane = threadIdx.x;
+    const int done0 = st->done, k = first ? 0 : st->nres, maxc = st->maxc;
+    const double tol = st->tol, watch = st->watch, stall = st->stall, ff0 = st->ff;
+    const double h = tid <= 200 ? st->hist[tid] : 0.0;
     const int p0 = part0 ? part0[sys] : slot0;
     const int np = nparts ? nparts[sys] : nslots;
-    double srr = 0.0, sff = 0.0;
-    // eight loads in flight per lane; the sums keep the order k, k + 64, ...
-    for (int k0 = lane; k0 < np; k0 += 64 * 8) {
-        double vr[8], vf[8];
+    double rr = 0.0, ff = 0.0;
+    // four loads in flight per thread; thread t adds slots t, t + 256, ...
+    for (int q0 = tid; q0 < np; q0 += 256 * 4) {
+        double vr[4], vf[4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int k = k0 + 64 * j;
-            const int kk = k < np ? k : k0;
-            vr[j] = partials[2 * (p0 + kk)];
-            vf[j] = partials[2 * (p0 + kk) + 1];
+        for (int j = 0; j < 4; ++j) {
+            const int q = q0 + 256 * j;
+            vr[j] = q < np ? partials[2 * (p0 + q)] : 0.0;
+            vf[j] = q < np ? partials[2 * (p0 + q) + 1] : 0.0;
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (k0 + 64 * j < np) {
-                srr += vr[j];
-                sff += vf[j];
-            }
+        for (int j = 0; j < 4; ++j) {
+            rr += vr[j];
+            ff += vf[j];
         }
     }
-    srr = wave_sum(srr);
-    sff = wave_sum(sff);
-    if (lane != 0) return;
-    if (first) {
-        st->ff = sff;
-        st->nres = 0;
+    if (!first && done0) return;
+    rr = wave_sum(rr);
+    ff = wave_sum(ff);
+    double mn = tid < k ? h : __builtin_inf();  // smallest of hist[0 .. k - 1]
+    for (int o = 32; o > 0; o >>= 1) {
+        const double x = __shfl_xor(mn, o, 64);
+        mn = x < mn ? x : mn;
     }
-    const double rel = sqrt(srr) / sqrt(st->ff);
-    const int k = st->nres;
+    shist[tid] = h;
+    if ((tid & 63) == 0) {
+        srr[tid >> 6] = rr;
+        sff[tid >> 6] = ff;
+        smn[tid >> 6] = mn;
+    }
+    __syncthreads();
+    if (tid != 0) return;
+    rr = ((srr[0] + srr[1]) + srr[2]) + srr[3];
+    ff = first ? ((sff[0] + sff[1]) + sff[2]) + sff[3] : ff0;
+    for (int q = 1; q < 4; ++q) smn[0] = smn[q] < smn[0] ? smn[q] : smn[0];
+    const double rel = sqrt(rr) / sqrt(ff);
+    if (first) st->ff = ff;
     if (k <= 200) st->hist[k] = rel;
     st->rel = rel;
     st->nres = k + 1;
     int done = 0;
     if (!isfinite(rel)) done = 2;
-    else if (rel <= st->tol) done = 1;
-    else if (k >= 1 && st->watch > 0.0 && !(rel <= st->watch * st->hist[k - 1])) done = 4;
+    else if (rel <= tol) done = 1;
+    else if (k >= 1 && watch > 0.0 && !(rel <= watch * shist[k - 1])) done = 4;
     else if (k <= 200) {
-        const int rule = history_rule(st->hist, k + 1, st->stall);
+        const double last[4] = {rel, k >= 1 ? shist[k - 1] : 0.0, k >= 2 ? shist[k - 2] : 0.0,
+                                k >= 3 ? shist[k - 3] : 0.0};
+        const int rule = history_rule_of(last, k, rel < smn[0] ? rel : smn[0], stall);
         if (rule == 2) done = 6;
         else if (rule == 1) done = 5;
     }
-    if (done == 0 && k >= st->maxc) done = 3;
+    if (done == 0 && k >= maxc) done = 3;
     st->done = done;
 }
 
 hipError_t launch_norm_finish(SolveState *states, int nsys, const double *partials, const int *part0,
                               const int *nparts, int slot0, int nslots, int first, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_norm_finish, dim3(nsys), dim3(64), 0, s, states, partials, part0, nparts, slot0, nslots,
+    hipLaunchKernelGGL(k_norm_finish, dim3(nsys), dim3(256), 0, s, states, partials, part0, nparts, slot0, nslots,
                        first);
     return hipGetLastError();
 }
@@ -945,12 +1032,21 @@ hipError_t launch_norm(const NormArgs &a, hipStream_t s)
     const int grid = a.nblocks;
     const bool vc = a.a != nullptr;
     switch (a.dim) {
-    case 1: hipLaunchKernelGGL((k_norm<1, false>), dim3(grid), dim3(256), 0, s, a); break;
+    case 1: hipLaunchKernelGGL(k_norm1, dim3(grid), dim3(256), 0, s, a); break;
     case 2:
-        if (vc) hipLaunchKernelGGL((k_norm<2, true>), dim3(grid), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((k_norm<2, false>), dim3(grid), dim3(256), 0, s, a);
+        if (!a.u) hipLaunchKernelGGL((k_norm2<false, false>), dim3(grid), dim3(256), 0, s, a);
+        else if (vc) hipLaunchKernelGGL((k_norm2<true, true>), dim3(grid), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((k_norm2<false, true>), dim3(grid), dim3(256), 0, s, a);
         break;
-    case 3: hipLaunchKernelGGL((k_norm3<32>), dim3(grid), dim3(256), 0, s, a); break;
+    case 3:
+        if (a.n <= 255) {
+            if (a.u) hipLaunchKernelGGL((k_norm3<8, true>), dim3(grid), dim3(256), 0, s, a);
+            else hipLaunchKernelGGL((k_norm3<8, false>), dim3(grid), dim3(256), 0, s, a);
+        } else {
+            if (a.u) hipLaunchKernelGGL((k_norm3<32, true>), dim3(grid), dim3(256), 0, s, a);
+            else hipLaunchKernelGGL((k_norm3<32, false>), dim3(grid), dim3(256), 0, s, a);
+        }
+        break;
     }
     return hipGetLastError();
 }

@@ -434,7 +434,8 @@ size_t carve(mg_handle_s *h, char *base)
         }
     }
     size_t nni0 = 0;
-    for (auto &S : h->sys) nni0 += (S.n + 15) / 16;
+    if (h->batch)
+        for (auto &S : h->sys) nni0 += norm_batch_items(S.n);
     nparts = std::max(nparts, nni0);
     nparts = std::max(nparts, (size_t)8192);
     if (h->dim == 3) {
@@ -466,7 +467,8 @@ size_t carve(mg_handle_s *h, char *base)
     h->d_nnparts = (int *)cv.take(sizeof(int) * nsys);
     h->d_nsys = (NormSys *)cv.take(sizeof(NormSys) * nsys);
     size_t nni = 0;
-    for (auto &S : h->sys) nni += (S.n + 15) / 16;
+    if (h->batch)
+        for (auto &S : h->sys) nni += norm_batch_items(S.n);
     h->d_nitems = (NormItem *)cv.take(sizeof(NormItem) * std::max<size_t>(nni, 1));
     h->d_flag = (int *)cv.take(sizeof(int) * 4);
     {
@@ -1571,7 +1573,7 @@ mg_status build_schedule(mg_handle_s *h)
         h->sys[s].part0 = part0[s];
         h->sys[s].nparts = nparts[s];
     }
-    // batched outer-norm items: rows in chunks of 16
+    // batched outer-norm items
     h->nitemv.clear();
     h->nsysv.assign(h->nsys, NormSys());
     int slot = 0;
@@ -1585,8 +1587,9 @@ mg_status build_schedule(mg_handle_s *h)
         ns.a = h->vc ? S.a64 : nullptr;
         ns.r32 = S.r32;
         ns.part0 = slot;
-        for (int j0 = 1; j0 <= S.n; j0 += 16) {
-            NormItem it{s, j0, std::min(j0 + 16, S.n + 1), slot++};
+        for (int q = 0; h->batch && q < norm_batch_items(S.n); ++q) {
+            NormItem it{s, 0, 0, slot++};
+            norm_batch_item(S.n, q, it);
             h->nitemv.push_back(it);
         }
         ns.nparts = slot - ns.part0;
@@ -1632,6 +1635,7 @@ mg_status setup_common(mg_handle_s *h, const std::vector<int> &ns, const mg_grid
     {
         const long long m = level_points(h->sys[0].n, h->dim);
         h->norm_blocks = (int)std::min<long long>(std::max<long long>((m + 255) / 256, 1), 2048);
+        if (h->dim == 2) h->norm_blocks = norm2_blocks(h->sys[0].n);
         h->norm_blocks = std::min(h->norm_blocks, h->npartials);
     }
     HIPCHK(h, tail_prepare(h->st, h->vc, h->dim));

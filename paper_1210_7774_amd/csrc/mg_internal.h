@@ -40,18 +40,24 @@ struct SolveState {
 //     the last two steps each reduced the residual by less than 1 / stall;
 //   0 otherwise.
 constexpr double kDivergeGrowth = 1e3;
+// The rules from what they read of the history: last[q] = hist[k - q] (q <= 3,
+// q <= k) and the smallest value of hist[0 .. k].
+__host__ __device__ inline int history_rule_of(const double *last, int k, double smallest, double stall)
+{
+    if (!(last[0] - last[0] == 0.0)) return 2;  // NaN or infinite
+    if (last[0] > kDivergeGrowth * smallest) return 2;
+    if (k >= 4 && last[0] > last[1] && last[1] > last[2] && last[2] > last[3]) return 2;
+    if (stall > 0.0 && k >= 3 && last[0] > stall * last[1] && last[1] > stall * last[2]) return 1;
+    return 0;
+}
 __host__ __device__ inline int history_rule(const double *hist, int nres, double stall)
 {
     if (!hist || nres < 1) return 0;
     const int k = nres - 1;
-    const double last = hist[k];
-    if (!(last - last == 0.0)) return 2;  // NaN or infinite
-    double mn = hist[0];
+    double mn = hist[0], last[4] = {0.0, 0.0, 0.0, 0.0};
     for (int i = 1; i <= k; ++i) mn = hist[i] < mn ? hist[i] : mn;
-    if (last > kDivergeGrowth * mn) return 2;
-    if (k >= 4 && hist[k] > hist[k - 1] && hist[k - 1] > hist[k - 2] && hist[k - 2] > hist[k - 3]) return 2;
-    if (stall > 0.0 && k >= 3 && hist[k] > stall * hist[k - 1] && hist[k - 1] > stall * hist[k - 2]) return 1;
-    return 0;
+    for (int q = 0; q <= 3 && q <= k; ++q) last[q] = hist[k - q];
+    return history_rule_of(last, k, mn, stall);
 }
 
 // One grid level of one system as the kernels see it.  Arrays are
@@ -254,7 +260,7 @@ size_t tail_max_lds();  // the largest dynamic LDS a tail launch may use
 hipError_t launch_ir_correct(int st, double *u, long long pitch, long long ppitch, const void *e, int n, int dim,
                              SolveState *state, hipStream_t s);
 
-// Batched FP64 residual (2D): work items are row chunks of one system.
+// Batched FP64 residual (2D): work items are blocks of one system.
 struct NormSys {
     int n;
     int part0, nparts;
@@ -265,8 +271,11 @@ struct NormSys {
     float *r32;
 };
 struct NormItem {
-    int sys, j0, j1, slot;
+    int sys, i0, j0, slot;  // first column and row of the item
 };
+int norm_batch_items(int n);                       // items of an n x n system
+void norm_batch_item(int n, int q, NormItem &it);  // the q-th one's i0, j0
+int norm2_blocks(int n);                           // blocks of the single-system 2D norm
 // flags: bit 0 = first norm of a solve (also measures ||f||), bit 1 = write r32
 hipError_t launch_norm_batch(const NormItem *items, int nitems, const NormSys *sys, SolveState *states,
                              double *partials, int flags, hipStream_t s);
