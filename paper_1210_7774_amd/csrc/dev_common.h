@@ -39,6 +39,23 @@ __device__ __forceinline__ void gst(T *p, T v)
     *(__attribute__((address_space(1))) T *)p = v;
 }
 
+// A value that is the same in every lane, moved to scalar registers: what was
+// loaded through a work item sits in vector registers, and a buffer descriptor
+// built from it would be applied in a loop over its distinct lane values
+// (about 12 instructions per access).
+template <class T>
+__device__ __forceinline__ T uniform(const T &v)
+{
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    struct W {
+        int w[sizeof(T) / 4];
+    };
+    W x = __builtin_bit_cast(W, v);
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(T) / 4); ++k) x.w[k] = __builtin_amdgcn_readfirstlane(x.w[k]);
+    return __builtin_bit_cast(T, x);
+}
+
 // ---- buffer (resource-descriptor) memory access ---------------------------
 // A raw buffer load whose byte offset lies beyond the descriptor's record
 // count returns 0 and such a store is dropped, so masked lanes and rows need
@@ -118,6 +135,25 @@ __device__ __forceinline__ int dpp_from_prev(int x, int edge)
 __device__ __forceinline__ int dpp_from_next(int x, int edge)
 {
     return __builtin_amdgcn_update_dpp(edge, x, 0x130, 0xf, 0xf, false);
+}
+// (edge value 0: the shift's own bound control writes the zero)
+__device__ __forceinline__ int dpp_from_prev0(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x138, 0xf, 0xf, true); }
+__device__ __forceinline__ int dpp_from_next0(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x130, 0xf, 0xf, true); }
+__device__ __forceinline__ float from_prev(float x) { return __int_as_float(dpp_from_prev0(__float_as_int(x))); }
+__device__ __forceinline__ float from_next(float x) { return __int_as_float(dpp_from_next0(__float_as_int(x))); }
+__device__ __forceinline__ double from_prev(double x)
+{
+    int2 v = __builtin_bit_cast(int2, x);
+    v.x = dpp_from_prev0(v.x);
+    v.y = dpp_from_prev0(v.y);
+    return __builtin_bit_cast(double, v);
+}
+__device__ __forceinline__ double from_next(double x)
+{
+    int2 v = __builtin_bit_cast(int2, x);
+    v.x = dpp_from_next0(v.x);
+    v.y = dpp_from_next0(v.y);
+    return __builtin_bit_cast(double, v);
 }
 __device__ __forceinline__ float from_prev(float x, float edge)
 {

@@ -107,8 +107,8 @@ __global__ __launch_bounds__((TileGeo<S, MODE, NS, T, FIN>::NT)) void k_tile2d(M
         wi.ja = 1 + T * (item / tiles_x);
         wi.part = item;
     } else {
-        wi = args.items[item];
-        L = args.levels[wi.lvl];
+        wi = uniform(args.items[item]);
+        L = uniform(args.levels[wi.lvl]);
     }
     // the stop flag is tested once the region's loads are issued (the same
     // value for the whole workgroup)

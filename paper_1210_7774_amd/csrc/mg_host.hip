@@ -1487,19 +1487,31 @@ mg_status build_schedule(mg_handle_s *h)
         for (auto &S : h->sys)
             for (int l = 0; l < S.lt; ++l)
                 if (S.lv[l].march && S.lv[l].n == n) ++count;
-        g.tiled = n <= env_int("MGX_TILE_MAX", 1023);
+        // LDS tiles where a launch is latency (a tile is one chain of about
+        // 5 us, a marched block one of its rows), marching where it is
+        // throughput (a marched point takes 0.4x the vector instructions: one
+        // halo column in twelve instead of half the region).  Up to 3072 tiles
+        // of 32 x 32, three rounds of the chip: one 1023^2 FP32 diffusion solve
+        // 1340 us tiled, 1450 marched; 32 levels of 255^2 in a batch 8.9 / 9.2 ms;
+        // one 2047^2 FP64 pass 37 / 27 us; 22 levels of 511^2 9.6 / 8.9 ms.
+        const long long t32 = (n + 31) / 32;
+        g.tiled = n <= env_int("MGX_TILE_MAX", 1 << 30) && t32 * t32 * count <= 3072;
         const int edge = tile2d_edge(n, count, nsweep);
         if (g.tiled) g.W = edge;
         const int strips = (n + g.W - 1) / g.W;
-        // block height: enough work items to fill the device, even, 8..256
-        bool any_finest = false;
-        for (auto &S : h->sys)
-            if (S.lt > 0 && S.lv[0].n == n) any_finest = true;
-        const int target = any_finest ? env_int("MGX_TARGET_ITEMS", 2048)
-                                      : env_int("MGX_TARGET_ITEMS_COARSE", env_int("MGX_TARGET_ITEMS", 2048));
-        const int min_hb = env_int("MGX_MIN_HB", 4);
-        int hb = 256;
-        while (hb > std::max(4, min_hb) && (long long)strips * ((n + hb - 1) / hb) * count < target) hb /= 2;
+        // Block height: a block marches hb rows plus about 12 of halo and lag,
+        // all blocks at once, each step as long as a fixed latency plus the
+        // issue and memory time of the wavefronts that share the SIMD.  With w =
+        // rows of all strips per SIMD, (hb + 12)(t0 + w / hb t1) is least at hb =
+        // sqrt(12 w t1 / t0).  5.5 sqrt(w) fits the measured optimum of finest
+        // levels (4095^2 FP64: flat from 60 to 80 rows, 3 % more at 128, 10 % at
+        // 16; 2047^2: 40, 4 % of the solve more at 16), 3 sqrt(w) that of levels
+        // below one, which read no state (2047^2 under 4095^2, both passes: 59 us
+        // at 16, 64 at 40, 78 at 74).  A batch's systems drop out as they
+        // converge: half of them on average.
+        const double rows = (double)strips * n * count / 1024.0 / (h->nsys > 1 ? 2.0 : 1.0);
+        const int hb_fit = (int)((has_finest ? 5.5 : 3.0) * std::sqrt(rows)) & ~1;
+        int hb = std::max(std::max(4, env_int("MGX_MIN_HB", 4)), std::min(256, hb_fit));
         hb = env_int("MGX_HB", hb);
         if (hb < 2) hb = 2;
         hb &= ~1;
