@@ -719,13 +719,15 @@ hipError_t launch_norm_batch(const NormItem *items, int nitems, const NormSys *s
 // value a thread; a single wavefront that walked the history in a loop took 4.5
 // to 6.4 us of every cycle, this form 3.8 to 4.8.
 __global__ __launch_bounds__(256) void k_norm_finish(SolveState *states, const double *partials, const int *part0,
-                                                     const int *nparts, int slot0, int nslots, int first)
+                                                     const int *nparts, int slot0, int nslots, int first,
+                                                     StateInit init, SolveState *pub)
 {
     __shared__ double srr[4], sff[4], smn[4], shist[256];
     const int sys = blockIdx.x, tid = threadIdx.x;
     SolveState *st = states + sys;
-    const int done0 = st->done, k = first ? 0 : st->nres, maxc = st->maxc;
-    const double tol = st->tol, watch = st->watch, stall = st->stall, ff0 = st->ff;
+    const int done0 = st->done, k = first ? 0 : st->nres, maxc = init.on ? init.maxc : st->maxc;
+    const double tol = init.on ? init.tol : st->tol, watch = init.on ? init.watch : st->watch;
+    const double stall = init.on ? init.stall : st->stall, ff0 = st->ff, rel0 = st->rel;
     const double h = tid <= 200 ? st->hist[tid] : 0.0;
     const int p0 = part0 ? part0[sys] : slot0;
     const int np = nparts ? nparts[sys] : nslots;
@@ -745,7 +747,18 @@ __global__ __launch_bounds__(256) void k_norm_finish(SolveState *states, const d
             ff += vf[j];
         }
     }
-    if (!first && done0) return;
+    if (!first && done0) {
+        // stopped earlier: k residuals are recorded
+        if (pub) {
+            if (tid < k && tid <= 200) pub[sys].hist[tid] = h;
+            if (tid == 0) {
+                pub[sys].nres = k;
+                pub[sys].rel = rel0;
+                pub[sys].done = done0;
+            }
+        }
+        return;
+    }
     rr = wave_sum(rr);
     ff = wave_sum(ff);
     double mn = tid < k ? h : __builtin_inf();  // smallest of hist[0 .. k - 1]
@@ -760,6 +773,7 @@ __global__ __launch_bounds__(256) void k_norm_finish(SolveState *states, const d
         smn[tid >> 6] = mn;
     }
     __syncthreads();
+    if (pub && tid > 0 && tid <= k && tid <= 200) pub[sys].hist[tid - 1] = shist[tid - 1];
     if (tid != 0) return;
     rr = ((srr[0] + srr[1]) + srr[2]) + srr[3];
     ff = first ? ((sff[0] + sff[1]) + sff[2]) + sff[3] : ff0;
@@ -782,13 +796,26 @@ __global__ __launch_bounds__(256) void k_norm_finish(SolveState *states, const d
     }
     if (done == 0 && k >= maxc) done = 3;
     st->done = done;
+    if (init.on) {
+        st->maxc = maxc;
+        st->tol = tol;
+        st->watch = watch;
+        st->stall = stall;
+    }
+    if (pub) {
+        if (k <= 200) pub[sys].hist[k] = rel;
+        pub[sys].nres = k + 1;
+        pub[sys].rel = rel;
+        pub[sys].done = done;
+    }
 }
 
 hipError_t launch_norm_finish(SolveState *states, int nsys, const double *partials, const int *part0,
-                              const int *nparts, int slot0, int nslots, int first, hipStream_t s)
+                              const int *nparts, int slot0, int nslots, int first, const StateInit &init,
+                              SolveState *pub, hipStream_t s)
 {
     hipLaunchKernelGGL(k_norm_finish, dim3(nsys), dim3(256), 0, s, states, partials, part0, nparts, slot0, nslots,
-                       first);
+                       first, init, pub);
     return hipGetLastError();
 }
 

@@ -128,7 +128,7 @@ __global__ __launch_bounds__((TileGeo<S, MODE, NS, T, FIN>::NT)) void k_tile2d(M
 
     // ---- load the region: clamped addresses, values selected afterwards, so
     // all of a thread's loads are in flight together
-    const bool uzero = MODE == 0 && L.uzero;
+    const bool uzero = MODE == 0 && (L.uzero || args.zero_in);
     C ux[2] = {(C)0, (C)0}, fx[2];
     {
         F a, b;

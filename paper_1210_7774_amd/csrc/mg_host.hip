@@ -188,7 +188,10 @@ struct mg_handle_s {
     hipGraphExec_t gexec = nullptr;
     hipGraph_t graph = nullptr;
     bool graph_ok = false;
-    bool first_zero = false;  // enqueueing a zero-start solve's first step (fused 3D path)
+    bool first_zero = false;  // enqueueing a zero-start solve's first step
+    bool publish = false;     // the norms being enqueued also write the host's copy of the states
+    SolveState *d_pub = nullptr;  // device address of h_states
+    StateInit init{};         // state set by the next first norm (init.on)
 };
 
 #define HIPCHK(h, call)                                                   \
@@ -874,6 +877,7 @@ mg_status enqueue_march(mg_handle_s *h, const Group &g, bool post, hipStream_t s
     a.partials = h->d_partials;
     a.part0 = h->d_part0;
     a.nparts = h->d_nparts;
+    a.zero_in = h->first_zero && !post && h->nsys == 1 && g.n == h->sys[0].n;
     if (g.tiled) {
         // one level: tiles from the workgroup index, the descriptor in the arguments
         if (h->nsys == 1) a.items = nullptr;
@@ -1026,7 +1030,8 @@ mg_status enqueue_m3(mg_handle_s *h, int s, int l, bool post, hipStream_t st, bo
     if (post && l == 0 && m3_norm_fused(h)) {
         const int pi = prof_begin(h, "norm_finish", 0.0, st);
         HIPCHK(h, launch_norm_finish(h->d_states, 1, h->d_partials, nullptr, nullptr, 0,
-                                     wf ? march3dw_blocks(L.n) : march3d_blocks(L.n, M3_TAIL_NORM, h->st), 0, st));
+                                     wf ? march3dw_blocks(L.n) : march3d_blocks(L.n, M3_TAIL_NORM, h->st), 0, StateInit{},
+                                     h->publish ? h->d_pub : nullptr, st));
         prof_end(h, pi, st);
     }
     return MG_OK;
@@ -1120,7 +1125,8 @@ mg_status enqueue_post_norm(mg_handle_s *h, hipStream_t st)
 {
     if (!h->ir && h->sys[0].lv[0].march && h->norm_in_post) {
         const int pi = prof_begin(h, "norm_finish", 0.0, st);
-        HIPCHK(h, launch_norm_finish(h->d_states, h->nsys, h->d_partials, h->d_part0, h->d_nparts, 0, 0, 0, st));
+        HIPCHK(h, launch_norm_finish(h->d_states, h->nsys, h->d_partials, h->d_part0, h->d_nparts, 0, 0, 0, StateInit{},
+                                     h->publish ? h->d_pub : nullptr, st));
         prof_end(h, pi, st);
     }
     return MG_OK;
@@ -1255,7 +1261,8 @@ mg_status enqueue_outer_norm(mg_handle_s *h, int first, bool write_r32, hipStrea
         HIPCHK(h, launch_norm(a, st));
         prof_end(h, pi, st);
         const int pf = prof_begin(h, "norm_finish", 0.0, st);
-        HIPCHK(h, launch_norm_finish(h->d_states, 1, h->d_partials, nullptr, nullptr, 0, h->norm_blocks, first, st));
+        HIPCHK(h, launch_norm_finish(h->d_states, 1, h->d_partials, nullptr, nullptr, 0, h->norm_blocks, first,
+                                     first ? h->init : StateInit{}, h->publish ? h->d_pub : nullptr, st));
         prof_end(h, pf, st);
         return MG_OK;
     }
@@ -1266,7 +1273,8 @@ mg_status enqueue_outer_norm(mg_handle_s *h, int first, bool write_r32, hipStrea
                                 first | (write_r32 ? 2 : 0), st));
     prof_end(h, pi, st);
     const int pf = prof_begin(h, "norm_finish", 0.0, st);
-    HIPCHK(h, launch_norm_finish(h->d_states, h->nsys, h->d_partials, h->d_npart0, h->d_nnparts, 0, 0, first, st));
+    HIPCHK(h, launch_norm_finish(h->d_states, h->nsys, h->d_partials, h->d_npart0, h->d_nnparts, 0, 0, first,
+                                 first ? h->init : StateInit{}, h->publish ? h->d_pub : nullptr, st));
     prof_end(h, pf, st);
     return MG_OK;
 }
@@ -1347,6 +1355,19 @@ mg_status state_init(mg_handle_s *h, double tol, int maxc, hipStream_t st)
     return MG_OK;
 }
 
+// A solve's first residual norm, which also sets the states up (the learned
+// smoother's ratio watch and the bf16-state stall rule as in state_init).
+mg_status enqueue_first_norm(mg_handle_s *h, double tol, int maxc, bool u_zero, bool publish = false)
+{
+    h->init = StateInit{1, maxc, tol, (h->learned && h->learned_on) ? kLearnedFallback : 0.0,
+                        h->st == ST_BF16 && tol >= 0.0 ? bf16_stall_ratio() : 0.0};
+    h->publish = publish;
+    const mg_status rc = enqueue_outer_norm(h, 1, h->ir, h->stream, u_zero);
+    h->publish = false;
+    h->init = StateInit{};
+    return rc;
+}
+
 mg_status build_graph(mg_handle_s *h)
 {
     if (h->gexec) {
@@ -1375,29 +1396,28 @@ mg_status build_graph(mg_handle_s *h)
     return MG_OK;
 }
 
+// k steps; the last one's norm publishes the states to the host (a captured
+// step always does: its replays are alike).
 mg_status enqueue_steps(mg_handle_s *h, int k)
 {
-    if (h->prof) {
-        for (int i = 0; i < k; ++i) {
-            mg_status rc = enqueue_step(h, h->stream);
-            ++h->prof_step;
-            if (rc != MG_OK) return rc;
-        }
-        return MG_OK;
-    }
-    if (h->opt.use_graph) {
+    mg_status rc = MG_OK;
+    if (!h->prof && h->opt.use_graph) {
         if (!h->graph_ok) {
-            mg_status rc = build_graph(h);
+            h->publish = true;
+            rc = build_graph(h);
+            h->publish = false;
             if (rc != MG_OK) return rc;
         }
         for (int i = 0; i < k; ++i) HIPCHK(h, hipGraphLaunch(h->gexec, h->stream));
         return MG_OK;
     }
-    for (int i = 0; i < k; ++i) {
-        mg_status rc = enqueue_step(h, h->stream);
-        if (rc != MG_OK) return rc;
+    for (int i = 0; i < k && rc == MG_OK; ++i) {
+        h->publish = i == k - 1;
+        rc = enqueue_step(h, h->stream);
+        if (h->prof) ++h->prof_step;
     }
-    return MG_OK;
+    h->publish = false;
+    return rc;
 }
 
 mg_status read_states(mg_handle_s *h)
@@ -1692,7 +1712,8 @@ mg_status setup_common(mg_handle_s *h, const std::vector<int> &ns, const mg_grid
     (void)g;
     (void)op;
     (void)ns;
-    HIPCHK(h, hipHostMalloc((void **)&h->h_states, sizeof(SolveState) * h->nsys, hipHostMallocDefault));
+    HIPCHK(h, hipHostMalloc((void **)&h->h_states, sizeof(SolveState) * h->nsys, hipHostMallocMapped));
+    HIPCHK(h, hipHostGetDevicePointer((void **)&h->d_pub, h->h_states, 0));
     HIPCHK(h, hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking));
     return MG_OK;
 }
@@ -1798,44 +1819,47 @@ mg_status solve_loop(mg_handle_s *h, double rtol, std::vector<mg_stats *> stats)
     mg_status rc = refresh(h, true);
     if (rc != MG_OK) return rc;
     const int maxc = h->opt.max_cycles;
-    rc = state_init(h, rtol, maxc, h->stream);
-    if (rc != MG_OK) return rc;
-    // zero start: the u passed in is not read.  The fused 3D plain path
-    // starts its first cycle's finest pre-smoothing from zero (the first
+    // zero start: the u passed in is not read.  The plain paths whose finest
+    // pre-smoothing can start from zero do so in the first cycle (its
     // post-smoothing then writes every point of u); FMG overwrites u anyway;
     // every other path zeroes u first.
     const bool zs = h->opt.zero_start != 0;
-    const bool zs_head = zs && !h->opt.fmg && h->m3 && !h->ir && h->sys[0].lt > 0;
+    const bool zs_head = zs && !h->opt.fmg && !h->ir && h->sys[0].lt > 0 &&
+                         (h->m3 || (h->sys[0].lv[0].march && h->sys[0].pitch0 == h->sys[0].n));
     if (zs && !zs_head && !h->opt.fmg) {
         Sys &S = h->sys[0];
         if (S.pitch0 != S.n || (h->dim == 3 && S.ppitch0 != (long long)S.n * S.n)) return MG_ERR_UNSUPPORTED;
         HIPCHK(h, launch_fill_zero(S.u, (long long)sizeof(double) * level_points(S.n, h->dim), h->stream));
     }
+    // The first norm sets the state up and the first cycles follow it without a
+    // look at it: an initial guess that already meets the tolerance (or is not
+    // finite) has them return at once.
     h->prof_step = -1;
-    rc = enqueue_outer_norm(h, 1, h->ir, h->stream, zs);
+    rc = enqueue_first_norm(h, rtol, maxc, zs);
     if (rc != MG_OK) return rc;
     h->prof_step = 0;
     int enq = 0;
-    if (h->opt.fmg) {
-        // the first step is one full-multigrid pass (enqueued directly, not
-        // part of the captured cycle)
-        rc = enqueue_fmg_step(h, h->stream);
+    int chunk = std::min(2, maxc);
+    if (h->opt.fmg || zs_head) {
+        // the first step is one full-multigrid pass, or a cycle from zero
+        // (enqueued directly, not part of the captured cycle)
+        h->first_zero = zs_head;
+        h->publish = maxc == 1;
+        rc = h->opt.fmg ? enqueue_fmg_step(h, h->stream) : enqueue_step(h, h->stream);
+        h->first_zero = h->publish = false;
         if (rc != MG_OK) return rc;
+        if (h->prof) ++h->prof_step;
         enq = 1;
-    } else if (zs_head) {
-        // the first step from zero (enqueued directly, not part of the
-        // captured cycle)
-        h->first_zero = true;
-        rc = enqueue_step(h, h->stream);
-        h->first_zero = false;
-        if (rc != MG_OK) return rc;
-        enq = 1;
+        chunk = std::min(1, maxc - 1);
     }
-    int chunk = 2;
+    if (chunk > 0) {
+        rc = enqueue_steps(h, chunk);
+        if (rc != MG_OK) return rc;
+        enq += chunk;
+    }
     bool fell_back = false;
     for (;;) {
-        rc = read_states(h);
-        if (rc != MG_OK) return rc;
+        HIPCHK(h, hipStreamSynchronize(h->stream));  // (the last norm wrote h_states)
         bool all_done = true;
         double worst_rho = 0.0, worst_rel = 0.0;
         int kmin = 1 << 30;
@@ -1872,15 +1896,15 @@ mg_status solve_loop(mg_handle_s *h, double rtol, std::vector<mg_stats *> stats)
                         if (S.pitch0 != S.n) return MG_ERR_NONFINITE;
                         HIPCHK(h, launch_fill_zero(S.u, (long long)sizeof(double) * level_points(S.n, h->dim), h->stream));
                     }
-                    rc = state_init(h, rtol, maxc, h->stream);
-                    if (rc != MG_OK) return rc;
-                    rc = enqueue_outer_norm(h, 1, h->ir, h->stream);
+                    rc = enqueue_first_norm(h, rtol, maxc, false, true);
                     if (rc != MG_OK) return rc;
                     enq = 0;
                 } else {
                     hipLaunchKernelGGL(k_state_rearm, dim3((h->nsys + 255) / 256), dim3(256), 0, h->stream,
                                        h->d_states, h->nsys);
                     HIPCHK(h, hipGetLastError());
+                    for (int s = 0; s < h->nsys; ++s)
+                        if (h->h_states[s].done == 4) h->h_states[s].done = 0;
                 }
                 continue;
             }
@@ -1898,6 +1922,8 @@ mg_status solve_loop(mg_handle_s *h, double rtol, std::vector<mg_stats *> stats)
                 hipLaunchKernelGGL(k_state_rearm, dim3((h->nsys + 255) / 256), dim3(256), 0, h->stream, h->d_states,
                                    h->nsys);
                 HIPCHK(h, hipGetLastError());
+                for (int s = 0; s < h->nsys; ++s)
+                    if (h->h_states[s].done == 5) h->h_states[s].done = 0;
                 continue;
             }
         }
@@ -1912,6 +1938,15 @@ mg_status solve_loop(mg_handle_s *h, double rtol, std::vector<mg_stats *> stats)
         if (rc != MG_OK) return rc;
         enq += chunk;
         (void)kmin;
+    }
+    if (zs && (zs_head || h->opt.fmg) && h->h_states[0].nres <= 1) {
+        // stopped by the first norm (a zero or non-finite f, a tolerance of 1
+        // or more): no cycle wrote u
+        Sys &S = h->sys[0];
+        if (S.pitch0 == S.n && (h->dim < 3 || S.ppitch0 == (long long)S.n * S.n)) {
+            HIPCHK(h, launch_fill_zero(S.u, (long long)sizeof(double) * level_points(S.n, h->dim), h->stream));
+            HIPCHK(h, hipStreamSynchronize(h->stream));
+        }
     }
     mg_status worst = MG_OK;
     for (int s = 0; s < h->nsys; ++s) {
@@ -2218,7 +2253,8 @@ extern "C" mg_status mg_residual(mg_handle h, const double *u, const double *f, 
     a.nblocks = h->norm_blocks;
     a.first = 1;
     HIPCHK(h, launch_norm(a, h->stream));
-    HIPCHK(h, launch_norm_finish(h->d_states, 1, h->d_partials, nullptr, nullptr, 0, h->norm_blocks, 1, h->stream));
+    HIPCHK(h, launch_norm_finish(h->d_states, 1, h->d_partials, nullptr, nullptr, 0, h->norm_blocks, 1, StateInit{},
+                                 nullptr, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
     return MG_OK;
 }

@@ -104,6 +104,7 @@ struct MarchArgs {
     double *partials;   // one per item (norm)
     const int *part0;   // per system: first partial slot
     const int *nparts;  // per system: number of partial slots
+    int zero_in;        // PRE: the input state is zero whatever the descriptor says
 };
 
 // ---- launchers (defined in the kernel translation units) -----------------
@@ -215,9 +216,17 @@ struct NormArgs {
     int first;          // 1: this norm also measures ||f||^2 and resets the history
 };
 hipError_t launch_norm(const NormArgs &a, hipStream_t s);
-// Reduce partials + stop test (must follow every norm-producing launch).
+// What a solve's first norm sets in the state (on: the other fields apply).
+struct StateInit {
+    int on, maxc;
+    double tol, watch, stall;
+};
+// Reduce partials + stop test (must follow every norm-producing launch).  pub:
+// host-visible copy of the states, written when not null (done, nres, rel and
+// the history), also for systems that stopped earlier.
 hipError_t launch_norm_finish(SolveState *states, int nsys, const double *partials, const int *part0,
-                              const int *nparts, int slot0, int nslots, int first, hipStream_t s);
+                              const int *nparts, int slot0, int nslots, int first, const StateInit &init,
+                              SolveState *pub, hipStream_t s);
 
 // Coarse-level tail: one workgroup per system runs the whole V-cycle on the
 // levels [lt, L) in LDS, reading f_lt and writing B_lt.
