@@ -1109,6 +1109,13 @@ mg_status enqueue_tail(mg_handle_s *h, hipStream_t st, int list)
         prof_end(h, pi, st);
         return MG_OK;
     }
+    // and a 1D hierarchy that is all tail (1023 .. 1, FP64: 8.7 us a call
+    // against 26.6)
+    if (list < 0 && h->dim == 1 && t.smoother == 0 && h->sys[0].lt == 0 && tail1d_supported(h->tail_top, h->tail_m)) {
+        HIPCHK(h, launch_tail1d(h->st, t, h->tail_descs[0], st));
+        prof_end(h, pi, st);
+        return MG_OK;
+    }
     // and so has the 3D one (15 .. 3, FP64: 14.1 us against 35)
     if (list < 0 && h->dim == 3 && t.smoother == 0 && tail3d_supported(h->tail_top, h->tail_m)) {
         HIPCHK(h, launch_tail3d(h->st, t, h->tail_descs[0], st));
@@ -1812,6 +1819,32 @@ void free_handle(mg_handle_s *h)
     delete h;
 }
 
+// Plain FP64 1D solves whose hierarchy fits one wavefront run in one launch
+// (timed and captured solves keep a launch per operation).
+bool use_solve1d(const mg_handle_s *h)
+{
+    return h->dim == 1 && !h->ir && !h->batch && !h->vc && !h->learned && !h->prof && !h->opt.use_graph && h->opt.smoother == MG_SM_RBGS &&
+           h->opt.cycle == MG_CYCLE_V && !h->opt.fmg && h->sys[0].lt == 0 &&
+           tail1d_supported(h->sys[0].n, h->tail_m);
+}
+
+mg_status solve1d(mg_handle_s *h, double rtol, mg_stats *st)
+{
+    if (!(rtol >= 0.0)) return MG_ERR_ARG;
+    Sys &S = h->sys[0];
+    const int maxc = h->opt.max_cycles, most = 32;  // cycles a launch: bounds its run time
+    const StateInit init{1, maxc, rtol, 0.0, 0.0};
+    for (int enq = 0; enq == 0 || (!h->h_states[0].done && enq < maxc);) {
+        const int k = std::min(most, maxc - enq);
+        HIPCHK(h, launch_solve1d(S.n, S.u, S.f, S.cinv, h->opt.nu1, h->opt.nu2, h->d_states, enq == 0 ? 1 : 0, k,
+                                 enq == 0 && h->opt.zero_start != 0, init, h->d_pub, h->stream));
+        HIPCHK(h, hipStreamSynchronize(h->stream));
+        enq += k;
+    }
+    if (st) fill_stats(h->h_states[0], st, false);
+    return status_of(h->h_states[0]);
+}
+
 // The solve loop shared by single systems and batches.
 mg_status solve_loop(mg_handle_s *h, double rtol, std::vector<mg_stats *> stats)
 {
@@ -2051,6 +2084,7 @@ extern "C" mg_status mg_solve(mg_handle h, double *u, const double *f, double rt
     if (!h || h->batch) return MG_ERR_ARG;
     mg_status rc = bind_call(h, 0, u, f);
     if (rc != MG_OK) return rc;
+    if (use_solve1d(h)) return solve1d(h, rtol, st);
     return solve_loop(h, rtol, {st});
 }
 

@@ -107,6 +107,12 @@ struct MarchArgs {
     int zero_in;        // PRE: the input state is zero whatever the descriptor says
 };
 
+// What a solve's first norm sets in the state (on: the other fields apply).
+struct StateInit {
+    int on, maxc;
+    double tol, watch, stall;
+};
+
 // ---- launchers (defined in the kernel translation units) -----------------
 // One full red-black sweep of the 3D Poisson operator, out of place (uin ->
 // uout; pitches in elements); the state and rhs types follow st.
@@ -216,11 +222,6 @@ struct NormArgs {
     int first;          // 1: this norm also measures ||f||^2 and resets the history
 };
 hipError_t launch_norm(const NormArgs &a, hipStream_t s);
-// What a solve's first norm sets in the state (on: the other fields apply).
-struct StateInit {
-    int on, maxc;
-    double tol, watch, stall;
-};
 // Reduce partials + stop test (must follow every norm-producing launch).  pub:
 // host-visible copy of the states, written when not null (done, nres, rel and
 // the history), also for systems that stopped earlier.
@@ -260,6 +261,12 @@ hipError_t launch_tail2d(int st, bool vc, const TailArgs &a, const LevelDesc &L,
 // The 3D one (k_tail3d.hip).
 bool tail3d_supported(int n_top, int m);
 hipError_t launch_tail3d(int st, const TailArgs &a, const LevelDesc &L, hipStream_t s);
+// The 1D ones (k_tail1d.hip): one V-cycle of a hierarchy that is all tail, and
+// `cycles` cycles of an FP64 solve with their norms and stop tests.
+bool tail1d_supported(int n, int m);
+hipError_t launch_tail1d(int st, const TailArgs &a, const LevelDesc &L, hipStream_t s);
+hipError_t launch_solve1d(int n, double *u, const double *f, const double *cinv, int nu1, int nu2, SolveState *st,
+                          int first, int cycles, bool zero, const StateInit &init, SolveState *pub, hipStream_t s);
 hipError_t tail_prepare(int st, bool vc, int dim);
 hipError_t launch_tail_sized(int st, bool vc, int dim, const TailArgs &a, size_t lds, int threads, hipStream_t s);
 // Dynamic LDS of the tail (levels n_top and below); faces adds the face tables.
