@@ -194,34 +194,95 @@ __global__ __launch_bounds__(256) void k_jacobi(GenArgs g)
 }
 
 // ---- residual + full weighting: fc(I) = sum_o w(o) r(2I + o) / 4^d ---------------
-template <class S, class F, int DIM, bool VC>
-__global__ __launch_bounds__(256) void k_resid_restrict(GenArgs g)
+template <class S, class F>
+__global__ __launch_bounds__(256) void k_resid_restrict1(GenArgs g)
 {
     using C = typename Traits<S>::C;
     if (g.state && g.state->done) return;
     const LevelDesc &L = g.L;
-    Idx<DIM> x{L.n, L.pitch, L.ppitch};
-    Idx<DIM> xc{L.nc, L.cpitch, L.cppitch};
+    Idx<1> x{L.n, L.pitch, L.ppitch};
     const S *u = (const S *)L.B;
     const F *f = (const F *)L.f;
-    const C *a = (const C *)L.a;
     F *fc = (F *)L.fc;
-    const long long mc = npts(L.nc, DIM);
-    for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < mc;
-         p += (long long)gridDim.x * blockDim.x) {
-        int I, J, K;
-        coords(p, L.nc, DIM, I, J, K);
+    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < L.nc; p += gridDim.x * blockDim.x) {
         C s = (C)0;
-        for (int oz = (DIM > 2 ? -1 : 0); oz <= (DIM > 2 ? 1 : 0); ++oz)
-            for (int oy = (DIM > 1 ? -1 : 0); oy <= (DIM > 1 ? 1 : 0); ++oy)
-                for (int ox = -1; ox <= 1; ++ox) {
-                    const int i = 2 * I + ox, j = DIM > 1 ? 2 * J + oy : 1, k = DIM > 2 ? 2 * K + oz : 1;
-                    const int wt = (2 - (ox < 0 ? -ox : ox)) * (DIM > 1 ? (2 - (oy < 0 ? -oy : oy)) : 1) *
-                                   (DIM > 2 ? (2 - (oz < 0 ? -oz : oz)) : 1);
-                    const C r = (C)f[x.off(i, j, k)] - apply_pt<S, DIM, VC>(u, a, x, L.inv_h2, i, j, k);
-                    s = s + (C)wt * r;
-                }
-        fc[xc.off(I, J, K)] = (F)(s * (C)(DIM == 1 ? 0.25 : DIM == 2 ? 0.0625 : 0.015625));
+        for (int ox = -1; ox <= 1; ++ox) {
+            const int i = 2 * (p + 1) + ox;
+            const C r = (C)f[i - 1] - apply_pt<S, 1, false>(u, nullptr, x, L.inv_h2, i, 1, 1);
+            s = s + (C)(2 - (ox < 0 ? -ox : ox)) * r;
+        }
+        fc[p] = (F)(s * (C)0.25);
+    }
+}
+
+// 2D: a wavefront takes 64 fine columns (30 coarse points of them) and kRRows
+// coarse rows, all loads in flight at once; the neighbours' values, their faces
+// and residuals come from the next lanes, so each residual and each face is
+// computed once or twice instead of 2.25 times (a coarse point by itself takes
+// nine residuals of five points and their 36 faces: 1023^2 variable-coefficient
+// FP32 13.2 us -> 7.3).  The sums and their order are those of the 1D kernel
+// above, rows from below, west to east.
+constexpr int kRRows = 4;
+template <class S, class F, bool VC>
+__global__ __launch_bounds__(256) void k_resid_restrict2(GenArgs g)
+{
+    using T = Traits<S>;
+    using C = typename T::C;
+    if (g.state && g.state->done) return;
+    const LevelDesc &L = g.L;
+    const int n = L.n, nc = L.nc, lane = threadIdx.x & 63;
+    const int strips = (nc + 29) / 30;
+    const long long unit = blockIdx.x * 4LL + (threadIdx.x >> 6);
+    const int I0 = 30 * (int)(unit % strips), J0 = kRRows * (int)(unit / strips);
+    if (J0 >= nc) return;
+    const S *ub = (const S *)L.B;
+    const F *fb = (const F *)L.f;
+    const C *a = (const C *)L.a;
+    constexpr int NR = 2 * kRRows + 3;  // fine rows 2 J0 .. 2 J0 + NR - 1
+    const int i = 2 * I0 + lane;        // this lane's fine column; the even lanes 2 .. 60 hold coarse ones
+    const bool cin = i >= 1 && i <= n;
+    C u[NR], f[NR], an[VC ? NR : 1];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+        const int j = 2 * J0 + q;
+        const bool in = cin && j >= 1 && j <= n;
+        u[q] = in ? T::ld(ub + (long long)(j - 1) * L.pitch + (i - 1)) : (C)0;
+        f[q] = in && q > 0 && q < NR - 1 ? (C)gld(fb + (long long)(j - 1) * L.pitch + (i - 1)) : (C)0;
+        if constexpr (VC) an[q] = gld(a + (long long)min(j, n + 1) * (n + 2) + min(i, n + 1));
+    }
+    C ws = (C)0, acc = (C)0;
+    if constexpr (VC) ws = harm(an[1], an[0]);
+    F *fc = (F *)L.fc;
+#pragma unroll
+    for (int q = 1; q < NR - 1; ++q) {
+        const C uc = u[q], w = from_prev(uc), e = from_next(uc);
+        C s;
+        if constexpr (!VC) {
+            s = (uc - w) + (uc - e);
+            s = (s + (uc - u[q - 1])) + (uc - u[q + 1]);
+        } else {
+            const C we = harm(an[q], from_next(an[q])), ww = from_prev(we), wn = harm(an[q], an[q + 1]);
+            s = ((ww * (uc - w) + we * (uc - e)) + ws * (uc - u[q - 1])) + wn * (uc - u[q + 1]);
+            ws = wn;
+        }
+        const C r = f[q] - s * (C)L.inv_h2, rl = from_prev(r), rr = from_next(r);
+        if (q % 2 == 0) {  // the coarse point's own row
+            acc = acc + (C)2 * rl;
+            acc = acc + (C)4 * r;
+            acc = acc + (C)2 * rr;
+            continue;
+        }
+        if (q > 1) {  // the row above it
+            acc = acc + rl;
+            acc = acc + (C)2 * r;
+            acc = acc + rr;
+            const int I = I0 + lane / 2, J = J0 + q / 2;
+            if (!(lane & 1) && lane >= 2 && lane <= 60 && I <= nc && J <= nc)
+                gst(fc + (long long)(J - 1) * L.cpitch + (I - 1), (F)(acc * (C)0.0625));
+        }
+        acc = rl;  // the row below the next
+        acc = acc + (C)2 * r;
+        acc = acc + rr;
     }
 }
 
@@ -366,42 +427,58 @@ __global__ __launch_bounds__(256) void k_prolong_correct3(GenArgs g)
 }
 
 // ---- prolongation + correction: B += P Bc ------------------------------------
-template <class S, int DIM>
-__global__ __launch_bounds__(256) void k_prolong_correct(GenArgs g)
+template <class S>
+__global__ __launch_bounds__(256) void k_prolong_correct1(GenArgs g)
 {
     using C = typename Traits<S>::C;
     if (g.state && g.state->done) return;
     const LevelDesc &L = g.L;
-    Idx<DIM> x{L.n, L.pitch, L.ppitch};
-    Idx<DIM> xc{L.nc, L.cpitch, L.cppitch};
+    Idx<1> xc{L.nc, L.cpitch, L.cppitch};
     S *u = (S *)L.B;
     const S *uc = (const S *)L.Bc;
-    const long long m = npts(L.n, DIM);
-    for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < m; p += (long long)gridDim.x * blockDim.x) {
-        int i, j, k;
-        coords(p, L.n, DIM, i, j, k);
-        // parents along each axis: even index -> one parent (weight 1), odd -> two (1/2 each)
-        const int i0 = i / 2, i1 = (i & 1) ? i0 + 1 : i0;
-        const int j0 = j / 2, j1 = (j & 1) ? j0 + 1 : j0;
-        const int k0 = k / 2, k1 = (k & 1) ? k0 + 1 : k0;
-        auto line = [&](int jj, int kk) -> C {
-            const C a0 = getu(uc, xc, i0, jj, kk);
-            return (i & 1) ? (a0 + getu(uc, xc, i1, jj, kk)) * (C)0.5 : a0;
-        };
-        auto plane = [&](int kk) -> C {
-            if (DIM < 2) return line(1, kk);
-            const C b0 = line(j0, kk);
-            return (j & 1) ? (b0 + line(j1, kk)) * (C)0.5 : b0;
-        };
-        C corr;
-        if (DIM < 3) {
-            corr = plane(1);
-        } else {
-            const C c0 = plane(k0);
-            corr = (k & 1) ? (c0 + plane(k1)) * (C)0.5 : c0;
-        }
-        S *pu = u + x.off(i, j, k);
-        Traits<S>::st(pu, Traits<S>::rnd(Traits<S>::ld(pu) + corr));
+    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < L.n; p += gridDim.x * blockDim.x) {
+        // even index -> one parent (weight 1), odd -> two (1/2 each)
+        const int i = p + 1, i0 = i / 2;
+        const C a0 = getu(uc, xc, i0, 1, 1);
+        const C corr = (i & 1) ? (a0 + getu(uc, xc, i0 + 1, 1, 1)) * (C)0.5 : a0;
+        Traits<S>::st(u + p, Traits<S>::rnd(Traits<S>::ld(u + p) + corr));
+    }
+}
+
+// 2D: a wavefront takes 64 columns of 8 rows, all loads in flight at once;
+// each coarse row is interpolated along x once (1023^2 FP32 8.2 us -> 6.3,
+// the index arithmetic of a point by itself being most of it).  Same order:
+// x, then y.
+template <class S>
+__global__ __launch_bounds__(256) void k_prolong_correct2(GenArgs g)
+{
+    using T = Traits<S>;
+    using C = typename T::C;
+    if (g.state && g.state->done) return;
+    const LevelDesc &L = g.L;
+    const int n = L.n, nc = L.nc, strips = (n + 63) / 64;
+    const long long unit = blockIdx.x * 4LL + (threadIdx.x >> 6);
+    const int i = 64 * (int)(unit % strips) + (int)(threadIdx.x & 63) + 1, j0 = 8 * (int)(unit / strips);
+    if (j0 >= n || i > n) return;
+    S *u = (S *)L.B + (i - 1);
+    const S *uc = (const S *)L.Bc;
+    const int i0 = i / 2, i1 = i0 + (i & 1);
+    C line[5], v[8];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        const int J = j0 / 2 + q;
+        const bool in = J >= 1 && J <= nc;
+        const S *row = uc + (long long)(J - 1) * L.cpitch;
+        const C a0 = in && i0 >= 1 ? T::ld(row + (i0 - 1)) : (C)0, a1 = in && i1 <= nc ? T::ld(row + (i1 - 1)) : (C)0;
+        line[q] = (i & 1) ? (a0 + a1) * (C)0.5 : a0;
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = j0 + q < n ? T::ld(u + (long long)(j0 + q) * L.pitch) : (C)0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        // row j0 + q + 1: odd rows lie between two coarse ones
+        const C corr = q % 2 == 0 ? (line[q / 2] + line[q / 2 + 1]) * (C)0.5 : line[(q + 1) / 2];
+        if (j0 + q < n) T::st(u + (long long)(j0 + q) * L.pitch, T::rnd(v[q] + corr));
     }
 }
 
@@ -949,8 +1026,12 @@ static hipError_t rr_dim(const GenArgs &g, hipStream_t s)
 {
     const int grid = grid_for(npts(g.L.nc, g.L.dim));
     switch (g.L.dim) {
-    case 1: hipLaunchKernelGGL((k_resid_restrict<S, F, 1, false>), dim3(grid), dim3(256), 0, s, g); break;
-    case 2: hipLaunchKernelGGL((k_resid_restrict<S, F, 2, VC>), dim3(grid), dim3(256), 0, s, g); break;
+    case 1: hipLaunchKernelGGL((k_resid_restrict1<S, F>), dim3(grid), dim3(256), 0, s, g); break;
+    case 2: {
+        const long long units = (long long)((g.L.nc + 29) / 30) * ((g.L.nc + kRRows - 1) / kRRows);
+        hipLaunchKernelGGL((k_resid_restrict2<S, F, VC>), dim3((unsigned)((units + 3) / 4)), dim3(256), 0, s, g);
+        break;
+    }
     case 3:
         hipLaunchKernelGGL((k_residual_to_a3<S, F>), dim3(grid_for(((long long)(g.L.n + 63) / 64) * ((g.L.n + 3) / 4) *
                                                                ((g.L.n + 31) / 32) * 256)),
@@ -976,8 +1057,12 @@ static hipError_t pc_dim(const GenArgs &g, hipStream_t s)
 {
     const int grid = grid_for(npts(g.L.n, g.L.dim));
     switch (g.L.dim) {
-    case 1: hipLaunchKernelGGL((k_prolong_correct<S, 1>), dim3(grid), dim3(256), 0, s, g); break;
-    case 2: hipLaunchKernelGGL((k_prolong_correct<S, 2>), dim3(grid), dim3(256), 0, s, g); break;
+    case 1: hipLaunchKernelGGL((k_prolong_correct1<S>), dim3(grid), dim3(256), 0, s, g); break;
+    case 2: {
+        const long long units = (long long)((g.L.n + 63) / 64) * ((g.L.n + 7) / 8);
+        hipLaunchKernelGGL((k_prolong_correct2<S>), dim3((unsigned)((units + 3) / 4)), dim3(256), 0, s, g);
+        break;
+    }
     case 3:
         hipLaunchKernelGGL((k_prolong_correct3<S>), dim3(grid_for(((long long)(g.L.n + 63) / 64) * ((g.L.n + 3) / 4) *
                                                                 ((g.L.n + 31) / 32) * 256)),

@@ -714,7 +714,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_lstep_fused(const S *ein, S *
     // offset, which reads 0 -- the zero boundary values; out-of-domain pixels
     // are selected away.
     {
-        const rsrc_t re = make_rsrc(ein, (uint32_t)n * (uint32_t)n * (uint32_t)sizeof(S));
+        const rsrc_t re = make_rsrc(ein, ein ? (uint32_t)n * (uint32_t)n * (uint32_t)sizeof(S) : 0u);
         const rsrc_t rfs = make_rsrc(f, (uint32_t)n * (uint32_t)n * 4u);
         const rsrc_t ras = make_rsrc(a, (uint32_t)an * (uint32_t)an * 4u);
         constexpr uint32_t SB = sizeof(S);
@@ -933,8 +933,9 @@ __global__ __launch_bounds__(kMThreads, 4) void k_lstep_march(const S *ein, S *e
 
     // s row rho = (h^2 f - A' e) / D' over the 64 columns from x0 - 4 (h^2
     // cancels), bf16-rounded, 0 outside the domain; loads through buffer
-    // descriptors, out-of-domain neighbours at an out-of-range offset (0)
-    const rsrc_t re = make_rsrc(ein, (uint32_t)n * (uint32_t)n * (uint32_t)sizeof(S));
+    // descriptors, out-of-domain neighbours at an out-of-range offset (0); an
+    // empty one for an iterate that is 0
+    const rsrc_t re = make_rsrc(ein, ein ? (uint32_t)n * (uint32_t)n * (uint32_t)sizeof(S) : 0u);
     const rsrc_t rfs = make_rsrc(f, (uint32_t)n * (uint32_t)n * 4u);
     const int an = n + 2;
     const rsrc_t ras = make_rsrc(a, (uint32_t)an * (uint32_t)an * 4u);

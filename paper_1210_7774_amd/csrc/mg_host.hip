@@ -714,8 +714,12 @@ GenArgs gen_args(const mg_handle_s *h, int s, int l)
     return g;
 }
 
-// Smoothing on one level with the generic kernels (in place on B).
-hipError_t gen_smooth(mg_handle_s *h, int s, int l, int nsweeps, hipStream_t st)
+// The level runs fused learned steps.
+bool learned_fused_on(const mg_handle_s *h, int l) { return l == 0 && h->learned && h->learned_on && !h->learned_unfused; }
+
+// Smoothing on one level with the generic kernels (in place on B); zero: B is
+// to be taken as 0 (fused learned steps only, at least one).
+hipError_t gen_smooth(mg_handle_s *h, int s, int l, int nsweeps, hipStream_t st, bool zero = false)
 {
     GenArgs g = gen_args(h, s, l);
     hipError_t e = hipSuccess;
@@ -731,8 +735,8 @@ hipError_t gen_smooth(mg_handle_s *h, int s, int l, int nsweeps, hipStream_t st)
         // fused steps ping-pong between the level's two state buffers
         void *src = L.B, *dst = L.A;
         for (int k = 0; k < nsweeps && e == hipSuccess; ++k) {
-            e = learned_step_fused(h->st, src, dst, (const float *)L.f, (const float *)L.a, L.n, L.h * L.h, h->lw,
-                                   st);
+            e = learned_step_fused(h->st, k == 0 && zero ? nullptr : src, dst, (const float *)L.f, (const float *)L.a,
+                                   L.n, L.h * L.h, h->lw, st);
             std::swap(src, dst);
         }
         if (e == hipSuccess && (nsweeps & 1)) e = launch_copy_state(h->st, g, g.L.A, g.L.B, st);
@@ -1042,13 +1046,16 @@ mg_status enqueue_generic_down(mg_handle_s *h, int s, int l, hipStream_t st, boo
     if (h->m3) return enqueue_m3(h, s, l, false, st, keep);
     Sys &S = h->sys[s];
     GenArgs g = gen_args(h, s, l);
-    if (g.L.uzero && !keep) {
+    // a level that starts from 0: the first fused learned step does not read
+    // B, the other smoothers update it in place
+    const bool zero = g.L.uzero && !keep, lean = zero && learned_fused_on(h, l) && h->opt.nu1 > 0;
+    if (zero && !lean) {
         const long long m = level_points(S.lv[l].n, h->dim);
         HIPCHK(h, launch_fill_zero(S.lv[l].B, (long long)state_bytes(h->st) * m, st));
     }
     const double pts = (double)level_points(S.lv[l].n, h->dim);
     int pi = prof_begin(h, smooth_class(h, l, S.lv[l].n), smooth_bytes(h, l, pts) * h->opt.nu1, st);
-    HIPCHK(h, gen_smooth(h, s, l, h->opt.nu1, st));
+    HIPCHK(h, gen_smooth(h, s, l, h->opt.nu1, st, lean));
     prof_end(h, pi, st);
     pi = prof_begin(h, lvname("resid_restrict", S.lv[l].n),
                     pts * (state_bytes(h->st) + h->fs) + (double)level_points(S.lv[l + 1].n, h->dim) * h->fs, st);
@@ -1823,8 +1830,8 @@ void free_handle(mg_handle_s *h)
 // (timed and captured solves keep a launch per operation).
 bool use_solve1d(const mg_handle_s *h)
 {
-    return h->dim == 1 && !h->ir && !h->batch && !h->vc && !h->learned && !h->prof && !h->opt.use_graph && h->opt.smoother == MG_SM_RBGS &&
-           h->opt.cycle == MG_CYCLE_V && !h->opt.fmg && h->sys[0].lt == 0 &&
+    return h->dim == 1 && !h->ir && !h->batch && !h->vc && !h->learned && !h->prof && !h->opt.use_graph &&
+           h->opt.smoother == MG_SM_RBGS && h->opt.cycle == MG_CYCLE_V && !h->opt.fmg && h->sys[0].lt == 0 &&
            tail1d_supported(h->sys[0].n, h->tail_m);
 }
 
