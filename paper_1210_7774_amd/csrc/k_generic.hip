@@ -445,11 +445,12 @@ __global__ __launch_bounds__(256) void k_prolong_correct1(GenArgs g)
     }
 }
 
-// 2D: a wavefront takes 64 columns of 8 rows, all loads in flight at once;
-// each coarse row is interpolated along x once (1023^2 FP32 8.2 us -> 6.3,
-// the index arithmetic of a point by itself being most of it).  Same order:
-// x, then y.
-template <class S>
+// 2D (ADD), and interpolation alone, B = P Bc: a wavefront takes 64 columns of
+// 8 rows, all loads in flight at once; each coarse row is interpolated along x
+// once (1023^2 FP32 8.2 us -> 6.3, the index arithmetic of a point by itself
+// being most of it; 2047^2 FP64 without the sum 19.4 -> 9.0).  Same order: x,
+// then y.
+template <class S, bool ADD>
 __global__ __launch_bounds__(256) void k_prolong_correct2(GenArgs g)
 {
     using T = Traits<S>;
@@ -473,7 +474,7 @@ __global__ __launch_bounds__(256) void k_prolong_correct2(GenArgs g)
         line[q] = (i & 1) ? (a0 + a1) * (C)0.5 : a0;
     }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = j0 + q < n ? T::ld(u + (long long)(j0 + q) * L.pitch) : (C)0;
+    for (int q = 0; q < 8; ++q) v[q] = ADD && j0 + q < n ? T::ld(u + (long long)(j0 + q) * L.pitch) : (C)0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         // row j0 + q + 1: odd rows lie between two coarse ones
@@ -1052,17 +1053,19 @@ hipError_t launch_resid_restrict(int st, bool vc, const GenArgs &g, hipStream_t 
     return hipErrorInvalidValue;
 }
 
+static unsigned pc2_grid(int n)
+{
+    const long long units = (long long)((n + 63) / 64) * ((n + 7) / 8);
+    return (unsigned)((units + 3) / 4);
+}
+
 template <class S>
 static hipError_t pc_dim(const GenArgs &g, hipStream_t s)
 {
     const int grid = grid_for(npts(g.L.n, g.L.dim));
     switch (g.L.dim) {
     case 1: hipLaunchKernelGGL((k_prolong_correct1<S>), dim3(grid), dim3(256), 0, s, g); break;
-    case 2: {
-        const long long units = (long long)((g.L.n + 63) / 64) * ((g.L.n + 7) / 8);
-        hipLaunchKernelGGL((k_prolong_correct2<S>), dim3((unsigned)((units + 3) / 4)), dim3(256), 0, s, g);
-        break;
-    }
+    case 2: hipLaunchKernelGGL((k_prolong_correct2<S, true>), dim3(pc2_grid(g.L.n)), dim3(256), 0, s, g); break;
     case 3:
         hipLaunchKernelGGL((k_prolong_correct3<S>), dim3(grid_for(((long long)(g.L.n + 63) / 64) * ((g.L.n + 3) / 4) *
                                                                 ((g.L.n + 31) / 32) * 256)),
@@ -1102,7 +1105,7 @@ hipError_t launch_interp(int st, const GenArgs &g, hipStream_t s)
 #define MGX_IP(S)                                                                              \
     switch (g.L.dim) {                                                                         \
     case 1: hipLaunchKernelGGL((k_interp<S, 1>), dim3(grid), dim3(256), 0, s, g); break;       \
-    case 2: hipLaunchKernelGGL((k_interp<S, 2>), dim3(grid), dim3(256), 0, s, g); break;       \
+    case 2: hipLaunchKernelGGL((k_prolong_correct2<S, false>), dim3(pc2_grid(g.L.n)), dim3(256), 0, s, g); break; \
     case 3: hipLaunchKernelGGL((k_interp<S, 3>), dim3(grid), dim3(256), 0, s, g); break;       \
     }
     switch (st) {

@@ -16,11 +16,13 @@
 // them without workgroup barriers.
 //
 // What bounds it is latency: about 45 dependent phases of one LDS round trip
-// each.  The level-by-level LDS form (k_tail.hip, which keeps the other
-// dimensions, Jacobi, W / F cycles and full multigrid) read every neighbour,
+// each.  The level-by-level LDS form (k_tail.hip, which keeps Jacobi, W / F
+// cycles and the sizes no register form covers) read every neighbour,
 // the rhs and the faces from LDS with 16 wavefronts at a barrier per half sweep
 // on every level: 29 us (63 .. 3, FP64) and 46 us (FP32 diffusion) against 11.8
 // and 13.3 us here, of which about 2 us are the launch and 2 the first loads.
+// Full multigrid with V-cycles on the tail's levels is the same kernel with
+// the rhs carried down first: 72 us level by level, 23 us here (63 .. 3, FP64).
 #include "dev_common.h"
 
 namespace mgx {
@@ -146,6 +148,127 @@ struct Tail2 {
         }
     }
 
+    // Full weighting of a block's four values: coarse point (p, r) into L.fc.
+    template <int K>
+    __device__ __forceinline__ void weight(TLevelLds<C, K> &L, const C (&res)[4])
+    {
+        constexpr int P = 1 << (K - 1);
+        const int p = tid % P, r = tid / P, q = (r + 1) * P + p;
+        const bool xin = p < P - 1, yin = r < P - 1;
+        if (active<K>(tid)) {
+            L.r[0][q] = res[RA];
+            L.r[1][q] = res[BA];
+        }
+        sync<K>();
+        if (active<K>(tid)) {
+            // rows 2r - 1, 2r, 2r + 1 of columns 2p - 1, 2p, 2p + 1, in order
+            const C nRA = L.r[0][q + P], nBA = L.r[1][q + P];
+            C s = res[RA];
+            s = s + (C)2 * res[BA];
+            s = s + from_next(res[RA], (C)0);
+            s = s + (C)2 * res[BB];
+            s = s + (C)4 * res[RB];
+            s = s + (C)2 * from_next(res[BB], (C)0);
+            s = s + nRA;
+            s = s + (C)2 * nBA;
+            s = s + from_next(nRA, (C)0);
+            L.fc[r * P + p] = (xin && yin) ? s * (C)0.0625 : (C)0;
+        }
+        sync<K>();
+    }
+
+    // 3 x 3 unknowns: FP64 inverse times rhs
+    __device__ __forceinline__ void coarsest(TLevelLds<C, 3> &L)
+    {
+        constexpr int P = 4;
+        if (tid < 9) {
+            double x = 0.0;
+#pragma unroll
+            for (int k = 0; k < 9; ++k) x += cinv[tid * 9 + k] * (double)L.fc[(k / 3) * P + k % 3];
+            L.uc[(tid / 3 + 1) * (P + 1) + tid % 3 + 1] = T::rnd((C)x);
+        }
+    }
+
+    // The next coarser level between a level's coarse rhs and its coarse
+    // state: a V-cycle visit from zero, or full multigrid.
+    template <int K, bool FMG>
+    __device__ __forceinline__ void below(TLds<C, K> &lds)
+    {
+        constexpr int P = 1 << (K - 1), Pc = P / 2;
+        TLevelLds<C, K> &L = lds.top;
+        C cf[4], cu[4] = {(C)0, (C)0, (C)0, (C)0};
+        const int pc = tid % Pc, rc = tid / Pc;
+        if (active<K - 1>(tid)) {
+            const C *fc = L.fc + 2 * rc * P + 2 * pc;
+            cf[RA] = fc[0];
+            cf[BA] = fc[1];
+            cf[BB] = fc[P];
+            cf[RB] = fc[P + 1];
+            if constexpr (!FMG) {
+                // the state starts from zero
+#pragma unroll
+                for (int k = 0; k < 4; ++k) lds.below.top.v[k][(rc + 1) * Pc + pc] = (C)0;
+            }
+        }
+        sync<K - 1>();
+        if constexpr (FMG) fmg<K - 1>(lds.below, cu, cf);
+        else visit<K - 1>(lds.below, cu, cf, true);
+        if (active<K - 1>(tid)) {
+            C *uc = L.uc + (2 * rc + 1) * (P + 1) + 2 * pc + 1;
+            uc[0] = cu[RA];
+            uc[1] = cu[BA];
+            uc[P + 1] = cu[BB];
+            uc[P + 2] = cu[RB];
+        }
+    }
+    template <int K, bool FMG>
+    __device__ __forceinline__ void coarse(TLds<C, K> &lds)
+    {
+        if constexpr (K == 3) {
+            coarsest(lds.top);
+        } else if constexpr (K == 5) {
+            if (tid < 64) below<K, FMG>(lds);  // the wavefront of the levels from here down
+        } else {
+            below<K, FMG>(lds);
+        }
+        sync<K>();
+    }
+
+    // u (ADD: +=) the bilinear interpolation of the coarse state (coarse point
+    // (p, r) is the block's (even, even) point)
+    template <int K, bool ADD>
+    __device__ __forceinline__ void interpolate(TLevelLds<C, K> &L, C (&u)[4])
+    {
+        constexpr int P = 1 << (K - 1);
+        const int p = tid % P, r = tid / P, q = (r + 1) * P + p;
+        const bool xin = p < P - 1, yin = r < P - 1;
+        if (active<K>(tid)) {
+            const C *uc = L.uc + (r + 1) * (P + 1) + p + 1;
+            const C c11 = uc[0], c01 = uc[-1], c10 = uc[-(P + 1)], c00 = uc[-(P + 1) - 1];
+            const C l0 = (c00 + c10) * (C)0.5, l1 = (c01 + c11) * (C)0.5;
+            if constexpr (!ADD) u[0] = u[1] = u[2] = u[3] = (C)0;
+            u[RA] = T::rnd(u[RA] + (l0 + l1) * (C)0.5);
+            u[BA] = xin ? T::rnd(u[BA] + (c10 + c11) * (C)0.5) : (C)0;
+            u[BB] = yin ? T::rnd(u[BB] + l1) : (C)0;
+            u[RB] = (xin && yin) ? T::rnd(u[RB] + c11) : (C)0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) L.v[k][q] = u[k];
+        }
+        sync<K>();
+    }
+
+    // Full multigrid from level K with rhs f: f carried down by full weighting,
+    // the coarsest level solved, then on each level the interpolated state and
+    // one visit.
+    template <int K>
+    __device__ __forceinline__ void fmg(TLds<C, K> &lds, C (&u)[4], const C (&f)[4])
+    {
+        weight<K>(lds.top, f);
+        coarse<K, true>(lds);
+        interpolate<K, false>(lds.top, u);
+        visit<K>(lds, u, f, true);
+    }
+
     // One V-cycle visit of level K from the state u (its four arrays are in
     // LDS) with rhs f.
     template <int K>
@@ -178,79 +301,10 @@ struct Tail2 {
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) res[k] = f[k] - a[k] * ih2;
-            L.r[0][q] = res[RA];
-            L.r[1][q] = res[BA];
         }
-        sync<K>();
-        if (active<K>(tid)) {
-            // rows 2r - 1, 2r, 2r + 1 of columns 2p - 1, 2p, 2p + 1, in order
-            const C nRA = L.r[0][q + P], nBA = L.r[1][q + P];
-            C s = res[RA];
-            s = s + (C)2 * res[BA];
-            s = s + from_next(res[RA], (C)0);
-            s = s + (C)2 * res[BB];
-            s = s + (C)4 * res[RB];
-            s = s + (C)2 * from_next(res[BB], (C)0);
-            s = s + nRA;
-            s = s + (C)2 * nBA;
-            s = s + from_next(nRA, (C)0);
-            L.fc[r * P + p] = (xin && yin) ? s * (C)0.0625 : (C)0;
-        }
-        sync<K>();
-        // ---- the coarse level
-        if constexpr (K == 3) {
-            // 3 x 3 unknowns: FP64 inverse times rhs
-            if (tid < 9) {
-                double x = 0.0;
-#pragma unroll
-                for (int k = 0; k < 9; ++k) x += cinv[tid * 9 + k] * (double)L.fc[(k / 3) * P + k % 3];
-                L.uc[(tid / 3 + 1) * (P + 1) + tid % 3 + 1] = T::rnd((C)x);
-            }
-        } else {
-            auto below = [&]() {
-                C cf[4], cu[4] = {(C)0, (C)0, (C)0, (C)0};
-                constexpr int Pc = P / 2;
-                const int pc = tid % Pc, rc = tid / Pc;
-                if (active<K - 1>(tid)) {
-                    const C *fc = L.fc + 2 * rc * P + 2 * pc;
-                    cf[RA] = fc[0];
-                    cf[BA] = fc[1];
-                    cf[BB] = fc[P];
-                    cf[RB] = fc[P + 1];
-                    // the state starts from zero
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) lds.below.top.v[k][(rc + 1) * Pc + pc] = (C)0;
-                }
-                sync<K - 1>();
-                visit<K - 1>(lds.below, cu, cf, true);
-                if (active<K - 1>(tid)) {
-                    C *uc = L.uc + (2 * rc + 1) * (P + 1) + 2 * pc + 1;
-                    uc[0] = cu[RA];
-                    uc[1] = cu[BA];
-                    uc[P + 1] = cu[BB];
-                    uc[P + 2] = cu[RB];
-                }
-            };
-            if constexpr (K == 5) {
-                if (tid < 64) below();  // the wavefront of the levels from here down
-            } else {
-                below();
-            }
-        }
-        sync<K>();
-        // ---- bilinear correction (coarse point (p, r) is the block's (even, even) point)
-        if (active<K>(tid)) {
-            const C *uc = L.uc + (r + 1) * (P + 1) + p + 1;
-            const C c11 = uc[0], c01 = uc[-1], c10 = uc[-(P + 1)], c00 = uc[-(P + 1) - 1];
-            const C l0 = (c00 + c10) * (C)0.5, l1 = (c01 + c11) * (C)0.5;
-            u[RA] = T::rnd(u[RA] + (l0 + l1) * (C)0.5);
-            u[BA] = xin ? T::rnd(u[BA] + (c10 + c11) * (C)0.5) : (C)0;
-            u[BB] = yin ? T::rnd(u[BB] + l1) : (C)0;
-            u[RB] = (xin && yin) ? T::rnd(u[RB] + c11) : (C)0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) L.v[k][q] = u[k];
-        }
-        sync<K>();
+        weight<K>(L, res);
+        coarse<K, false>(lds);
+        interpolate<K, true>(L, u);
         smooth<K>(L, nu2, u, f, last);
     }
 
@@ -306,7 +360,7 @@ __device__ __forceinline__ void tail_zero(TLds<C, K> &lds, int tid, int nt)
 
 }  // namespace
 
-template <class S, class F, bool VC, int K>
+template <class S, class F, bool VC, int K, bool FMG>
 __global__ __launch_bounds__(K == 6 ? 1024 : K == 5 ? 256 : 64) void k_tail2d(TailArgs args, LevelDesc L1)
 {
     using T = Traits<S>;
@@ -336,7 +390,7 @@ __global__ __launch_bounds__(K == 6 ? 1024 : K == 5 ? 256 : 64) void k_tail2d(Ta
         const C fv = (C)gld((const F *)L.f + o);
         f[k] = in[k] ? fv : (C)0;
         u[k] = (C)0;
-        if (!L.uzero) {
+        if (!FMG && !L.uzero) {
             const C uv = T::ld((const S *)L.B + o);
             u[k] = in[k] ? uv : (C)0;
         }
@@ -356,24 +410,25 @@ __global__ __launch_bounds__(K == 6 ? 1024 : K == 5 ? 256 : 64) void k_tail2d(Ta
         for (int k = 0; k < 4; ++k) lds.top.v[k][(r + 1) * P + p] = u[k];
     }
     __syncthreads();
-    t.template visit<K>(lds, u, f, true);
+    if constexpr (FMG) t.template fmg<K>(lds, u, f);
+    else t.template visit<K>(lds, u, f, true);
     S *b = (S *)L.B;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
         if (in[k]) T::st(b + (long long)(i - 1 + di[k]) + (long long)(j - 1 + dj[k]) * L.pitch, u[k]);
 }
 
-template <class S, class F, bool VC>
+template <class S, class F, bool VC, bool FMG>
 static hipError_t tail2d_n(const TailArgs &a, const LevelDesc &L, hipStream_t s)
 {
     switch (L.n) {
-    case 7: hipLaunchKernelGGL((k_tail2d<S, F, VC, 3>), dim3(a.nsys), dim3(64), 0, s, a, L); break;
-    case 15: hipLaunchKernelGGL((k_tail2d<S, F, VC, 4>), dim3(a.nsys), dim3(64), 0, s, a, L); break;
-    case 31: hipLaunchKernelGGL((k_tail2d<S, F, VC, 5>), dim3(a.nsys), dim3(256), 0, s, a, L); break;
+    case 7: hipLaunchKernelGGL((k_tail2d<S, F, VC, 3, FMG>), dim3(a.nsys), dim3(64), 0, s, a, L); break;
+    case 15: hipLaunchKernelGGL((k_tail2d<S, F, VC, 4, FMG>), dim3(a.nsys), dim3(64), 0, s, a, L); break;
+    case 31: hipLaunchKernelGGL((k_tail2d<S, F, VC, 5, FMG>), dim3(a.nsys), dim3(256), 0, s, a, L); break;
     case 63:
         // FP64 faces of four levels do not fit in the registers of 1024 threads
         if constexpr (!(VC && sizeof(S) == 8)) {
-            hipLaunchKernelGGL((k_tail2d<S, F, VC, 6>), dim3(a.nsys), dim3(1024), 0, s, a, L);
+            hipLaunchKernelGGL((k_tail2d<S, F, VC, 6, FMG>), dim3(a.nsys), dim3(1024), 0, s, a, L);
             break;
         }
         return hipErrorInvalidValue;
@@ -389,12 +444,14 @@ bool tail2d_supported(int st, bool vc, int n_top, int m)
     return n_top == 7 || n_top == 15 || n_top == 31;
 }
 
-hipError_t launch_tail2d(int st, bool vc, const TailArgs &a, const LevelDesc &L, hipStream_t s)
+hipError_t launch_tail2d(int st, bool vc, bool fmg, const TailArgs &a, const LevelDesc &L, hipStream_t s)
 {
     switch (st) {
-    case ST_F64: return vc ? tail2d_n<double, double, true>(a, L, s) : tail2d_n<double, double, false>(a, L, s);
-    case ST_F32: return vc ? tail2d_n<float, float, true>(a, L, s) : tail2d_n<float, float, false>(a, L, s);
-    case ST_BF16: return vc ? tail2d_n<bf16_t, float, true>(a, L, s) : tail2d_n<bf16_t, float, false>(a, L, s);
+    case ST_F64:
+        if (fmg) return vc ? tail2d_n<double, double, true, true>(a, L, s) : tail2d_n<double, double, false, true>(a, L, s);
+        return vc ? tail2d_n<double, double, true, false>(a, L, s) : tail2d_n<double, double, false, false>(a, L, s);
+    case ST_F32: return vc ? tail2d_n<float, float, true, false>(a, L, s) : tail2d_n<float, float, false, false>(a, L, s);
+    case ST_BF16: return vc ? tail2d_n<bf16_t, float, true, false>(a, L, s) : tail2d_n<bf16_t, float, false, false>(a, L, s);
     }
     return hipErrorInvalidValue;
 }

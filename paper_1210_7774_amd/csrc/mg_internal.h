@@ -257,7 +257,7 @@ enum TailOp {
 // The 2D red-black V-cycle tail (k_tail2d.hip) for the given top level and m
 // coarsest unknowns; L: the top level's descriptor (used when a.nsys == 1).
 bool tail2d_supported(int st, bool vc, int n_top, int m);
-hipError_t launch_tail2d(int st, bool vc, const TailArgs &a, const LevelDesc &L, hipStream_t s);
+hipError_t launch_tail2d(int st, bool vc, bool fmg, const TailArgs &a, const LevelDesc &L, hipStream_t s);
 // The 3D one (k_tail3d.hip).
 bool tail3d_supported(int n_top, int m);
 hipError_t launch_tail3d(int st, const TailArgs &a, const LevelDesc &L, hipStream_t s);
