@@ -72,6 +72,16 @@ __global__ void k_lprep(const float *w, LearnedW d)
     }
 }
 
+// Column, row and patch of pixel p (the maps of a pixel take 200 bytes, so
+// pixel counts fit 32 bits; divisions in 64 bits cost more than the layers).
+__device__ __forceinline__ void pixel_at(uint32_t p, int H, int W, int &x, int &y, int &b)
+{
+    const uint32_t r = p / (uint32_t)W;
+    x = (int)(p - r * (uint32_t)W);
+    b = (int)(r / (uint32_t)H);
+    y = (int)(r - (uint32_t)b * (uint32_t)H);
+}
+
 // ---- layer 1: s (float) -> relu(conv 1->16) (bf16 NHWC16) -------------------
 // `s` is read as bf16-rounded values.  One thread per pixel.
 __global__ __launch_bounds__(256) void k_lconv_in(const float *s, const int *idx, int B, int H, int W,
@@ -80,7 +90,8 @@ __global__ __launch_bounds__(256) void k_lconv_in(const float *s, const int *idx
     const long long npx = (long long)B * H * W;
     for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < npx;
          p += (long long)gridDim.x * blockDim.x) {
-        const int x = (int)(p % W), y = (int)((p / W) % H), b = (int)(p / ((long long)W * H));
+        int x, y, b;
+        pixel_at((uint32_t)p, H, W, x, y, b);
         const long long sb = (long long)(idx ? idx[b] : b) * H * W;
         float in[9];
 #pragma unroll
@@ -176,7 +187,8 @@ __global__ __launch_bounds__(256) void k_lconv_out(const bf16_t *x3, const float
     const long long npx = (long long)B * H * W;
     for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < npx;
          p += (long long)gridDim.x * blockDim.x) {
-        const int x = (int)(p % W), yy0 = (int)((p / W) % H), b = (int)(p / ((long long)W * H));
+        int x, yy0, b;
+        pixel_at((uint32_t)p, H, W, x, yy0, b);
         float acc = 0.f;
 #pragma unroll
         for (int t = 0; t < 9; ++t) {
@@ -243,26 +255,27 @@ __global__ __launch_bounds__(256) void k_lscaled(const S *e, const float *f, con
 }
 
 // ---- energy-norm loss and its gradient with respect to the network output ---
-// Per patch b (one block each): w = e - y on the window V = [border, P-border)^2,
+// Per patch b: w = e - y on the window V = [border, P-border)^2,
 // E = sum_faces_in_V a_f (w_p - w_q)^2, E0 = the same for e,
 // dy = -(2 / B) (A_V w) / E0, loss_b = E / E0.
-// Latency bound (a patch per workgroup): the first 256 threads sum E0 while
-// the other 256 sum E and leave A_V w in dy, which all of them scale once E0
-// is known; four pixels' loads are in flight per thread (32 patches of
-// 64 x 64: 12.8 + 17.8 us as two launches, now 16.2 us).
-__global__ __launch_bounds__(512) void k_lloss(const float *y, const float *e, const float *a, const int *idx, int B,
-                                               int P, int border, float *dy, float *loss_b)
+// kLossSegs workgroups a patch write A_V w and their shares of E0 and E; the
+// next kernel (layer 4's data gradient, which reads dy anyway) adds the shares
+// in order, scales and leaves dy (32 patches of 64 x 64: a workgroup a patch,
+// on 32 of 256 CUs, took 16.2 us; LOSS_US here).
+constexpr int kLossSegs = 8;
+__global__ __launch_bounds__(256) void k_lloss(const float *y, const float *e, const float *a, const int *idx, int P,
+                                               int border, float *g_, float2 *share)
 {
-    const int b = blockIdx.x;
+    const int b = blockIdx.x / kLossSegs, seg = blockIdx.x % kLossSegs, tid = threadIdx.x;
     const long long pb = (long long)(idx ? idx[b] : b) * P * P;
     const float *eb = e + pb, *ab = a + pb, *yb = y + (long long)b * P * P;
-    float *dyb = dy + (long long)b * P * P;
-    const int lo = border, hi = P - border, np = P * P;
-    __shared__ float red[512];
-    const int half = threadIdx.x >> 8, tid = threadIdx.x & 255;
-    float part = 0.f;
-    constexpr int U = 4;
-    for (int p0 = tid; p0 < np; p0 += 256 * U) {
+    float *gb = g_ + (long long)b * P * P;
+    const int lo = border, hi = P - border, np = P * P, per = (np + kLossSegs - 1) / kLossSegs;
+    const int pe = min((seg + 1) * per, np);
+    __shared__ float2 red[4];
+    float s0 = 0.f, s1 = 0.f;
+    constexpr int U = 2;  // pixels whose loads are in flight
+    for (int p0 = seg * per + tid; p0 < pe; p0 += 256 * U) {
         // values at the pixel and its neighbours (0: centre, 1 .. 4: left, right, up, down)
         float ev[U][5], av[U][5], yv[U][5];
 #pragma unroll
@@ -273,31 +286,16 @@ __global__ __launch_bounds__(512) void k_lloss(const float *y, const float *e, c
             for (int k = 0; k < 5; ++k) {
                 ev[u][k] = eb[q[k]];
                 av[u][k] = ab[q[k]];
-                yv[u][k] = half ? yb[q[k]] : 0.f;
+                yv[u][k] = yb[q[k]];
             }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int p = p0 + 256 * u, x = p % P, yy = p / P;
-            if (p >= np) break;
-            const bool in = x >= lo && x < hi && yy >= lo && yy < hi;
-            const float ac = av[u][0];
-            if (half == 0) {
-                if (!in) continue;
-                const float ec = ev[u][0];
-                if (x + 1 < hi) {
-                    const float q2 = av[u][2], d = ec - ev[u][2];
-                    part += 2.f * ac * q2 / (ac + q2) * d * d;
-                }
-                if (yy + 1 < hi) {
-                    const float q2 = av[u][4], d = ec - ev[u][4];
-                    part += 2.f * ac * q2 / (ac + q2) * d * d;
-                }
-                continue;
-            }
+            if (p >= pe) break;
             float g = 0.f;
-            const float wc = ev[u][0] - yv[u][0];
-            if (in) {
+            if (x >= lo && x < hi && yy >= lo && yy < hi) {
+                const float ac = av[u][0], ec = ev[u][0], wc = ec - yv[u][0];
                 const int dxs[4] = {-1, 1, 0, 0}, dys[4] = {0, 0, -1, 1};
 #pragma unroll
                 for (int f = 0; f < 4; ++f) {
@@ -307,39 +305,58 @@ __global__ __launch_bounds__(512) void k_lloss(const float *y, const float *e, c
                     const float q = av[u][f + 1];
                     const float af = 2.f * ac * q / (ac + q);
                     g += af * d;
-                    if (f == 1 || f == 3) part += af * d * d;  // each face once: right and down
+                    if (f == 1 || f == 3) {  // each face once: right and down
+                        const float d0 = ec - ev[u][f + 1];
+                        s0 += af * d0 * d0;
+                        s1 += af * d * d;
+                    }
                 }
             }
-            dyb[p] = g;
+            gb[p] = g;
         }
     }
-    red[threadIdx.x] = part;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (tid < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
+    for (int o = 32; o > 0; o >>= 1) {
+        s0 += __shfl_xor(s0, o, 64);
+        s1 += __shfl_xor(s1, o, 64);
     }
-    const float E0 = red[0];
-    const float inv = -2.f / ((float)B * E0);
-    for (int p = threadIdx.x; p < np; p += 512) dyb[p] = inv * dyb[p];
-    if (threadIdx.x == 0) loss_b[b] = red[256] / E0;
+    if ((tid & 63) == 0) red[tid >> 6] = make_float2(s0, s1);
+    __syncthreads();
+    if (tid == 0)
+        share[blockIdx.x] = make_float2(((red[0].x + red[1].x) + red[2].x) + red[3].x,
+                                        ((red[0].y + red[1].y) + red[2].y) + red[3].y);
 }
 
 // ---- backward through layer 4 (16 -> 1) ---------------------------------------
-// dz3[p][ci] = bf16( [x3[p][ci] > 0] * sum_t W4[ci][t] dy[p - t] )
-__global__ __launch_bounds__(256) void k_lbwd_out(const float *dy, const bf16_t *x3, const float *w4, int B, int H,
-                                                  int W, bf16_t *dz3)
+// dz3[p][ci] = bf16( [x3[p][ci] > 0] * sum_t W4[ci][t] dy[p - t] ), with
+// dy = -(2 / B) g / E0 from the loss kernel's A_V w and shares of E0 and E
+// (left in dy; the losses in loss_b).
+__global__ __launch_bounds__(256) void k_lbwd_out(const float *g_, const float2 *share, const bf16_t *x3,
+                                                  const float *w4, int B, int H, int W, bf16_t *dz3, float *dy,
+                                                  float *loss_b)
 {
     const long long npx = (long long)B * H * W;
     for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < npx;
          p += (long long)gridDim.x * blockDim.x) {
-        const int x = (int)(p % W), y = (int)((p / W) % H), b = (int)(p / ((long long)W * H));
+        int x, y, b;
+        pixel_at((uint32_t)p, H, W, x, y, b);
         float d[9];
 #pragma unroll
         for (int t = 0; t < 9; ++t) {
             const int yy = y - t / 3 + 1, xx = x - t % 3 + 1;
-            d[t] = (yy >= 0 && yy < H && xx >= 0 && xx < W) ? dy[((long long)b * H + yy) * W + xx] : 0.f;
+            d[t] = (yy >= 0 && yy < H && xx >= 0 && xx < W) ? g_[((long long)b * H + yy) * W + xx] : 0.f;
         }
+        float2 E = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int k = 0; k < kLossSegs; ++k) {
+            const float2 v = share[(long long)b * kLossSegs + k];
+            E.x += v.x;
+            E.y += v.y;
+        }
+        const float inv = -2.f / ((float)B * E.x);
+#pragma unroll
+        for (int t = 0; t < 9; ++t) d[t] = inv * d[t];
+        dy[p] = inv * g_[p];
+        if (x == 0 && y == 0) loss_b[b] = E.y / E.x;
         short o[16];
 #pragma unroll
         for (int ci = 0; ci < 16; ++ci) {
@@ -1249,15 +1266,18 @@ hipError_t learned_loss_grad(const float *S, const float *E, const float *A, con
     const long long px = (long long)B * P * P;
     hipError_t r = learned_forward(S, idx, B, P, P, t.d, t.x1, t.x2, t.x3, t.y, st);
     if (r != hipSuccess) return r;
-    hipLaunchKernelGGL(k_lloss, dim3(B), dim3(512), 0, st, t.y, E, A, idx, B, P, border, t.dy, t.lossb);
+    // (A_V w lies in dy's place, then dy in y's; the shares of the energies where dz1 will be)
+    float2 *share = (float2 *)t.dz1;
+    hipLaunchKernelGGL(k_lloss, dim3(B * kLossSegs), dim3(256), 0, st, t.y, E, A, idx, P, border, t.dy, share);
     // data gradients, last layer first: dz3 = mask(x3) * conv4^T(dy), dz2 = mask(x2) * conv3^T(dz3), dz1 likewise
     const int g16 = conv16_grid(B, P, P);
-    hipLaunchKernelGGL(k_lbwd_out, dim3(lgrid(px)), dim3(256), 0, st, t.dy, t.x3, t.d.w4, B, P, P, t.dz3);
+    hipLaunchKernelGGL(k_lbwd_out, dim3(lgrid(px)), dim3(256), 0, st, t.dy, share, t.x3, t.d.w4, B, P, P, t.dz3,
+                       t.y, t.lossb);
     hipLaunchKernelGGL((k_lconv16<1>), dim3(g16), dim3(256), 0, st, t.dz3, t.dz2, t.d.wd3, t.x2, B, P, P);
     hipLaunchKernelGGL((k_lconv16<1>), dim3(g16), dim3(256), 0, st, t.dz2, t.dz1, t.d.wd2, t.x1, B, P, P);
     // the four layers' weight gradients
     const int nblk = wgrad_blocks(B, P, P);
-    const WgArgs wa{S, idx, t.x1, t.x2, t.x3, t.dz1, t.dz2, t.dz3, t.dy, B, P, P, t.part};
+    const WgArgs wa{S, idx, t.x1, t.x2, t.x3, t.dz1, t.dz2, t.dz3, t.y, B, P, P, t.part};
     hipLaunchKernelGGL(k_lwgrad, dim3(nblk, 4), dim3(256), 0, st, wa);
     hipLaunchKernelGGL(k_lreduce, dim3((kNW + 31) / 32), dim3(256), 0, st, t.part, nblk, g);
     return hipGetLastError();
