@@ -262,8 +262,10 @@ mg_status mg_jacobi5_static(const double *in, double *out, int rows, int cols, i
  * measures launch shapes on the device.  For every 2D level size that runs
  * the fused PRE/POST kernels, mg_autotune times the PRE launch with block
  * heights 4 .. 256 and, on sizes that hold no system's finest level, LDS
- * tiles (a finest level of up to 1023 points an edge always runs tiles and is
- * listed untimed), on the bound arrays (u[s], f[s]: nsys device pointers, as for a
+ * tiles (a size that holds a finest level runs tiles when all its levels
+ * together are at most 3072 tiles of 32 x 32 points -- a single system up to
+ * 1023 points an edge -- and is then listed untimed), on the bound arrays
+ * (u[s], f[s]: nsys device pointers, as for a
  * solve), `reps` (1 .. 50) timed launches per candidate, and keeps the
  * fastest; the choice lasts for the handle's life.  The finest level's
  * smoother runs in place, so u[s] comes back smoothed (a better iterate of
@@ -274,7 +276,7 @@ mg_status mg_jacobi5_static(const double *in, double *out, int rows, int cols, i
  * the caller's arrays); mg_tune_set applies one (e.g. read back from a
  * cache): MG_ERR_ARG for n < 1 or hb outside 2 .. 256; odd hb is rounded
  * down; a size that holds a finest level keeps the form the library gives it
- * (tiles up to 1023 points an edge, marching with this block height above),
+ * (tiles up to the limit above, marching with this block height beyond),
  * and 3D handles keep the entry without using it. */
 mg_status mg_autotune(mg_handle h, double *const *u, const double *const *f, int reps);
 mg_status mg_tune_get(mg_handle h, int *n, int *hb, int *tiled, int max, int *count);

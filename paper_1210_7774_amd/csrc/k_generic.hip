@@ -611,14 +611,16 @@ __global__ __launch_bounds__(256) void k_norm1(NormArgs g)
 // row's north face.  Bandwidth bound for many systems; the thread-per-point
 // form it replaces spent itself on four FP64 divisions and ten cache loads a
 // point: 1023^2 diffusion 11.2 -> 9.9 us, 48 systems of 13.7 M unknowns
-// 155 -> 88 us (all active).
+// 155 -> 88 us (all active).  A unit's loads are all in flight at once (four
+// rows a round before: 2047^2 diffusion 24.8 -> 21.8 us, 4095^2 47.3 -> 44.8,
+// 1023^2 diffusion 9.6 -> 9.4).
 // HASU false: the zero iterate (r = f), the same sums in the same order.
 constexpr int kNormRows = 8;
 template <bool VC, bool HASU>
 __device__ __forceinline__ void norm2_unit(const double *u, const double *f, const double *a, int n, long long pitch,
                                            double ih2, int ic, int j0, float *r32, double *r64, double &rr, double &ff)
 {
-    constexpr int B = 4;  // rows per round of loads
+    constexpr int B = kNormRows;
     const int lane = threadIdx.x & 63;
     const int i = ic + lane;                                   // this lane's column
     const bool cin = i <= n;
@@ -646,48 +648,46 @@ __device__ __forceinline__ void norm2_unit(const double *u, const double *f, con
         arow(j0, ac, ae);
         ws = harm(as, ac);
     }
-    for (int j = j0; j < j1; j += B) {
-        double un[B], une[B], fv[B], an[B], ane[B];
+    double un[B], une[B], fv[B], an[B], ane[B];
 #pragma unroll
-        for (int k = 0; k < B; ++k) {
-            row(j + k + 1, un[k], une[k]);
-            fv[k] = cin && j + k <= n ? gld(f + (long long)(j + k - 1) * pitch + (i - 1)) : 0.0;
-            if constexpr (VC && HASU) arow(j + k + 1, an[k], ane[k]);
-        }
-        // the strip's west faces of the round's rows, one a lane
-        double wl = 0.0;
-        if constexpr (VC && HASU) {
-            const long long o = (long long)min(j + (lane & (B - 1)), n + 1) * (n + 2) + ic;
-            wl = harm(gld(a + o - 1), gld(a + o));
-        }
+    for (int k = 0; k < B; ++k) {
+        row(j0 + k + 1, un[k], une[k]);
+        fv[k] = cin && j0 + k <= n ? gld(f + (long long)(j0 + k - 1) * pitch + (i - 1)) : 0.0;
+        if constexpr (VC && HASU) arow(j0 + k + 1, an[k], ane[k]);
+    }
+    // the strip's west faces of the rows, one a lane
+    double wl = 0.0;
+    if constexpr (VC && HASU) {
+        const long long o = (long long)min(j0 + (lane & (B - 1)), n + 1) * (n + 2) + ic;
+        wl = harm(gld(a + o - 1), gld(a + o));
+    }
 #pragma unroll
-        for (int k = 0; k < B; ++k) {
-            if (j + k >= j1) break;
-            const double w = from_prev(uc, ue), e = from_next(uc, ue);
-            double s = 0.0;
-            if constexpr (!HASU) {
-            } else if constexpr (!VC) {
-                s = (uc - w) + (uc - e);
-                s = (s + (uc - us)) + (uc - un[k]);
-            } else {
-                const double we = harm(ac, from_next(ac, ae)), ww = from_prev(we, lane_value(wl, k));
-                const double wn = harm(ac, an[k]);
-                s = ((ww * (uc - w) + we * (uc - e)) + ws * (uc - us)) + wn * (uc - un[k]);
-                ws = wn;
-                ac = an[k];
-                ae = ane[k];
-            }
-            const double r = cin ? fv[k] - s * ih2 : 0.0;
-            rr += r * r;
-            ff += fv[k] * fv[k];
-            // contiguous interior outputs
-            const long long p = (long long)(j + k - 1) * n + (i - 1);
-            if (cin && r32) gst(r32 + p, (float)r);
-            if (cin && r64) gst(r64 + p, r);
-            us = uc;
-            uc = un[k];
-            ue = une[k];
+    for (int k = 0; k < B; ++k) {
+        if (j0 + k >= j1) break;
+        const double w = from_prev(uc, ue), e = from_next(uc, ue);
+        double s = 0.0;
+        if constexpr (!HASU) {
+        } else if constexpr (!VC) {
+            s = (uc - w) + (uc - e);
+            s = (s + (uc - us)) + (uc - un[k]);
+        } else {
+            const double we = harm(ac, from_next(ac, ae)), ww = from_prev(we, lane_value(wl, k));
+            const double wn = harm(ac, an[k]);
+            s = ((ww * (uc - w) + we * (uc - e)) + ws * (uc - us)) + wn * (uc - un[k]);
+            ws = wn;
+            ac = an[k];
+            ae = ane[k];
         }
+        const double r = cin ? fv[k] - s * ih2 : 0.0;
+        rr += r * r;
+        ff += fv[k] * fv[k];
+        // contiguous interior outputs
+        const long long p = (long long)(j0 + k - 1) * n + (i - 1);
+        if (cin && r32) gst(r32 + p, (float)r);
+        if (cin && r64) gst(r64 + p, r);
+        us = uc;
+        uc = un[k];
+        ue = une[k];
     }
 }
 

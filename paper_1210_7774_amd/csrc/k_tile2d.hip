@@ -30,8 +30,9 @@
 // 4.6 / 4.2 us here (T = 16); 511 FP64 8.4 / 8.8 us in the first tiled form (two
 // strided passes over the region per stage, all values in LDS), 5.0 / 4.8 us
 // here; 1023 FP64 18.8 / 20.7 -> 10.0 / 11.2 us; 1023 FP32 diffusion finest
-// 36.1 / 49.8 us marching, 11.2 / 14.0 us here.  At 2047 marching is level with
-// it and above that ahead (no halo rows to recompute).
+// 36.1 / 49.8 us marching, 11.2 / 14.0 us here.  Where a launch has work for more
+// than about three rounds of the chip marching is ahead (it recomputes one halo
+// column in twelve instead of half the region): 2047 FP64 27 us a pass against 37.
 #include "dev_common.h"
 
 namespace mgx {
