@@ -1829,11 +1829,12 @@ void free_handle(mg_handle_s *h)
 }
 
 // Plain FP64 1D solves whose hierarchy fits one wavefront run in one launch
-// (timed and captured solves keep a launch per operation).
+// (solves with every launch timed, and captured ones, keep a launch per
+// operation).
 bool use_solve1d(const mg_handle_s *h)
 {
-    return h->dim == 1 && !h->ir && !h->batch && !h->vc && !h->learned && !h->prof && !h->opt.use_graph &&
-           h->opt.smoother == MG_SM_RBGS && h->opt.cycle == MG_CYCLE_V && !h->opt.fmg && h->sys[0].lt == 0 &&
+    return h->dim == 1 && !h->ir && !h->batch && !h->vc && !h->learned && (!h->prof || h->prof_finest_only) &&
+           !h->opt.use_graph && h->opt.smoother == MG_SM_RBGS && h->opt.cycle == MG_CYCLE_V && !h->opt.fmg && h->sys[0].lt == 0 &&
            tail1d_supported(h->sys[0].n, h->tail_m);
 }
 
