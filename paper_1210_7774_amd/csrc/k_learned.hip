@@ -126,8 +126,10 @@ __global__ __launch_bounds__(256) void k_lconv_in(const float *s, const int *idx
 // Latency bound at training sizes (32 patches of 64 x 64: 8 MB, 8192 row
 // tiles): a wave per row tile loaded its nine weight blocks and nine input
 // blocks for nine products; four rows per wave load the weights once and each
-// input row once for the three output rows that read it: 8.2 -> 6.5 us
-// (forward), 8.8 -> 8.2 us (data gradient).
+// input row once for the three output rows that read it.  The weights are the
+// products' rows, so a lane ends with four channels of one pixel: one 8-byte
+// store and mask load a row, not four of 2 bytes (forward 8.2 -> 6.3 us, data
+// gradient 8.8 -> 8.2 with four rows, 6.5 with the wide accesses).
 static constexpr int kConvRows = 4;
 template <int MODE>
 __global__ __launch_bounds__(256) void k_lconv16(const bf16_t *in, bf16_t *out, const bf16_t *wt, const bf16_t *act,
@@ -158,6 +160,13 @@ __global__ __launch_bounds__(256) void k_lconv16(const bf16_t *in, bf16_t *out, 
                 rows[r][kx] = *(const v4s *)(in + (((long long)b * H + yy) * W + xx) * 16 + kq);
         }
     }
+    v4s mask[kConvRows];
+#pragma unroll
+    for (int ry = 0; ry < kConvRows; ++ry) {
+        mask[ry] = (v4s){0, 0, 0, 0};
+        if (MODE == 1 && y0 + ry < H && x0 + i < W)
+            mask[ry] = *(const v4s *)(act + (((long long)b * H + y0 + ry) * W + x0 + i) * 16 + kq);
+    }
 #pragma unroll
     for (int ry = 0; ry < kConvRows; ++ry) {
         const int y = y0 + ry;
@@ -165,19 +174,20 @@ __global__ __launch_bounds__(256) void k_lconv16(const bf16_t *in, bf16_t *out, 
         v4f acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int t = 0; t < 9; ++t)
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(rows[MODE == 0 ? ry + t / 3 : ry + 2 - t / 3][t % 3], bw[t],
+            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bw[t], rows[MODE == 0 ? ry + t / 3 : ry + 2 - t / 3][t % 3],
                                                             acc, 0, 0, 0);
-        // lane holds pixels x0 + kq + q, channel i
+        // lane holds pixel x0 + i, channels kq + q
+        if (x0 + i >= W) continue;
+        const long long o = (((long long)b * H + y) * W + x0 + i) * 16 + kq;
+        v4s r;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int x = x0 + kq + q;
-            if (x >= W) continue;
-            const long long o = (((long long)b * H + y) * W + x) * 16 + i;
             float v = acc[q];
             if (MODE == 0) v = relu(v);
-            else v = (bf16_to_f32(act[o]) > 0.f) ? v : 0.f;
-            out[o] = f32_to_bf16(v);
+            else v = (bf16_to_f32((bf16_t)mask[ry][q]) > 0.f) ? v : 0.f;
+            r[q] = (short)f32_to_bf16(v);
         }
+        *(v4s *)(out + o) = r;
     }
 }
 
