@@ -16,14 +16,18 @@
 // them without workgroup barriers.
 //
 // What bounds it is latency: about 45 dependent phases of one LDS round trip
-// each.  The level-by-level LDS form (k_tail.hip, which keeps Jacobi, W / F
-// cycles and the sizes no register form covers) read every neighbour,
+// each.  The level-by-level LDS form (k_tail.hip, which keeps Jacobi and the
+// sizes no register form covers) read every neighbour,
 // the rhs and the faces from LDS with 16 wavefronts at a barrier per half sweep
 // on every level: 29 us (63 .. 3, FP64) and 46 us (FP32 diffusion) against 11.8
 // and 13.3 us here, of which about 2 us are the launch and 2 the first loads.
 // Full multigrid with V-cycles on the tail's levels is the same kernel with
 // the rhs carried down first: 72 us level by level, 23 us here (63 .. 3, FP64).
+// W and F cycles repeat the visits of the levels below: solves with 6 cycles of
+// 255^2 FP64 W 2455 -> 945 us, F 811 -> 512, of 63^2 FP32 diffusion F 732 -> 298
+// (FP64 from 63 spills 54 registers there and is still the faster form).
 #include "dev_common.h"
+#include "mg.h"
 
 namespace mgx {
 
@@ -75,7 +79,7 @@ struct TLds {
 template <class C>
 struct TLds<C, 2> {};
 
-template <class S, bool VC, int KTOP>
+template <class S, bool VC, int KTOP, bool MULTI>
 struct Tail2 {
     using T = Traits<S>;
     using C = typename T::C;
@@ -190,9 +194,15 @@ struct Tail2 {
     }
 
     // The next coarser level between a level's coarse rhs and its coarse
-    // state: a V-cycle visit from zero, or full multigrid.
+    // state: a V-cycle visit from zero, the visits of a W or F cycle (MULTI: two
+    // W visits, or an F and then a V visit, the second from the first's
+    // result), or full multigrid.
+    static __device__ __forceinline__ int next_kind(int v, int kind)
+    {
+        return v > 0 && kind == MG_CYCLE_F ? MG_CYCLE_V : kind;
+    }
     template <int K, bool FMG>
-    __device__ __forceinline__ void below(TLds<C, K> &lds)
+    __device__ __forceinline__ void below(TLds<C, K> &lds, int kind)
     {
         constexpr int P = 1 << (K - 1), Pc = P / 2;
         TLevelLds<C, K> &L = lds.top;
@@ -211,8 +221,15 @@ struct Tail2 {
             }
         }
         sync<K - 1>();
-        if constexpr (FMG) fmg<K - 1>(lds.below, cu, cf);
-        else visit<K - 1>(lds.below, cu, cf, true);
+        if constexpr (FMG) {
+            fmg<K - 1>(lds.below, cu, cf, kind);
+        } else if constexpr (MULTI) {
+            const int visits = kind == MG_CYCLE_V ? 1 : 2;
+            for (int v = 0; v < visits; ++v)
+                visit<K - 1>(lds.below, cu, cf, v == visits - 1, next_kind(v, kind));
+        } else {
+            visit<K - 1>(lds.below, cu, cf, true, kind);
+        }
         if (active<K - 1>(tid)) {
             C *uc = L.uc + (2 * rc + 1) * (P + 1) + 2 * pc + 1;
             uc[0] = cu[RA];
@@ -222,14 +239,14 @@ struct Tail2 {
         }
     }
     template <int K, bool FMG>
-    __device__ __forceinline__ void coarse(TLds<C, K> &lds)
+    __device__ __forceinline__ void coarse(TLds<C, K> &lds, int kind)
     {
         if constexpr (K == 3) {
             coarsest(lds.top);
         } else if constexpr (K == 5) {
-            if (tid < 64) below<K, FMG>(lds);  // the wavefront of the levels from here down
+            if (tid < 64) below<K, FMG>(lds, kind);  // the wavefront of the levels from here down
         } else {
-            below<K, FMG>(lds);
+            below<K, FMG>(lds, kind);
         }
         sync<K>();
     }
@@ -261,18 +278,18 @@ struct Tail2 {
     // the coarsest level solved, then on each level the interpolated state and
     // one visit.
     template <int K>
-    __device__ __forceinline__ void fmg(TLds<C, K> &lds, C (&u)[4], const C (&f)[4])
+    __device__ __forceinline__ void fmg(TLds<C, K> &lds, C (&u)[4], const C (&f)[4], int kind)
     {
         weight<K>(lds.top, f);
-        coarse<K, true>(lds);
+        coarse<K, true>(lds, kind);
         interpolate<K, false>(lds.top, u);
-        visit<K>(lds, u, f, true);
+        visit<K>(lds, u, f, true, kind);
     }
 
-    // One V-cycle visit of level K from the state u (its four arrays are in
-    // LDS) with rhs f.
+    // One visit of level K from the state u (its four arrays are in LDS) with
+    // rhs f, by a cycle of the given kind (V unless MULTI).
     template <int K>
-    __device__ __forceinline__ void visit(TLds<C, K> &lds, C (&u)[4], const C (&f)[4], bool last)
+    __device__ __forceinline__ void visit(TLds<C, K> &lds, C (&u)[4], const C (&f)[4], bool last, int kind)
     {
         constexpr int P = 1 << (K - 1);
         constexpr C ih2 = (C)(double)(1LL << (2 * K));
@@ -303,7 +320,7 @@ struct Tail2 {
             for (int k = 0; k < 4; ++k) res[k] = f[k] - a[k] * ih2;
         }
         weight<K>(L, res);
-        coarse<K, false>(lds);
+        coarse<K, false>(lds, kind);
         interpolate<K, true>(L, u);
         smooth<K>(L, nu2, u, f, last);
     }
@@ -360,7 +377,7 @@ __device__ __forceinline__ void tail_zero(TLds<C, K> &lds, int tid, int nt)
 
 }  // namespace
 
-template <class S, class F, bool VC, int K, bool FMG>
+template <class S, class F, bool VC, int K, bool FMG, bool MULTI>
 __global__ __launch_bounds__(K == 6 ? 1024 : K == 5 ? 256 : 64) void k_tail2d(TailArgs args, LevelDesc L1)
 {
     using T = Traits<S>;
@@ -373,7 +390,7 @@ __global__ __launch_bounds__(K == 6 ? 1024 : K == 5 ? 256 : 64) void k_tail2d(Ta
     const LevelDesc *dl = args.levels + (long long)sys * args.nlev;
     // (a single system's top level comes in the arguments)
     const LevelDesc L = args.nsys == 1 ? L1 : dl[0];
-    Tail2<S, VC, K> t;
+    Tail2<S, VC, K, MULTI> t;
     t.tid = tid;
     t.nu1 = args.nu1;
     t.nu2 = args.nu2;
@@ -410,25 +427,31 @@ __global__ __launch_bounds__(K == 6 ? 1024 : K == 5 ? 256 : 64) void k_tail2d(Ta
         for (int k = 0; k < 4; ++k) lds.top.v[k][(r + 1) * P + p] = u[k];
     }
     __syncthreads();
-    if constexpr (FMG) t.template fmg<K>(lds, u, f);
-    else t.template visit<K>(lds, u, f, true);
+    if constexpr (FMG) {
+        t.template fmg<K>(lds, u, f, args.cycle);
+    } else if constexpr (MULTI) {
+        for (int v = 0; v < args.visits; ++v)
+            t.template visit<K>(lds, u, f, v == args.visits - 1, t.next_kind(v, args.cycle));
+    } else {
+        t.template visit<K>(lds, u, f, true, MG_CYCLE_V);
+    }
     S *b = (S *)L.B;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
         if (in[k]) T::st(b + (long long)(i - 1 + di[k]) + (long long)(j - 1 + dj[k]) * L.pitch, u[k]);
 }
 
-template <class S, class F, bool VC, bool FMG>
+template <class S, class F, bool VC, bool FMG, bool MULTI>
 static hipError_t tail2d_n(const TailArgs &a, const LevelDesc &L, hipStream_t s)
 {
     switch (L.n) {
-    case 7: hipLaunchKernelGGL((k_tail2d<S, F, VC, 3, FMG>), dim3(a.nsys), dim3(64), 0, s, a, L); break;
-    case 15: hipLaunchKernelGGL((k_tail2d<S, F, VC, 4, FMG>), dim3(a.nsys), dim3(64), 0, s, a, L); break;
-    case 31: hipLaunchKernelGGL((k_tail2d<S, F, VC, 5, FMG>), dim3(a.nsys), dim3(256), 0, s, a, L); break;
+    case 7: hipLaunchKernelGGL((k_tail2d<S, F, VC, 3, FMG, MULTI>), dim3(a.nsys), dim3(64), 0, s, a, L); break;
+    case 15: hipLaunchKernelGGL((k_tail2d<S, F, VC, 4, FMG, MULTI>), dim3(a.nsys), dim3(64), 0, s, a, L); break;
+    case 31: hipLaunchKernelGGL((k_tail2d<S, F, VC, 5, FMG, MULTI>), dim3(a.nsys), dim3(256), 0, s, a, L); break;
     case 63:
         // FP64 faces of four levels do not fit in the registers of 1024 threads
         if constexpr (!(VC && sizeof(S) == 8)) {
-            hipLaunchKernelGGL((k_tail2d<S, F, VC, 6, FMG>), dim3(a.nsys), dim3(1024), 0, s, a, L);
+            hipLaunchKernelGGL((k_tail2d<S, F, VC, 6, FMG, MULTI>), dim3(a.nsys), dim3(1024), 0, s, a, L);
             break;
         }
         return hipErrorInvalidValue;
@@ -444,14 +467,20 @@ bool tail2d_supported(int st, bool vc, int n_top, int m)
     return n_top == 7 || n_top == 15 || n_top == 31;
 }
 
+template <class S, class F, bool FMG>
+static hipError_t tail2d_s(bool vc, const TailArgs &a, const LevelDesc &L, hipStream_t s)
+{
+    if (a.cycle != MG_CYCLE_V)
+        return vc ? tail2d_n<S, F, true, FMG, true>(a, L, s) : tail2d_n<S, F, false, FMG, true>(a, L, s);
+    return vc ? tail2d_n<S, F, true, FMG, false>(a, L, s) : tail2d_n<S, F, false, FMG, false>(a, L, s);
+}
+
 hipError_t launch_tail2d(int st, bool vc, bool fmg, const TailArgs &a, const LevelDesc &L, hipStream_t s)
 {
     switch (st) {
-    case ST_F64:
-        if (fmg) return vc ? tail2d_n<double, double, true, true>(a, L, s) : tail2d_n<double, double, false, true>(a, L, s);
-        return vc ? tail2d_n<double, double, true, false>(a, L, s) : tail2d_n<double, double, false, false>(a, L, s);
-    case ST_F32: return vc ? tail2d_n<float, float, true, false>(a, L, s) : tail2d_n<float, float, false, false>(a, L, s);
-    case ST_BF16: return vc ? tail2d_n<bf16_t, float, true, false>(a, L, s) : tail2d_n<bf16_t, float, false, false>(a, L, s);
+    case ST_F64: return fmg ? tail2d_s<double, double, true>(vc, a, L, s) : tail2d_s<double, double, false>(vc, a, L, s);
+    case ST_F32: return tail2d_s<float, float, false>(vc, a, L, s);
+    case ST_BF16: return tail2d_s<bf16_t, float, false>(vc, a, L, s);
     }
     return hipErrorInvalidValue;
 }

@@ -1108,13 +1108,13 @@ mg_status enqueue_tail(mg_handle_s *h, hipStream_t st, int list)
     }
     const double tb = (double)h->nsys * level_points(h->tail_top, h->dim) * (h->fs + state_bytes(h->st));
     const int pi = prof_begin(h, "tail", tb, st);
-    // the 2D red-black V-cycle, and full multigrid of V-cycles, have a
-    // register-resident form (the others -- W / F schedules, Jacobi, a 1-point
-    // coarsest grid -- run level by level in LDS: 11.8 us against 29 for
-    // 63 .. 3 in FP64)
-    const bool fmg_v = list == TL_FMG && h->opt.cycle == MG_CYCLE_V && h->st == ST_F64;
-    if ((list < 0 || fmg_v) && h->dim == 2 && t.smoother == 0 && tail2d_supported(h->st, h->vc, h->tail_top, h->tail_m)) {
-        HIPCHK(h, launch_tail2d(h->st, h->vc, fmg_v, t, h->tail_descs[0], st));
+    // the 2D red-black cycles and full multigrid have a register-resident form
+    // (Jacobi and a 1-point coarsest grid run level by level in LDS: 11.8 us
+    // against 29 for a V-cycle 63 .. 3 in FP64)
+    t.cycle = list < 0 ? MG_CYCLE_V : h->opt.cycle;
+    t.visits = list == TL_PAIR ? 2 : 1;
+    if ((list != TL_FMG || h->st == ST_F64) && h->dim == 2 && t.smoother == 0 && tail2d_supported(h->st, h->vc, h->tail_top, h->tail_m)) {
+        HIPCHK(h, launch_tail2d(h->st, h->vc, list == TL_FMG, t, h->tail_descs[0], st));
         prof_end(h, pi, st);
         return MG_OK;
     }

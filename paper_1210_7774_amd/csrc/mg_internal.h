@@ -243,6 +243,7 @@ struct TailArgs {
     int faces;                // 2D diffusion: face weights precomputed in LDS (the LDS holds them)
     const int *ops;           // device: a schedule of level operations (W / F cycles, full
     int nops;                 //   multigrid), or null for the V-cycle
+    int cycle, visits;        // k_tail2d: cycle type of the top level's visits (the first of them), and how many
 };
 // Operations of a tail schedule: op = kind | level << 4 | sweeps << 12 (level
 // relative to the tail's top level)
