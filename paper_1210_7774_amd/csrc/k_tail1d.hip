@@ -11,12 +11,15 @@
 // each); the level-by-level LDS form (k_tail.hip) paid an LDS round trip and a
 // barrier of 16 wavefronts for each: an FP64 cycle of 1023 points takes 8.7 us
 // from call to call, against 26.6 (2047: 11.5 against 31.5; 31: 8.0 against 13.3).
+// W and F cycles repeat the visits of the levels below (solves of one cycle:
+// 1023 FP64 W 1519 -> 221 us, 2047 F 190 -> 68, 1023 FP32 F 279 -> 77).
 //
 // k_solve1d keeps the solve in the registers too: the residual norm and the
 // stop test follow each cycle in the wavefront (the other forms launch a norm
 // and a stop-test kernel per cycle), so a solve is one launch: 1023 points FP64
 // 71 -> 23 us (11.2 us of it the kernel), 2047 75 -> 26, 31 55 -> 17.
 #include "dev_common.h"
+#include "mg.h"
 
 namespace mgx {
 
@@ -89,9 +92,23 @@ struct Tail1 {
         }
     }
 
-    // One V-cycle visit of the level of 2^K - 1 points.
-    template <int K>
-    __device__ __forceinline__ void visit(C (&u)[per(K)], const C (&f)[per(K)])
+    // The visits of a level by one visit of its parent: one (V), two W visits,
+    // or an F and then a V visit, the second from the first's result.
+    template <int K, bool MULTI>
+    __device__ __forceinline__ void below(C (&u)[per(K)], const C (&f)[per(K)], int kind)
+    {
+        if constexpr (MULTI && K > 1) {
+            const int visits = kind == MG_CYCLE_V ? 1 : 2;
+            for (int v = 0; v < visits; ++v) visit<K, true>(u, f, v > 0 && kind == MG_CYCLE_F ? MG_CYCLE_V : kind);
+        } else {
+            visit<K, MULTI>(u, f, kind);
+        }
+    }
+
+    // One visit of the level of 2^K - 1 points, by a cycle of the given kind (V
+    // unless MULTI).
+    template <int K, bool MULTI>
+    __device__ __forceinline__ void visit(C (&u)[per(K)], const C (&f)[per(K)], int kind)
     {
         if constexpr (K == 1) {
             // one unknown: FP64 inverse times rhs
@@ -113,7 +130,7 @@ struct Tail1 {
                     cu[s] = (C)0;
                 }
                 if (!in<K - 1>(mc - 1)) cf[mc - 1] = (C)0;
-                visit<K - 1>(cu, cf);
+                below<K - 1, MULTI>(cu, cf, kind);
                 const C left = from_prev(cu[mc - 1]);
 #pragma unroll
                 for (int s = 0; s < mc; ++s) {
@@ -130,7 +147,7 @@ struct Tail1 {
                 v = __shfl(v * (C)0.25, (2 * lane + 1) & 63, 64);
                 cf[0] = lane < nc ? v : (C)0;
                 cu[0] = (C)0;
-                visit<K - 1>(cu, cf);
+                below<K - 1, MULTI>(cu, cf, kind);
                 const int i = lane + 1, il = i >> 1, ir = (i + 1) >> 1;  // coarse indices left and right of i
                 const C a = __shfl(cu[0], (il - 1) & 63, 64), b = __shfl(cu[0], (ir - 1) & 63, 64);
                 const C cl = il >= 1 && il <= nc ? a : (C)0, cr = ir <= nc ? b : (C)0;
@@ -144,9 +161,9 @@ struct Tail1 {
 
 }  // namespace
 
-// The tail of a 1D handle whose whole hierarchy is the tail: one V-cycle on
-// the level L.
-template <class S, class F, int K>
+// The tail of a 1D handle whose whole hierarchy is the tail: one cycle on the
+// level L.
+template <class S, class F, int K, bool MULTI>
 __global__ __launch_bounds__(64) void k_tail1d(TailArgs args, LevelDesc L)
 {
     using T1 = Tail1<S>;
@@ -164,7 +181,7 @@ __global__ __launch_bounds__(64) void k_tail1d(TailArgs args, LevelDesc L)
         u[s] = ok && !L.uzero ? (C)Traits<S>::ld((const S *)L.B + i) : (C)0;
     }
     if (done) return;
-    t.template visit<K>(u, f);
+    t.template visit<K, MULTI>(u, f, args.cycle);
 #pragma unroll
     for (int s = 0; s < m; ++s)
         if (m * lane + s < n) Traits<S>::st((S *)L.B + m * lane + s, u[s]);
@@ -227,7 +244,7 @@ __global__ __launch_bounds__(64) void k_solve1d(double *u_, const double *f_, co
     };
     if (first) norm();
     for (int c = 0; c < cycles && !done; ++c) {
-        t.template visit<K>(u, f);
+        t.template visit<K, false>(u, f, MG_CYCLE_V);
         norm();
     }
 #pragma unroll
@@ -263,10 +280,13 @@ template <class S, class F>
 static hipError_t tail1d_n(const TailArgs &a, const LevelDesc &L, hipStream_t s)
 {
     const int n = L.n;
-#define MGX_T1_GO(K)                                                                        \
-    {                                                                                       \
-        hipLaunchKernelGGL((k_tail1d<S, F, K>), dim3(1), dim3(64), 0, s, a, L);             \
-        return hipGetLastError();                                                           \
+#define MGX_T1_GO(K)                                                                              \
+    {                                                                                             \
+        if (a.cycle != MG_CYCLE_V)                                                                \
+            hipLaunchKernelGGL((k_tail1d<S, F, K, true>), dim3(1), dim3(64), 0, s, a, L);         \
+        else                                                                                      \
+            hipLaunchKernelGGL((k_tail1d<S, F, K, false>), dim3(1), dim3(64), 0, s, a, L);        \
+        return hipGetLastError();                                                                 \
     }
     MGX_T1_CASES(MGX_T1_GO)
 #undef MGX_T1_GO

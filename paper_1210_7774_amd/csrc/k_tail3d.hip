@@ -14,12 +14,20 @@
 //
 // Latency bound, about 25 dependent phases; the level-by-level LDS form
 // (k_tail.hip) took 29.8 us (FP32) and 35.4 us (FP64) a cycle, this one 9.2 and
-// 14.1 us.
+// 14.1 us.  W and F cycles repeat the visits of the levels below (solves of 7
+// cycles: 63^3 FP32 W 1897 -> 810 us, FP64 F 1262 -> 813, 127^3 FP32 F 1879 -> 1477).
 #include "dev_common.h"
+#include "mg.h"
 
 namespace mgx {
 
 namespace {
+
+// the cycle type of a level's v-th visit in one visit of its parent
+__device__ __forceinline__ int t3_next_kind(int v, int kind)
+{
+    return v > 0 && kind == MG_CYCLE_F ? MG_CYCLE_V : kind;
+}
 
 __device__ __forceinline__ void t3_wave_sync()
 {
@@ -110,10 +118,10 @@ struct Tail3 {
         }
     }
 
-    // One V-cycle visit of level K from the state u (its arrays are in LDS)
-    // with rhs f.
-    template <int K>
-    __device__ __forceinline__ void visit(T3Lds<C, K> &lds, C (&u)[8], const C (&f)[8], bool last)
+    // One visit of level K from the state u (its arrays are in LDS) with rhs f,
+    // by a cycle of the given kind (V unless MULTI).
+    template <int K, bool MULTI>
+    __device__ __forceinline__ void visit(T3Lds<C, K> &lds, C (&u)[8], const C (&f)[8], bool last, int kind)
     {
         constexpr int P = 1 << (K - 1);
         constexpr C ih2 = (C)(double)(1LL << (2 * K));
@@ -183,7 +191,13 @@ struct Tail3 {
                 B.v[d][(cz + 1) * B.ZS + (cy + 1) * B.YS + cx] = (C)0;
             }
             t3_wave_sync();
-            visit<K - 1>(lds.below, cu, cf, true);
+            if constexpr (MULTI) {
+                const int visits = kind == MG_CYCLE_V ? 1 : 2;
+                for (int v = 0; v < visits; ++v)
+                    visit<K - 1, true>(lds.below, cu, cf, v == visits - 1, t3_next_kind(v, kind));
+            } else {
+                visit<K - 1, false>(lds.below, cu, cf, true, kind);
+            }
 #pragma unroll
             for (int d = 0; d < 8; ++d)
                 L.uc[((2 * cz + 1 + (d >> 2)) * U1 + 2 * cy + 1 + ((d >> 1) & 1)) * U1 + 2 * cx + 1 + (d & 1)] = cu[d];
@@ -238,7 +252,7 @@ __device__ __forceinline__ void t3_zero(T3Lds<C, K> &lds, int tid, int nt)
 
 }  // namespace
 
-template <class S, class F, int K>
+template <class S, class F, int K, bool MULTI>
 __global__ __launch_bounds__(K == 4 ? 512 : 64) void k_tail3d(TailArgs args, LevelDesc L)
 {
     using T = Traits<S>;
@@ -274,7 +288,12 @@ __global__ __launch_bounds__(K == 4 ? 512 : 64) void k_tail3d(TailArgs args, Lev
     for (int d = 0; d < 8; ++d) lds.top.v[d][(pz + 1) * Lv::ZS + (py + 1) * Lv::YS + px] = u[d];
     __syncthreads();
     Tail3<S> t{tid, args.nu1, args.nu2, cinv};
-    t.template visit<K>(lds, u, f, true);
+    if constexpr (MULTI) {
+        for (int v = 0; v < args.visits; ++v)
+            t.template visit<K, true>(lds, u, f, v == args.visits - 1, t3_next_kind(v, args.cycle));
+    } else {
+        t.template visit<K, false>(lds, u, f, true, MG_CYCLE_V);
+    }
     S *b = (S *)L.B;
 #pragma unroll
     for (int d = 0; d < 8; ++d)
@@ -283,14 +302,19 @@ __global__ __launch_bounds__(K == 4 ? 512 : 64) void k_tail3d(TailArgs args, Lev
 
 bool tail3d_supported(int n_top, int m) { return m == 27 && (n_top == 7 || n_top == 15); }
 
+template <class S, class F, bool MULTI>
+static hipError_t tail3d_k(const TailArgs &a, const LevelDesc &L, hipStream_t s)
+{
+    if (a.nsys != 1) return hipErrorInvalidValue;
+    if (L.n == 15) hipLaunchKernelGGL((k_tail3d<S, F, 4, MULTI>), dim3(1), dim3(512), 0, s, a, L);
+    else if (L.n == 7) hipLaunchKernelGGL((k_tail3d<S, F, 3, MULTI>), dim3(1), dim3(64), 0, s, a, L);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
 template <class S, class F>
 static hipError_t tail3d_n(const TailArgs &a, const LevelDesc &L, hipStream_t s)
 {
-    if (a.nsys != 1) return hipErrorInvalidValue;
-    if (L.n == 15) hipLaunchKernelGGL((k_tail3d<S, F, 4>), dim3(1), dim3(512), 0, s, a, L);
-    else if (L.n == 7) hipLaunchKernelGGL((k_tail3d<S, F, 3>), dim3(1), dim3(64), 0, s, a, L);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+    return a.cycle != MG_CYCLE_V ? tail3d_k<S, F, true>(a, L, s) : tail3d_k<S, F, false>(a, L, s);
 }
 
 hipError_t launch_tail3d(int st, const TailArgs &a, const LevelDesc &L, hipStream_t s)

@@ -1120,13 +1120,13 @@ mg_status enqueue_tail(mg_handle_s *h, hipStream_t st, int list)
     }
     // and a 1D hierarchy that is all tail (1023 .. 1, FP64: 8.7 us a call
     // against 26.6)
-    if (list < 0 && h->dim == 1 && t.smoother == 0 && h->sys[0].lt == 0 && tail1d_supported(h->tail_top, h->tail_m)) {
+    if ((list < 0 || list == TL_SELF) && h->dim == 1 && t.smoother == 0 && h->sys[0].lt == 0 && tail1d_supported(h->tail_top, h->tail_m)) {
         HIPCHK(h, launch_tail1d(h->st, t, h->tail_descs[0], st));
         prof_end(h, pi, st);
         return MG_OK;
     }
-    // and so has the 3D one (15 .. 3, FP64: 14.1 us against 35)
-    if (list < 0 && h->dim == 3 && t.smoother == 0 && tail3d_supported(h->tail_top, h->tail_m)) {
+    // and so have the 3D cycles (15 .. 3, FP64 V: 14.1 us against 35)
+    if (list != TL_FMG && h->dim == 3 && t.smoother == 0 && tail3d_supported(h->tail_top, h->tail_m)) {
         HIPCHK(h, launch_tail3d(h->st, t, h->tail_descs[0], st));
         prof_end(h, pi, st);
         return MG_OK;
