@@ -5,10 +5,10 @@
 //   up:    bilinear/trilinear prolongation + correction, nu2 sweeps
 // It reads the top level's rhs and writes its final state.  These levels are
 // far too small to fill the GPU, so they run back to back in one launch
-// instead of a dozen latency-bound ones.  The red-black cycles (in 2D also full
-// multigrid) have register-resident forms in k_tail1d.hip, k_tail2d.hip and
-// k_tail3d.hip; this form runs the rest: Jacobi, full multigrid in 1D and 3D,
-// coarsest grids other than 3^d (1D: 1 point), and 1D hierarchies above 2047
+// instead of a dozen latency-bound ones.  The red-black cycles (in 1D and 2D
+// also full multigrid) have register-resident forms in k_tail1d.hip,
+// k_tail2d.hip and k_tail3d.hip; this form runs the rest: Jacobi, full multigrid
+// in 3D, coarsest grids other than 3^d (1D: 1 point), and 1D hierarchies above 2047
 // points or below 31.
 #include "dev_common.h"
 

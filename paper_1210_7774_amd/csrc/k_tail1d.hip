@@ -12,7 +12,9 @@
 // barrier of 16 wavefronts for each: an FP64 cycle of 1023 points takes 8.7 us
 // from call to call, against 26.6 (2047: 11.5 against 31.5; 31: 8.0 against 13.3).
 // W and F cycles repeat the visits of the levels below (solves of one cycle:
-// 1023 FP64 W 1519 -> 221 us, 2047 F 190 -> 68, 1023 FP32 F 279 -> 77).
+// 1023 FP64 W 1519 -> 221 us, 2047 F 190 -> 68, 1023 FP32 F 279 -> 77).  Full
+// multigrid carries the rhs down first (solves with a full-multigrid start and
+// no further cycle: 1023 169 -> 56 us, of F cycles 486 -> 98).
 //
 // k_solve1d keeps the solve in the registers too: the residual norm and the
 // stop test follow each cycle in the wavefront (the other forms launch a norm
@@ -92,6 +94,55 @@ struct Tail1 {
         }
     }
 
+    // full weighting of a level's values onto the next coarser level
+    template <int K>
+    __device__ __forceinline__ void weight(const C (&r)[per(K)], C (&cf)[per(K - 1)])
+    {
+        constexpr int m = per(K), mc = per(K - 1);
+        if constexpr (m > 1) {
+            // coarse point s of the lane sits on its fine point 2 s + 1
+            const C right = from_next(r[0]);
+#pragma unroll
+            for (int s = 0; s < mc; ++s) {
+                C v = r[2 * s];
+                v = v + (C)2 * r[2 * s + 1];
+                v = v + (2 * s + 2 < m ? r[2 * s + 2 < m ? 2 * s + 2 : 0] : right);
+                cf[s] = v * (C)0.25;
+            }
+            if (!in<K - 1>(mc - 1)) cf[mc - 1] = (C)0;
+        } else {
+            // one point a lane: coarse point I on fine point 2 I, packed to lane I - 1
+            C v = from_prev(r[0]);
+            v = v + (C)2 * r[0];
+            v = v + from_next(r[0]);
+            v = __shfl(v * (C)0.25, (2 * lane + 1) & 63, 64);
+            cf[0] = lane < (1 << (K - 1)) - 1 ? v : (C)0;
+        }
+    }
+
+    // u += the interpolation of the next coarser level's state
+    template <int K>
+    __device__ __forceinline__ void interpolate(const C (&cu)[per(K - 1)], C (&u)[per(K)])
+    {
+        constexpr int m = per(K), mc = per(K - 1);
+        if constexpr (m > 1) {
+            const C left = from_prev(cu[mc - 1]);
+#pragma unroll
+            for (int s = 0; s < mc; ++s) {
+                const C l = s > 0 ? cu[s > 0 ? s - 1 : 0] : left;
+                u[2 * s] = T::rnd(u[2 * s] + (l + cu[s]) * (C)0.5);
+                u[2 * s + 1] = s + 1 < mc || in<K>(2 * s + 1) ? T::rnd(u[2 * s + 1] + cu[s]) : (C)0;
+            }
+        } else {
+            constexpr int nc = (1 << (K - 1)) - 1;
+            const int i = lane + 1, il = i >> 1, ir = (i + 1) >> 1;  // coarse indices left and right of i
+            const C a = __shfl(cu[0], (il - 1) & 63, 64), b = __shfl(cu[0], (ir - 1) & 63, 64);
+            const C cl = il >= 1 && il <= nc ? a : (C)0, cr = ir <= nc ? b : (C)0;
+            const C corr = (i & 1) ? (cl + cr) * (C)0.5 : cl;
+            u[0] = in<K>(0) ? T::rnd(u[0] + corr) : (C)0;
+        }
+    }
+
     // The visits of a level by one visit of its parent: one (V), two W visits,
     // or an F and then a V visit, the second from the first's result.
     template <int K, bool MULTI>
@@ -114,47 +165,35 @@ struct Tail1 {
             // one unknown: FP64 inverse times rhs
             u[0] = lane == 0 ? T::rnd((C)(cinv * (double)f[0])) : (C)0;
         } else {
-            constexpr int m = per(K), mc = per(K - 1);
+            constexpr int mc = per(K - 1);
             smooth<K>(u, f, nu1);
-            C r[m], cf[mc], cu[mc];
+            C r[per(K)], cf[mc], cu[mc];
             residual<K>(u, f, r);
-            if constexpr (m > 1) {
-                // coarse point s of the lane sits on its fine point 2 s + 1
-                const C right = from_next(r[0]);
+            weight<K>(r, cf);
 #pragma unroll
-                for (int s = 0; s < mc; ++s) {
-                    C v = r[2 * s];
-                    v = v + (C)2 * r[2 * s + 1];
-                    v = v + (2 * s + 2 < m ? r[2 * s + 2 < m ? 2 * s + 2 : 0] : right);
-                    cf[s] = v * (C)0.25;
-                    cu[s] = (C)0;
-                }
-                if (!in<K - 1>(mc - 1)) cf[mc - 1] = (C)0;
-                below<K - 1, MULTI>(cu, cf, kind);
-                const C left = from_prev(cu[mc - 1]);
-#pragma unroll
-                for (int s = 0; s < mc; ++s) {
-                    const C l = s > 0 ? cu[s > 0 ? s - 1 : 0] : left;
-                    u[2 * s] = T::rnd(u[2 * s] + (l + cu[s]) * (C)0.5);
-                    u[2 * s + 1] = s + 1 < mc || in<K>(2 * s + 1) ? T::rnd(u[2 * s + 1] + cu[s]) : (C)0;
-                }
-            } else {
-                // one point a lane: coarse point I on fine point 2 I, packed to lane I - 1
-                constexpr int nc = (1 << (K - 1)) - 1;
-                C v = from_prev(r[0]);
-                v = v + (C)2 * r[0];
-                v = v + from_next(r[0]);
-                v = __shfl(v * (C)0.25, (2 * lane + 1) & 63, 64);
-                cf[0] = lane < nc ? v : (C)0;
-                cu[0] = (C)0;
-                below<K - 1, MULTI>(cu, cf, kind);
-                const int i = lane + 1, il = i >> 1, ir = (i + 1) >> 1;  // coarse indices left and right of i
-                const C a = __shfl(cu[0], (il - 1) & 63, 64), b = __shfl(cu[0], (ir - 1) & 63, 64);
-                const C cl = il >= 1 && il <= nc ? a : (C)0, cr = ir <= nc ? b : (C)0;
-                const C corr = (i & 1) ? (cl + cr) * (C)0.5 : cl;
-                u[0] = in<K>(0) ? T::rnd(u[0] + corr) : (C)0;
-            }
+            for (int s = 0; s < mc; ++s) cu[s] = (C)0;
+            below<K - 1, MULTI>(cu, cf, kind);
+            interpolate<K>(cu, u);
             smooth<K>(u, f, nu2);
+        }
+    }
+
+    // Full multigrid from this level: f carried down by full weighting, the
+    // coarsest level solved, then on each level the interpolated state and one
+    // visit.
+    template <int K>
+    __device__ __forceinline__ void fmg(C (&u)[per(K)], const C (&f)[per(K)], int kind)
+    {
+        if constexpr (K == 1) {
+            visit<1, true>(u, f, kind);
+        } else {
+            C cf[per(K - 1)], cu[per(K - 1)];
+            weight<K>(f, cf);
+            fmg<K - 1>(cu, cf, kind);
+#pragma unroll
+            for (int s = 0; s < per(K); ++s) u[s] = (C)0;
+            interpolate<K>(cu, u);
+            visit<K, true>(u, f, kind);
         }
     }
 };
@@ -162,8 +201,8 @@ struct Tail1 {
 }  // namespace
 
 // The tail of a 1D handle whose whole hierarchy is the tail: one cycle on the
-// level L.
-template <class S, class F, int K, bool MULTI>
+// level L, or one full-multigrid pass.
+template <class S, class F, int K, bool MULTI, bool FMG>
 __global__ __launch_bounds__(64) void k_tail1d(TailArgs args, LevelDesc L)
 {
     using T1 = Tail1<S>;
@@ -178,10 +217,11 @@ __global__ __launch_bounds__(64) void k_tail1d(TailArgs args, LevelDesc L)
         const int i = m * lane + s;
         const bool ok = i < n;
         f[s] = ok ? (C)gld((const F *)L.f + i) : (C)0;
-        u[s] = ok && !L.uzero ? (C)Traits<S>::ld((const S *)L.B + i) : (C)0;
+        u[s] = ok && !FMG && !L.uzero ? (C)Traits<S>::ld((const S *)L.B + i) : (C)0;
     }
     if (done) return;
-    t.template visit<K, MULTI>(u, f, args.cycle);
+    if constexpr (FMG) t.template fmg<K>(u, f, args.cycle);
+    else t.template visit<K, MULTI>(u, f, args.cycle);
 #pragma unroll
     for (int s = 0; s < m; ++s)
         if (m * lane + s < n) Traits<S>::st((S *)L.B + m * lane + s, u[s]);
@@ -276,30 +316,32 @@ bool tail1d_supported(int n, int m) { return m == 1 && n >= 31 && n <= 2047; }
     case 2047: GO(11);   \
     }
 
-template <class S, class F>
+template <class S, class F, bool MULTI, bool FMG>
 static hipError_t tail1d_n(const TailArgs &a, const LevelDesc &L, hipStream_t s)
 {
     const int n = L.n;
-#define MGX_T1_GO(K)                                                                              \
-    {                                                                                             \
-        if (a.cycle != MG_CYCLE_V)                                                                \
-            hipLaunchKernelGGL((k_tail1d<S, F, K, true>), dim3(1), dim3(64), 0, s, a, L);         \
-        else                                                                                      \
-            hipLaunchKernelGGL((k_tail1d<S, F, K, false>), dim3(1), dim3(64), 0, s, a, L);        \
-        return hipGetLastError();                                                                 \
+#define MGX_T1_GO(K)                                                                          \
+    {                                                                                         \
+        hipLaunchKernelGGL((k_tail1d<S, F, K, MULTI, FMG>), dim3(1), dim3(64), 0, s, a, L);   \
+        return hipGetLastError();                                                             \
     }
     MGX_T1_CASES(MGX_T1_GO)
 #undef MGX_T1_GO
     return hipErrorInvalidValue;
 }
+template <class S, class F>
+static hipError_t tail1d_c(const TailArgs &a, const LevelDesc &L, hipStream_t s)
+{
+    return a.cycle != MG_CYCLE_V ? tail1d_n<S, F, true, false>(a, L, s) : tail1d_n<S, F, false, false>(a, L, s);
+}
 
-hipError_t launch_tail1d(int st, const TailArgs &a, const LevelDesc &L, hipStream_t s)
+hipError_t launch_tail1d(int st, bool fmg, const TailArgs &a, const LevelDesc &L, hipStream_t s)
 {
     if (a.nsys != 1) return hipErrorInvalidValue;
     switch (st) {
-    case ST_F64: return tail1d_n<double, double>(a, L, s);
-    case ST_F32: return tail1d_n<float, float>(a, L, s);
-    case ST_BF16: return tail1d_n<bf16_t, float>(a, L, s);
+    case ST_F64: return fmg ? tail1d_n<double, double, true, true>(a, L, s) : tail1d_c<double, double>(a, L, s);
+    case ST_F32: return tail1d_c<float, float>(a, L, s);
+    case ST_BF16: return tail1d_c<bf16_t, float>(a, L, s);
     }
     return hipErrorInvalidValue;
 }

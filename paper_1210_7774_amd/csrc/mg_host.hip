@@ -1120,8 +1120,9 @@ mg_status enqueue_tail(mg_handle_s *h, hipStream_t st, int list)
     }
     // and a 1D hierarchy that is all tail (1023 .. 1, FP64: 8.7 us a call
     // against 26.6)
-    if ((list < 0 || list == TL_SELF) && h->dim == 1 && t.smoother == 0 && h->sys[0].lt == 0 && tail1d_supported(h->tail_top, h->tail_m)) {
-        HIPCHK(h, launch_tail1d(h->st, t, h->tail_descs[0], st));
+    if ((list != TL_FMG || h->st == ST_F64) && h->dim == 1 && t.smoother == 0 && h->sys[0].lt == 0 &&
+        tail1d_supported(h->tail_top, h->tail_m)) {
+        HIPCHK(h, launch_tail1d(h->st, list == TL_FMG, t, h->tail_descs[0], st));
         prof_end(h, pi, st);
         return MG_OK;
     }
@@ -1834,8 +1835,8 @@ void free_handle(mg_handle_s *h)
 bool use_solve1d(const mg_handle_s *h)
 {
     return h->dim == 1 && !h->ir && !h->batch && !h->vc && !h->learned && (!h->prof || h->prof_finest_only) &&
-           !h->opt.use_graph && h->opt.smoother == MG_SM_RBGS && h->opt.cycle == MG_CYCLE_V && !h->opt.fmg && h->sys[0].lt == 0 &&
-           tail1d_supported(h->sys[0].n, h->tail_m);
+           !h->opt.use_graph && h->opt.smoother == MG_SM_RBGS && h->opt.cycle == MG_CYCLE_V && !h->opt.fmg &&
+           h->sys[0].lt == 0 && tail1d_supported(h->sys[0].n, h->tail_m);
 }
 
 mg_status solve1d(mg_handle_s *h, double rtol, mg_stats *st)
