@@ -467,9 +467,11 @@ __global__ __launch_bounds__(256) void k_lwgrad(WgArgs a)
 #pragma unroll
                 for (int t = 0; t < 9; ++t) {
                     const short *r = t < 3 ? r0 : t < 6 ? r1 : r2;
+                    // (the left tap of the output pixel past the row's end reads the last
+                    // pixel, which has no such product: 0, not infinity times z = 0)
                     v4s ax;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) ax[q] = r[q + t % 3];
+                    for (int q = 0; q < 4; ++q) ax[q] = t % 3 == 0 && x0 + kq + q >= W ? (short)0 : r[q + t % 3];
                     acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ax, z, acc[t], 0, 0, 0);
                 }
 #pragma unroll
@@ -513,6 +515,11 @@ __global__ __launch_bounds__(256) void k_lwgrad(WgArgs a)
                 const int x = x0 + kq + q, yy = y + sy, xx = x + sx;
                 cv[q] = x < W ? ch[((long long)y * W + x) * 16 + c] : (bf16_t)0;
                 ov[q] = (c < 9 && x < W && yy >= 0 && yy < H && xx >= 0 && xx < W) ? one[(long long)yy * W + xx] : 0.f;
+                // layer 4: dy at a border pixel also meets the zeros around x3 (0
+                // unless dy is not finite)
+                const int yo = y - sy, xo = x - sx;
+                if (layer == 4 && c < 9 && x < W && (yo < 0 || yo >= H || xo < 0 || xo >= W))
+                    ov[q] += 0.f * one[(long long)y * W + x];
             }
             if (layer == 1) {
                 v4s av, bv;
