@@ -492,11 +492,16 @@ size_t carve(mg_handle_s *h, char *base)
             const long long m = (long long)L.n * (h->dim > 1 ? L.n : 1) * (h->dim > 2 ? L.n : 1);
             L.pitch = L.n;
             L.ppitch = (long long)L.n * L.n;
+            long long spare = m;
             if (l == 0 && !h->ir) {
                 L.pitch = S.pitch0;
                 L.ppitch = S.ppitch0;
+                // A is addressed with the caller's pitches (the 3D red-black
+                // passes keep it contiguous)
+                if (h->dim == 2 || (h->dim == 3 && h->opt.smoother == MG_SM_JACOBI))
+                    spare = (L.n - 1) * ((h->dim > 2 ? L.ppitch : 0) + L.pitch) + L.n;
             }
-            L.A = cv.take(ssz * m);
+            L.A = cv.take(ssz * spare);
             if (l > 0 || h->ir) {
                 L.B = cv.take(ssz * m);
                 L.f = cv.take((size_t)h->fs * m);
