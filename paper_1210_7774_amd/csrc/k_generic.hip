@@ -555,6 +555,17 @@ __global__ void k_fill_zero(uint32_t *p, long long nwords)
         p[q] = 0u;
 }
 
+// the grid points of an array with pitches, without what lies between its rows
+__global__ __launch_bounds__(256) void k_zero_points(double *u, int n, int dim, long long pitch, long long ppitch)
+{
+    const long long m = npts(n, dim);
+    for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < m; p += (long long)gridDim.x * blockDim.x) {
+        int i, j, k;
+        coords(p, n, dim, i, j, k);
+        u[(long long)(i - 1) + (long long)(j - 1) * pitch + (long long)(k - 1) * ppitch] = 0.0;
+    }
+}
+
 template <class S, int DIM>
 __global__ __launch_bounds__(256) void k_copy_state(GenArgs g, const S *src, S *dst)
 {
@@ -1121,6 +1132,12 @@ hipError_t launch_fill_zero(void *p, long long bytes, hipStream_t s)
 {
     const long long nw = bytes / 4;
     hipLaunchKernelGGL(k_fill_zero, dim3(grid_for(nw)), dim3(256), 0, s, (uint32_t *)p, nw);
+    return hipGetLastError();
+}
+
+hipError_t launch_zero_points(double *u, int n, int dim, long long pitch, long long ppitch, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_zero_points, dim3(grid_for(npts(n, dim))), dim3(256), 0, s, u, n, dim, pitch, ppitch);
     return hipGetLastError();
 }
 

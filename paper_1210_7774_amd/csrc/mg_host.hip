@@ -1992,10 +1992,8 @@ mg_status solve_loop(mg_handle_s *h, double rtol, std::vector<mg_stats *> stats)
         // stopped by the first norm (a zero or non-finite f, a tolerance of 1
         // or more): no cycle wrote u
         Sys &S = h->sys[0];
-        if (S.pitch0 == S.n && (h->dim < 3 || S.ppitch0 == (long long)S.n * S.n)) {
-            HIPCHK(h, launch_fill_zero(S.u, (long long)sizeof(double) * level_points(S.n, h->dim), h->stream));
-            HIPCHK(h, hipStreamSynchronize(h->stream));
-        }
+        HIPCHK(h, launch_zero_points(S.u, S.n, h->dim, S.pitch0, S.ppitch0, h->stream));
+        HIPCHK(h, hipStreamSynchronize(h->stream));
     }
     mg_status worst = MG_OK;
     for (int s = 0; s < h->nsys; ++s) {

@@ -201,6 +201,8 @@ hipError_t launch_jacobi(int st, bool vc, const GenArgs &g, hipStream_t s);
 hipError_t launch_resid_restrict(int st, bool vc, const GenArgs &g, hipStream_t s);
 hipError_t launch_prolong_correct(int st, const GenArgs &g, hipStream_t s);
 hipError_t launch_fill_zero(void *p, long long bytes, hipStream_t s);
+// u = 0 at the n^dim points of an FP64 array (pitches in elements)
+hipError_t launch_zero_points(double *u, int n, int dim, long long pitch, long long ppitch, hipStream_t s);
 // full multigrid: fc = R f on a level (rhs type by st), B = P Bc (set)
 hipError_t launch_restrict_rhs(int st, const GenArgs &g, hipStream_t s);
 hipError_t launch_interp(int st, const GenArgs &g, hipStream_t s);

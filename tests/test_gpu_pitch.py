@@ -70,3 +70,24 @@ def test_padded_solve(dim, n, row, plane, opts, vc):
     assert torch.equal(uv, uc)
     uv.fill_(FILL)
     assert bool((ut == FILL).all())
+
+
+@pytest.mark.parametrize("dim,n,row,plane,fmg", [(3, 31, 34, 31, 0), (3, 31, 31, 33, 0), (3, 63, 70, 64, 0),
+                                                 (3, 31, 34, 33, 1), (2, 63, 65, 0, 1), (2, 255, 260, 0, 1)])
+def test_padded_zero_start(dim, n, row, plane, fmg):
+    """u is not read; a solve that its first norm ends (a tolerance of 1, f = 0)
+    leaves u = 0."""
+    print("padded zero start", dim, n, row, plane, fmg, flush=True)
+    fn = torch.from_numpy(np.ascontiguousarray(I.normal_rhs(n, dim, 55))).to("cuda")
+    for rtol, rhs in ((1e-9, fn), (1.0, fn), (1e-9, torch.zeros_like(fn))):
+        uc = torch.full_like(fn, FILL)
+        want = solve(n, dim, uc, rhs, n, n, rtol, zero_start=1, fmg=fmg)
+        (ut, uv), (ft, fv) = padded(n, dim, row, plane), padded(n, dim, row, plane)
+        fv.copy_(rhs)
+        got = solve(n, dim, ut, ft, row, plane, rtol, zero_start=1, fmg=fmg)
+        assert got == want
+        assert torch.equal(uv, uc)
+        if want[1] == 0:
+            assert float(uv.abs().max()) == 0.0
+        uv.fill_(FILL)
+        assert bool((ut == FILL).all())
