@@ -800,6 +800,12 @@ hipError_t launch_norm_batch(const NormItem *items, int nitems, const NormSys *s
     return hipGetLastError();
 }
 
+// (the host may poll this flag while the stream runs on)
+__device__ __forceinline__ void publish_done(SolveState *pub, int done)
+{
+    __hip_atomic_store(&pub->done, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // ---- reduction of the partial sums + stop test: one workgroup per system ----
 // part0 / nparts: per-system slot ranges (device), or null for one system
 // whose slots are [slot0, slot0 + nslots).
@@ -843,7 +849,7 @@ __global__ __launch_bounds__(256) void k_norm_finish(SolveState *states, const d
             if (tid == 0) {
                 pub[sys].nres = k;
                 pub[sys].rel = rel0;
-                pub[sys].done = done0;
+                publish_done(pub + sys, done0);
             }
         }
         return;
@@ -895,7 +901,7 @@ __global__ __launch_bounds__(256) void k_norm_finish(SolveState *states, const d
         if (k <= 200) pub[sys].hist[k] = rel;
         pub[sys].nres = k + 1;
         pub[sys].rel = rel;
-        pub[sys].done = done;
+        publish_done(pub + sys, done);
     }
 }
 

@@ -192,6 +192,8 @@ struct mg_handle_s {
     bool publish = false;     // the norms being enqueued also write the host's copy of the states
     SolveState *d_pub = nullptr;  // device address of h_states
     StateInit init{};         // state set by the next first norm (init.on)
+    int ahead = -1;           // launches still allowed before the first norm is looked at (-1: none awaited)
+    bool ended = false;       // the first norm ended the solve
 };
 
 #define HIPCHK(h, call)                                                   \
@@ -869,12 +871,63 @@ double smooth_bytes(mg_handle_s *h, int l, double pts)
     return pts * (2 * sb + h->fs);
 }
 
+// ---- the first norm of a solve ------------------------------------------------
+// done is -1 in the host's copy of the states until the norm has run.
+void arm_published(mg_handle_s *h)
+{
+    for (int s = 0; s < h->nsys; ++s) __atomic_store_n(&h->h_states[s].done, -1, __ATOMIC_RELAXED);
+}
+
+int published(const mg_handle_s *h, int s) { return __atomic_load_n(&h->h_states[s].done, __ATOMIC_RELAXED); }
+
+// Polls until every system is published.  A stream that failed publishes
+// nothing: the calls that follow report it.  (A poll leaves the stream running; a
+// synchronisation has a marker to send and costs 15 to 20 us on an idle one, so
+// a chunk's end is not polled for: its synchronisation goes out with the chunk.)
+void await_published(const mg_handle_s *h)
+{
+    int s = 0;
+    for (unsigned spin = 1;; ++spin) {
+        while (s < h->nsys && published(h, s) >= 0) ++s;
+        if (s == h->nsys) return;
+        __builtin_ia32_pause();
+        if (spin % 4096 == 0) {
+            if (hipStreamQuery(h->stream) != hipErrorNotReady) return;
+            (void)hipGetLastError();
+        }
+    }
+}
+
+// Whether the solve being enqueued ended at its first norm: asked before every
+// level operation (of that many launches), which is then left out.  kAhead
+// launches go out behind the norm unseen, so that the GPU has work while the
+// host looks.  A solve whose guess already meets the tolerance (1023^2 FP64
+// diffusion, W cycles of 80 launches): 35 us, 421 with two cycles enqueued
+// unseen; 255^2 FP64 28, 65 unseen.  Solves with cycles take 0 to 4 us longer
+// than unseen with kAhead = 2, 6 to 14 with 0; four launches cost an ended
+// solve 5 to 7 us more.
+constexpr int kAhead = 2;
+bool ended_at_first_norm(mg_handle_s *h, int launches)
+{
+    if (h->ahead < 0) return h->ended;
+    if (h->ahead >= launches) {
+        h->ahead -= launches;
+        return false;
+    }
+    await_published(h);
+    h->ahead = -1;
+    h->ended = true;
+    for (int s = 0; s < h->nsys; ++s) h->ended = h->ended && published(h, s) > 0;
+    return h->ended;
+}
+
 // Enqueue one V-cycle of the working precision on every system.  March
 // groups and generic levels are interleaved by level size (down: finest
 // first; up: coarsest first): with the learned smoother the finest level is
 // generic while the coarser ones march.
 mg_status enqueue_march(mg_handle_s *h, const Group &g, bool post, hipStream_t st, bool keep = false)
 {
+    if (ended_at_first_norm(h, 1)) return MG_OK;
     MarchArgs a;
     std::memset(&a, 0, sizeof(a));
     a.levels = keep ? h->d_descs_keep : h->d_descs;
@@ -1048,6 +1101,7 @@ mg_status enqueue_m3(mg_handle_s *h, int s, int l, bool post, hipStream_t st, bo
 
 mg_status enqueue_generic_down(mg_handle_s *h, int s, int l, hipStream_t st, bool keep = false)
 {
+    if (ended_at_first_norm(h, h->m3 ? 1 : kAhead + 1)) return MG_OK;  // (a generic level: several launches)
     if (h->m3) return enqueue_m3(h, s, l, false, st, keep);
     Sys &S = h->sys[s];
     GenArgs g = gen_args(h, s, l);
@@ -1071,6 +1125,7 @@ mg_status enqueue_generic_down(mg_handle_s *h, int s, int l, hipStream_t st, boo
 
 mg_status enqueue_generic_up(mg_handle_s *h, int s, int l, hipStream_t st)
 {
+    if (ended_at_first_norm(h, h->m3 ? 1 : kAhead + 1)) return MG_OK;
     if (h->m3) return enqueue_m3(h, s, l, true, st);
     Sys &S = h->sys[s];
     GenArgs g = gen_args(h, s, l);
@@ -1090,6 +1145,7 @@ mg_status enqueue_generic_up(mg_handle_s *h, int s, int l, hipStream_t st)
 // of the handle's level-operation schedules (TailList).
 mg_status enqueue_tail(mg_handle_s *h, hipStream_t st, int list)
 {
+    if (ended_at_first_norm(h, 1)) return MG_OK;
     TailArgs t;
     std::memset(&t, 0, sizeof(t));
     t.levels = h->d_tail;
@@ -1145,7 +1201,7 @@ mg_status enqueue_tail(mg_handle_s *h, hipStream_t st, int list)
 // plain mode: the finest POST measured the residual; reduce + stop test
 mg_status enqueue_post_norm(mg_handle_s *h, hipStream_t st)
 {
-    if (!h->ir && h->sys[0].lv[0].march && h->norm_in_post) {
+    if (!h->ir && h->sys[0].lv[0].march && h->norm_in_post && !ended_at_first_norm(h, 1)) {
         const int pi = prof_begin(h, "norm_finish", 0.0, st);
         HIPCHK(h, launch_norm_finish(h->d_states, h->nsys, h->d_partials, h->d_part0, h->d_nparts, 0, 0, 0, StateInit{},
                                      h->publish ? h->d_pub : nullptr, st));
@@ -1192,7 +1248,7 @@ mg_status enqueue_visit(mg_handle_s *h, int l, int kind, bool keep, hipStream_t 
 mg_status enqueue_fmg(mg_handle_s *h, hipStream_t st)
 {
     Sys &S = h->sys[0];
-    for (int l = 0; l < S.lt; ++l) {
+    for (int l = 0; l < S.lt && !ended_at_first_norm(h, 1); ++l) {
         const GenArgs g = gen_args(h, 0, l);
         const int pi = prof_begin(h, lvname("fmg_restrict", S.lv[l].n),
                                   (double)(level_points(S.lv[l].n, h->dim) + level_points(S.lv[l + 1].n, h->dim)) *
@@ -1202,7 +1258,7 @@ mg_status enqueue_fmg(mg_handle_s *h, hipStream_t st)
     }
     mg_status rc = enqueue_tail(h, st, TL_FMG);
     if (rc != MG_OK) return rc;
-    for (int l = S.lt - 1; l >= 0; --l) {
+    for (int l = S.lt - 1; l >= 0 && !ended_at_first_norm(h, 1); --l) {
         const GenArgs g = gen_args(h, 0, l);
         const double sb = (double)state_bytes(h->st);
         const int pi = prof_begin(h, lvname("fmg_interp", S.lv[l].n),
@@ -1261,6 +1317,7 @@ mg_status enqueue_cycle(mg_handle_s *h, hipStream_t st)
 // IR: also writes the FP32 inner rhs.  first: measures ||f|| too.
 mg_status enqueue_outer_norm(mg_handle_s *h, int first, bool write_r32, hipStream_t st, bool u_zero = false)
 {
+    if (!first && ended_at_first_norm(h, 2)) return MG_OK;
     if (h->nsys == 1 && !h->batch) {
         Sys &S = h->sys[0];
         NormArgs a;
@@ -1318,7 +1375,7 @@ mg_status enqueue_ir_step(mg_handle_s *h, hipStream_t st)
     if (rc != MG_OK) return rc;
     for (int s = 0; s < h->nsys; ++s) {
         Sys &S = h->sys[s];
-        if (!S.lv[0].march && !(h->m3 && S.lt > 0)) {
+        if (!S.lv[0].march && !(h->m3 && S.lt > 0) && !ended_at_first_norm(h, 1)) {
             HIPCHK(h, launch_ir_correct(h->st, S.u, S.pitch0, S.ppitch0, S.lv[0].B, S.n, h->dim, h->d_states + s, st));
         }
     }
@@ -1378,12 +1435,14 @@ mg_status state_init(mg_handle_s *h, double tol, int maxc, hipStream_t st)
 }
 
 // A solve's first residual norm, which also sets the states up (the learned
-// smoother's ratio watch and the bf16-state stall rule as in state_init).
-mg_status enqueue_first_norm(mg_handle_s *h, double tol, int maxc, bool u_zero, bool publish = false)
+// smoother's ratio watch and the bf16-state stall rule as in state_init) and
+// publishes them (the stream is idle or does not write them before it).
+mg_status enqueue_first_norm(mg_handle_s *h, double tol, int maxc, bool u_zero)
 {
+    arm_published(h);
     h->init = StateInit{1, maxc, tol, (h->learned && h->learned_on) ? kLearnedFallback : 0.0,
                         h->st == ST_BF16 && tol >= 0.0 ? bf16_stall_ratio() : 0.0};
-    h->publish = publish;
+    h->publish = true;
     const mg_status rc = enqueue_outer_norm(h, 1, h->ir, h->stream, u_zero);
     h->publish = false;
     h->init = StateInit{};
@@ -1424,13 +1483,18 @@ mg_status enqueue_steps(mg_handle_s *h, int k)
 {
     mg_status rc = MG_OK;
     if (!h->prof && h->opt.use_graph) {
-        if (!h->graph_ok) {
-            h->publish = true;
-            rc = build_graph(h);
-            h->publish = false;
-            if (rc != MG_OK) return rc;
+        for (int i = 0; i < k && !ended_at_first_norm(h, 1); ++i) {
+            if (!h->graph_ok) {
+                const int ahead = h->ahead;  // (a captured step is a whole one)
+                h->ahead = -1;
+                h->publish = true;
+                rc = build_graph(h);
+                h->publish = false;
+                h->ahead = ahead;
+                if (rc != MG_OK) return rc;
+            }
+            HIPCHK(h, hipGraphLaunch(h->gexec, h->stream));
         }
-        for (int i = 0; i < k; ++i) HIPCHK(h, hipGraphLaunch(h->gexec, h->stream));
         return MG_OK;
     }
     for (int i = 0; i < k && rc == MG_OK; ++i) {
@@ -1880,31 +1944,43 @@ mg_status solve_loop(mg_handle_s *h, double rtol, std::vector<mg_stats *> stats)
         if (S.pitch0 != S.n || (h->dim == 3 && S.ppitch0 != (long long)S.n * S.n)) return MG_ERR_UNSUPPORTED;
         HIPCHK(h, launch_fill_zero(S.u, (long long)sizeof(double) * level_points(S.n, h->dim), h->stream));
     }
-    // The first norm sets the state up and the first cycles follow it without a
-    // look at it: an initial guess that already meets the tolerance (or is not
-    // finite) has them return at once.
+    // The first norm sets the state up; an initial guess that already meets the
+    // tolerance (or is not finite) needs no cycle, and the first ones are
+    // enqueued with an eye on it (a captured cycle is one launch of all its
+    // kernels, so it waits for the norm).
     h->prof_step = -1;
     rc = enqueue_first_norm(h, rtol, maxc, zs);
     if (rc != MG_OK) return rc;
     h->prof_step = 0;
     int enq = 0;
     int chunk = std::min(2, maxc);
-    if (h->opt.fmg || zs_head) {
-        // the first step is one full-multigrid pass, or a cycle from zero
-        // (enqueued directly, not part of the captured cycle)
-        h->first_zero = zs_head;
-        h->publish = maxc == 1;
-        rc = h->opt.fmg ? enqueue_fmg_step(h, h->stream) : enqueue_step(h, h->stream);
-        h->first_zero = h->publish = false;
-        if (rc != MG_OK) return rc;
-        if (h->prof) ++h->prof_step;
-        enq = 1;
-        chunk = std::min(1, maxc - 1);
-    }
-    if (chunk > 0) {
-        rc = enqueue_steps(h, chunk);
-        if (rc != MG_OK) return rc;
-        enq += chunk;
+    {
+        struct Watch {
+            mg_handle_s *h;
+            ~Watch()
+            {
+                h->ahead = -1;
+                h->ended = false;
+            }
+        } watch{h};
+        const bool direct = h->opt.fmg || zs_head;  // the first step is not the captured cycle
+        h->ahead = h->opt.use_graph && !h->prof && !direct ? 0 : kAhead;
+        if (direct) {
+            // the first step is one full-multigrid pass, or a cycle from zero
+            h->first_zero = zs_head;
+            h->publish = maxc == 1;
+            rc = h->opt.fmg ? enqueue_fmg_step(h, h->stream) : enqueue_step(h, h->stream);
+            h->first_zero = h->publish = false;
+            if (rc != MG_OK) return rc;
+            if (h->prof) ++h->prof_step;
+            enq = 1;
+            chunk = std::min(1, maxc - 1);
+        }
+        if (chunk > 0) {
+            rc = enqueue_steps(h, chunk);
+            if (rc != MG_OK) return rc;
+            enq += chunk;
+        }
     }
     bool fell_back = false;
     for (;;) {
@@ -1945,7 +2021,7 @@ mg_status solve_loop(mg_handle_s *h, double rtol, std::vector<mg_stats *> stats)
                         if (S.pitch0 != S.n) return MG_ERR_NONFINITE;
                         HIPCHK(h, launch_fill_zero(S.u, (long long)sizeof(double) * level_points(S.n, h->dim), h->stream));
                     }
-                    rc = enqueue_first_norm(h, rtol, maxc, false, true);
+                    rc = enqueue_first_norm(h, rtol, maxc, false);
                     if (rc != MG_OK) return rc;
                     enq = 0;
                 } else {
