@@ -302,8 +302,10 @@ __global__ __launch_bounds__(64) void k_solve1d(double *u_, const double *f_, co
 }
 
 // 32 points a lane (2047) fill the register file; 4095 would spill.  Below 31
-// nothing is gained by a form of its own (the LDS form is launch bound there).
+// nothing is gained by a cycle of its own (the LDS form is launch bound there),
+// but a solve is one launch instead of eight (7 points: 65 -> 20 us).
 bool tail1d_supported(int n, int m) { return m == 1 && n >= 31 && n <= 2047; }
+bool solve1d_supported(int n, int m) { return m == 1 && n <= 2047; }
 
 #define MGX_T1_CASES(GO) \
     switch (n) {         \
@@ -354,6 +356,12 @@ hipError_t launch_solve1d(int n, double *u, const double *f, const double *cinv,
         hipLaunchKernelGGL((k_solve1d<K>), dim3(1), dim3(64), 0, s, u, f, cinv, nu1, nu2, st, first, cycles,      \
                            zero ? 1 : 0, init, pub);                                                              \
         return hipGetLastError();                                                                                 \
+    }
+    switch (n) {
+    case 1: MGX_T1_GO(1);
+    case 3: MGX_T1_GO(2);
+    case 7: MGX_T1_GO(3);
+    case 15: MGX_T1_GO(4);
     }
     MGX_T1_CASES(MGX_T1_GO)
 #undef MGX_T1_GO

@@ -1905,7 +1905,7 @@ bool use_solve1d(const mg_handle_s *h)
 {
     return h->dim == 1 && !h->ir && !h->batch && !h->vc && !h->learned && (!h->prof || h->prof_finest_only) &&
            !h->opt.use_graph && h->opt.smoother == MG_SM_RBGS && h->opt.cycle == MG_CYCLE_V && !h->opt.fmg &&
-           h->sys[0].lt == 0 && tail1d_supported(h->sys[0].n, h->tail_m);
+           h->sys[0].lt == 0 && solve1d_supported(h->sys[0].n, h->tail_m);
 }
 
 mg_status solve1d(mg_handle_s *h, double rtol, mg_stats *st)

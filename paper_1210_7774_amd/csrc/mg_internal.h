@@ -267,6 +267,7 @@ hipError_t launch_tail3d(int st, const TailArgs &a, const LevelDesc &L, hipStrea
 // The 1D ones (k_tail1d.hip): one V-cycle of a hierarchy that is all tail, and
 // `cycles` cycles of an FP64 solve with their norms and stop tests.
 bool tail1d_supported(int n, int m);
+bool solve1d_supported(int n, int m);
 hipError_t launch_tail1d(int st, bool fmg, const TailArgs &a, const LevelDesc &L, hipStream_t s);
 hipError_t launch_solve1d(int n, double *u, const double *f, const double *cinv, int nu1, int nu2, SolveState *st,
                           int first, int cycles, bool zero, const StateInit &init, SolveState *pub, hipStream_t s);
