@@ -614,7 +614,7 @@ __global__ __launch_bounds__(256) void k_norm1(NormArgs g)
     norm_block_sum(rr, ff, g.partials, blockIdx.x);
 }
 
-// 2D: one wavefront takes kNormRows rows of 64 columns and marches down them.
+// 2D: one wavefront takes B rows of 64 columns and marches down them.
 // u, f and the coefficient are loaded once per point (the x neighbours are the
 // adjacent lanes', the y neighbours the rows before and after; lanes 0 and 63
 // also load the column beside the strip), and a face mean is computed once:
@@ -624,20 +624,31 @@ __global__ __launch_bounds__(256) void k_norm1(NormArgs g)
 // point: 1023^2 diffusion 11.2 -> 9.9 us, 48 systems of 13.7 M unknowns
 // 155 -> 88 us (all active).  A unit's loads are all in flight at once (four
 // rows a round before: 2047^2 diffusion 24.8 -> 21.8 us, 4095^2 47.3 -> 44.8,
-// 1023^2 diffusion 9.6 -> 9.4).
+// 1023^2 diffusion 9.6 -> 9.4; 8 rows a unit).
 // HASU false: the zero iterate (r = f), the same sums in the same order.
 constexpr int kNormRows = 8;
-template <bool VC, bool HASU>
+// Rows a unit of a single system's norm takes: fewer where 8 give less than two
+// wavefronts a SIMD (2048 units), which then wait on one unit's chain of loads and
+// divisions.  A residual call, 8 / 2 / 1 rows and a thread a point: 255^2
+// diffusion 21.8 / 19.9 / 19.6 / 19.4 us, 511^2 22.4 / 21.1 / 21.8 / 22.2, 1023^2
+// 25.8 / 27.9 / 29.1 / 29.3.
+static int norm2_rows(int n)
+{
+    const long long nsx = (n + 63) / 64;
+    for (int b : {kNormRows, 2})
+        if (nsx * ((n + b - 1) / b) >= 2048) return b;
+    return 1;
+}
+template <bool VC, bool HASU, int B>
 __device__ __forceinline__ void norm2_unit(const double *u, const double *f, const double *a, int n, long long pitch,
                                            double ih2, int ic, int j0, float *r32, double *r64, double &rr, double &ff)
 {
-    constexpr int B = kNormRows;
     const int lane = threadIdx.x & 63;
     const int i = ic + lane;                                   // this lane's column
     const bool cin = i <= n;
     const int ie = lane == 0 ? ic - 1 : ic + 64;               // the column beside the strip (lanes 0, 63)
     const bool ein = (lane == 0 || lane == 63) && ie >= 1 && ie <= n;
-    const int j1 = min(j0 + kNormRows, n + 1);
+    const int j1 = min(j0 + B, n + 1);
     auto row = [&](int j, double &c, double &e) {
         const bool ok = HASU && j >= 1 && j <= n;
         c = ok && cin ? gld(u + (long long)(j - 1) * pitch + (i - 1)) : 0.0;
@@ -702,15 +713,15 @@ __device__ __forceinline__ void norm2_unit(const double *u, const double *f, con
     }
 }
 
-template <bool VC, bool HASU>
+template <bool VC, bool HASU, int B>
 __global__ __launch_bounds__(256) void k_norm2(NormArgs g)
 {
     if (!g.first && g.state->done) return;
-    const int nsx = (g.n + 63) / 64, nunits = nsx * ((g.n + kNormRows - 1) / kNormRows);
+    const int nsx = (g.n + 63) / 64, nunits = nsx * ((g.n + B - 1) / B);
     double rr = 0.0, ff = 0.0;
     for (int t = blockIdx.x * 4 + (threadIdx.x >> 6); t < nunits; t += gridDim.x * 4)
-        norm2_unit<VC, HASU>(g.u, g.f, g.a, g.n, g.pitch, g.inv_h2, 1 + 64 * (t % nsx), 1 + kNormRows * (t / nsx), g.r32,
-                       g.r64, rr, ff);
+        norm2_unit<VC, HASU, B>(g.u, g.f, g.a, g.n, g.pitch, g.inv_h2, 1 + 64 * (t % nsx), 1 + B * (t / nsx), g.r32,
+                                g.r64, rr, ff);
     norm_block_sum(rr, ff, g.partials, blockIdx.x);
 }
 
@@ -724,7 +735,8 @@ void norm_batch_item(int n, int q, NormItem &it)
 }
 int norm2_blocks(int n)
 {
-    const long long units = (long long)((n + 63) / 64) * ((n + kNormRows - 1) / kNormRows);
+    const int b = norm2_rows(n);
+    const long long units = (long long)((n + 63) / 64) * ((n + b - 1) / b);
     return (int)std::min<long long>((units + 3) / 4, 2048);
 }
 
@@ -786,8 +798,8 @@ __global__ __launch_bounds__(256) void k_norm_batch(const NormItem *items, const
     const int ic = it.i0 + 64 * (int)(threadIdx.x >> 6);
     float *r32 = (flags & 2) ? S.r32 : nullptr;
     if (ic <= S.n) {
-        if (S.a) norm2_unit<true, true>(S.u, S.f, S.a, S.n, S.pitch, S.inv_h2, ic, it.j0, r32, nullptr, rr, ff);
-        else norm2_unit<false, true>(S.u, S.f, S.a, S.n, S.pitch, S.inv_h2, ic, it.j0, r32, nullptr, rr, ff);
+        if (S.a) norm2_unit<true, true, kNormRows>(S.u, S.f, S.a, S.n, S.pitch, S.inv_h2, ic, it.j0, r32, nullptr, rr, ff);
+        else norm2_unit<false, true, kNormRows>(S.u, S.f, S.a, S.n, S.pitch, S.inv_h2, ic, it.j0, r32, nullptr, rr, ff);
     }
     norm_block_sum(rr, ff, partials, it.slot);
 }
@@ -1165,16 +1177,25 @@ hipError_t launch_copy_state(int st, const GenArgs &g, const void *src, void *ds
     return hipGetLastError();
 }
 
+template <int B>
+static void launch_norm2(const NormArgs &a, int grid, hipStream_t s)
+{
+    if (!a.u) hipLaunchKernelGGL((k_norm2<false, false, B>), dim3(grid), dim3(256), 0, s, a);
+    else if (a.a) hipLaunchKernelGGL((k_norm2<true, true, B>), dim3(grid), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_norm2<false, true, B>), dim3(grid), dim3(256), 0, s, a);
+}
+
 hipError_t launch_norm(const NormArgs &a, hipStream_t s)
 {
     const int grid = a.nblocks;
-    const bool vc = a.a != nullptr;
     switch (a.dim) {
     case 1: hipLaunchKernelGGL(k_norm1, dim3(grid), dim3(256), 0, s, a); break;
     case 2:
-        if (!a.u) hipLaunchKernelGGL((k_norm2<false, false>), dim3(grid), dim3(256), 0, s, a);
-        else if (vc) hipLaunchKernelGGL((k_norm2<true, true>), dim3(grid), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((k_norm2<false, true>), dim3(grid), dim3(256), 0, s, a);
+        switch (norm2_rows(a.n)) {
+        case 1: launch_norm2<1>(a, grid, s); break;
+        case 2: launch_norm2<2>(a, grid, s); break;
+        default: launch_norm2<kNormRows>(a, grid, s);
+        }
         break;
     case 3:
         if (a.n <= 255) {
