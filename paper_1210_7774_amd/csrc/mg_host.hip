@@ -903,9 +903,9 @@ void await_published(const mg_handle_s *h)
 // launches go out behind the norm unseen, so that the GPU has work while the
 // host looks.  A solve whose guess already meets the tolerance (1023^2 FP64
 // diffusion, W cycles of 80 launches): 35 us, 421 with two cycles enqueued
-// unseen; 255^2 FP64 28, 65 unseen.  Solves with cycles take 0 to 4 us longer
-// than unseen with kAhead = 2, 6 to 14 with 0; four launches cost an ended
-// solve 5 to 7 us more.
+// unseen; 255^2 FP64 28, 65 unseen.  Solves with cycles take 0 to 15 us longer
+// than unseen with kAhead = 2 (the most where the launches bound them), 6 to 25
+// with 0; four launches cost an ended solve 5 to 7 us more.
 constexpr int kAhead = 2;
 bool ended_at_first_norm(mg_handle_s *h, int launches)
 {
@@ -1964,7 +1964,8 @@ mg_status solve_loop(mg_handle_s *h, double rtol, std::vector<mg_stats *> stats)
             }
         } watch{h};
         const bool direct = h->opt.fmg || zs_head;  // the first step is not the captured cycle
-        h->ahead = h->opt.use_graph && !h->prof && !direct ? 0 : kAhead;
+        // (from zero the first norm is 1 unless f is 0 or not finite: not waited for)
+        if (!zs || rtol >= 1.0) h->ahead = h->opt.use_graph && !h->prof && !direct ? 0 : kAhead;
         if (direct) {
             // the first step is one full-multigrid pass, or a cycle from zero
             h->first_zero = zs_head;
