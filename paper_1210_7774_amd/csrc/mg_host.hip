@@ -1436,13 +1436,13 @@ mg_status state_init(mg_handle_s *h, double tol, int maxc, hipStream_t st)
 
 // A solve's first residual norm, which also sets the states up (the learned
 // smoother's ratio watch and the bf16-state stall rule as in state_init) and
-// publishes them (the stream is idle or does not write them before it).
-mg_status enqueue_first_norm(mg_handle_s *h, double tol, int maxc, bool u_zero)
+// may publish them (nothing enqueued before does).
+mg_status enqueue_first_norm(mg_handle_s *h, double tol, int maxc, bool u_zero, bool publish)
 {
-    arm_published(h);
+    if (publish) arm_published(h);
     h->init = StateInit{1, maxc, tol, (h->learned && h->learned_on) ? kLearnedFallback : 0.0,
                         h->st == ST_BF16 && tol >= 0.0 ? bf16_stall_ratio() : 0.0};
-    h->publish = true;
+    h->publish = publish;
     const mg_status rc = enqueue_outer_norm(h, 1, h->ir, h->stream, u_zero);
     h->publish = false;
     h->init = StateInit{};
@@ -1947,9 +1947,11 @@ mg_status solve_loop(mg_handle_s *h, double rtol, std::vector<mg_stats *> stats)
     // The first norm sets the state up; an initial guess that already meets the
     // tolerance (or is not finite) needs no cycle, and the first ones are
     // enqueued with an eye on it (a captured cycle is one launch of all its
-    // kernels, so it waits for the norm).
+    // kernels, so it waits for the norm).  From zero the norm is 1 unless f is 0
+    // or not finite: it is not waited for.
+    const bool look = !zs || rtol >= 1.0;
     h->prof_step = -1;
-    rc = enqueue_first_norm(h, rtol, maxc, zs);
+    rc = enqueue_first_norm(h, rtol, maxc, zs, look);
     if (rc != MG_OK) return rc;
     h->prof_step = 0;
     int enq = 0;
@@ -1964,8 +1966,7 @@ mg_status solve_loop(mg_handle_s *h, double rtol, std::vector<mg_stats *> stats)
             }
         } watch{h};
         const bool direct = h->opt.fmg || zs_head;  // the first step is not the captured cycle
-        // (from zero the first norm is 1 unless f is 0 or not finite: not waited for)
-        if (!zs || rtol >= 1.0) h->ahead = h->opt.use_graph && !h->prof && !direct ? 0 : kAhead;
+        if (look) h->ahead = h->opt.use_graph && !h->prof && !direct ? 0 : kAhead;
         if (direct) {
             // the first step is one full-multigrid pass, or a cycle from zero
             h->first_zero = zs_head;
@@ -2022,7 +2023,7 @@ mg_status solve_loop(mg_handle_s *h, double rtol, std::vector<mg_stats *> stats)
                         if (S.pitch0 != S.n) return MG_ERR_NONFINITE;
                         HIPCHK(h, launch_fill_zero(S.u, (long long)sizeof(double) * level_points(S.n, h->dim), h->stream));
                     }
-                    rc = enqueue_first_norm(h, rtol, maxc, false);
+                    rc = enqueue_first_norm(h, rtol, maxc, false, true);
                     if (rc != MG_OK) return rc;
                     enq = 0;
                 } else {
