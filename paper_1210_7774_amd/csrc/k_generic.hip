@@ -245,10 +245,28 @@ __global__ __launch_bounds__(256) void k_resid_restrict2(GenArgs g)
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
         const int j = 2 * J0 + q;
-        const bool in = cin && j >= 1 && j <= n;
-        u[q] = in ? T::ld(ub + (long long)(j - 1) * L.pitch + (i - 1)) : (C)0;
-        f[q] = in && q > 0 && q < NR - 1 ? (C)gld(fb + (long long)(j - 1) * L.pitch + (i - 1)) : (C)0;
+        const bool in = cin && j >= 1 && j <= n, fin = q > 0 && q < NR - 1;
+        if constexpr (sizeof(C) == 8) {
+            u[q] = in ? T::ld(ub + (long long)(j - 1) * L.pitch + (i - 1)) : (C)0;
+            f[q] = in && fin ? (C)gld(fb + (long long)(j - 1) * L.pitch + (i - 1)) : (C)0;
+        } else {
+            // 4- and 2-byte loads at clamped places, selected below: under a
+            // condition they wait for one another (511^2 FP32 7.7 -> 6.7 us, bfloat16
+            // 9.9 -> 6.7; FP64 with coefficients 6.8 -> 7.2, so not there)
+            const long long o = (long long)(min(max(j, 1), n) - 1) * L.pitch + (min(max(i, 1), n) - 1);
+            u[q] = T::ld(ub + o);
+            f[q] = fin ? (C)gld(fb + o) : (C)0;
+        }
         if constexpr (VC) an[q] = gld(a + (long long)min(j, n + 1) * (n + 2) + min(i, n + 1));
+    }
+    if constexpr (sizeof(C) == 4) {
+#pragma unroll
+        for (int q = 0; q < NR; ++q) {
+            const int j = 2 * J0 + q;
+            const bool in = cin && j >= 1 && j <= n;
+            u[q] = in ? u[q] : (C)0;
+            f[q] = in ? f[q] : (C)0;
+        }
     }
     C ws = (C)0, acc = (C)0;
     if constexpr (VC) ws = harm(an[1], an[0]);
@@ -464,17 +482,26 @@ __global__ __launch_bounds__(256) void k_prolong_correct2(GenArgs g)
     S *u = (S *)L.B + (i - 1);
     const S *uc = (const S *)L.Bc;
     const int i0 = i / 2, i1 = i0 + (i & 1);
-    C line[5], v[8];
+    // (loads at clamped places, selected afterwards: a two-byte load under a
+    // condition fills half a register and waits for its other half; 255^2
+    // bfloat16 8.8 -> 6.5 us, a thread a point 6.4)
+    const int c0 = max(i0, 1) - 1, c1 = min(i1, nc) - 1;
+    C a[5][2], line[5], v[8];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        const S *row = uc + (long long)(min(max(j0 / 2 + q, 1), nc) - 1) * L.cpitch;
+        a[q][0] = T::ld(row + c0);
+        a[q][1] = T::ld(row + c1);
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = ADD ? T::ld(u + (long long)min(j0 + q, n - 1) * L.pitch) : (C)0;
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
         const int J = j0 / 2 + q;
         const bool in = J >= 1 && J <= nc;
-        const S *row = uc + (long long)(J - 1) * L.cpitch;
-        const C a0 = in && i0 >= 1 ? T::ld(row + (i0 - 1)) : (C)0, a1 = in && i1 <= nc ? T::ld(row + (i1 - 1)) : (C)0;
+        const C a0 = in && i0 >= 1 ? a[q][0] : (C)0, a1 = in && i1 <= nc ? a[q][1] : (C)0;
         line[q] = (i & 1) ? (a0 + a1) * (C)0.5 : a0;
     }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = ADD && j0 + q < n ? T::ld(u + (long long)(j0 + q) * L.pitch) : (C)0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         // row j0 + q + 1: odd rows lie between two coarse ones
