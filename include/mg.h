@@ -263,23 +263,24 @@ mg_status mg_jacobi5_static(const double *in, double *out, int rows, int cols, i
  * "Performance Study": block counts tuned per workload); here the library
  * measures launch shapes on the device.  For every 2D level size that runs
  * the fused PRE/POST kernels, mg_autotune times the PRE launch with block
- * heights 4 .. 256 and, on sizes that hold no system's finest level, LDS
- * tiles (a size that holds a finest level runs tiles when all its levels
- * together are at most 3072 tiles of 32 x 32 points -- a single system up to
- * 1023 points an edge -- and is then listed untimed), on the bound arrays
- * (u[s], f[s]: nsys device pointers, as for a
- * solve), `reps` (1 .. 50) timed launches per candidate, and keeps the
- * fastest; the choice lasts for the handle's life.  The finest level's
- * smoother runs in place, so u[s] comes back smoothed (a better iterate of
- * the same system), not unchanged.  3D handles: MG_OK, nothing tuned.
- * Synchronises; not inside a graph capture.
- * mg_tune_get lists the choices (level size n, block height hb, tiled
- * 0/1; count = how many there are, of which min(count, max) are written to
- * the caller's arrays); mg_tune_set applies one (e.g. read back from a
- * cache): MG_ERR_ARG for n < 1 or hb outside 2 .. 256; odd hb is rounded
- * down; a size that holds a finest level keeps the form the library gives it
- * (tiles up to the limit above, marching with this block height beyond),
- * and 3D handles keep the entry without using it. */
+ * heights 4 .. 256 and with LDS tiles on the bound arrays (u[s], f[s]: nsys
+ * device pointers, as for a solve), `reps` (1 .. 50) timed launches per
+ * candidate, and keeps the fastest; the choice lasts for the handle's life.
+ * A size that holds a system's finest level runs tiles by itself when all its
+ * levels together are at most 3072 tiles of 32 x 32 points (a single system
+ * up to 1023 points an edge), and only then has them as a candidate.  The
+ * finest level's smoother runs in place, so u[s] comes back smoothed (a better
+ * iterate of the same system), not unchanged.  3D handles: MG_OK, nothing
+ * tuned.  Synchronises; not inside a graph capture.
+ * mg_tune_get lists the choices (level size n, block height hb or the tiles'
+ * edge, and tiled: 1 tiles, 0 marching with that block height, -1 the form the
+ * library gives the size by itself, which the tuner found fastest on a size
+ * that holds a finest level; count = how many there are, of which min(count,
+ * max) are written to the caller's arrays); mg_tune_set applies one (e.g. read
+ * back from a cache): MG_ERR_ARG for n < 1 or hb outside 2 .. 256; odd hb is
+ * rounded down; tiles on a size that holds a finest level and is beyond the
+ * limit above march with this block height, and 3D handles keep the entry
+ * without using it. */
 mg_status mg_autotune(mg_handle h, double *const *u, const double *const *f, int reps);
 mg_status mg_tune_get(mg_handle h, int *n, int *hb, int *tiled, int max, int *count);
 mg_status mg_tune_set(mg_handle h, int n, int hb, int tiled);

@@ -191,7 +191,8 @@ class Solver:
     def autotune(self, u, f, reps=10, cache=None):
         """Time the fused 2D level kernels' launch shapes on (u, f) and keep
         the fastest; u is smoothed in place.  Returns {n: (block height,
-        tiled)}, which tune_set() accepts.  cache: a JSON file path; a stored
+        tiled)}, which tune_set() accepts; tiled is None where the library's
+        own form of a size that holds the finest level was fastest.  cache: a JSON file path; a stored
         entry for this device, precision, operator and size is applied
         without timing, a miss is tuned and stored."""
         _check_f64(u, self.shape, "u")
@@ -303,12 +304,12 @@ def _tune_get(obj):
     rc = L.mg_tune_get(obj.handle, n, hb, tl, m, ctypes.byref(cnt))
     if rc != _abi.MG_OK:
         raise MGError(rc, "mg_tune_get")
-    return {int(n[i]): (int(hb[i]), bool(tl[i])) for i in range(m)}
+    return {int(n[i]): (int(hb[i]), None if tl[i] < 0 else bool(tl[i])) for i in range(m)}
 
 
 def _tune_set(obj, choices):
     for n, (hb, tiled) in dict(choices).items():
-        rc = _abi.lib().mg_tune_set(obj.handle, int(n), int(hb), 1 if tiled else 0)
+        rc = _abi.lib().mg_tune_set(obj.handle, int(n), int(hb), -1 if tiled is None else int(bool(tiled)))
         if rc != _abi.MG_OK:
             raise MGError(rc, "mg_tune_set")
 

@@ -2,8 +2,8 @@
 
 The file maps a key (device, solver form -- precision, smoother, sweeps --,
 operator and the systems' sizes) to
-the choices mg_tune_get reports: {level size: [block height, tiled]}.  A
-missing, unreadable or malformed file or entry is a miss: the caller tunes
+the choices mg_tune_get reports: {level size: [block height, tiled]}, tiled
+null where the library's own form is kept.  A missing, unreadable or malformed file or entry is a miss: the caller tunes
 again and the entry is rewritten.  Writes go to a temporary file that then
 replaces the cache, so a reader never sees half a file.
 """
@@ -13,7 +13,7 @@ import json
 import os
 import tempfile
 
-VERSION = 1
+VERSION = 2  # (1 had no null: its false stood for the library's form too)
 
 
 def key(device: str, form: str, operator: str, sizes) -> str:
@@ -39,7 +39,7 @@ def load(path: str, k: str):
         for n, v in ent.items():
             hb, tiled = v
             n, hb = int(n), int(hb)
-            if n < 1 or not 2 <= hb <= 256 or not isinstance(tiled, bool):
+            if n < 1 or not 2 <= hb <= 256 or not (tiled is None or isinstance(tiled, bool)):
                 return None
             out[n] = (hb, tiled)
     except (TypeError, ValueError):
@@ -49,7 +49,7 @@ def load(path: str, k: str):
 
 def store(path: str, k: str, choices) -> None:
     data = _read(path)
-    data[k] = {str(int(n)): [int(hb), bool(t)] for n, (hb, t) in sorted(choices.items())}
+    data[k] = {str(int(n)): [int(hb), None if t is None else bool(t)] for n, (hb, t) in sorted(choices.items())}
     d = os.path.dirname(os.path.abspath(path))
     fd, tmp = tempfile.mkstemp(prefix=".tune", dir=d)
     try:
