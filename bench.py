@@ -354,6 +354,20 @@ def mixed_forms(args, n, f, f_np, u64, ms64):
     return forms, speed
 
 
+def active_share(name, ns, cycles):
+    """The share of a batched launch's bytes that is moved: systems that have
+    converged move nothing.  A launch of level size n holds that level of every
+    system of n points an edge or more, the tail one level of each system, the
+    norm every finest level (and once before the first cycle)."""
+    if "n=" in name:
+        n = int(name.split("n=")[1])
+        took = [c for c, m in zip(cycles, ns) if m >= n]
+        return sum(took) / (len(took) * max(cycles))
+    if name == "norm":
+        return sum((c + 1) * m * m for c, m in zip(cycles, ns)) / ((max(cycles) + 1) * sum(m * m for m in ns))
+    return sum(cycles) / (len(cycles) * max(cycles))
+
+
 def run_batch(args):
     import torch
 
@@ -400,11 +414,7 @@ def run_batch(args):
             raise SystemExit("batch verification failed: oracle residual %.3e" % worst)
         out["oracle_worst_rel_res"] = worst
     rows = kernel_table(timings) if timings else []
-    # systems that have converged move nothing: a launch's bytes are those of
-    # the systems of its size, times the share of the cycles they take part in
-    share = {n: sum(c for c, m in zip(system_cycles, ns) if m == n) / (ns.count(n) * max(system_cycles)) for n in set(ns)}
-    rows = [(name, (cnt, avg, b * share.get(int(name.split("n=")[1]), 1.0) if "n=" in name else b))
-            for name, (cnt, avg, b) in rows]
+    rows = [(name, (cnt, avg, b * active_share(name, ns, system_cycles))) for name, (cnt, avg, b) in rows]
     out["roofline"] = roofline_of(rows) if rows else None
     out["cpu_baseline"] = None
     out["autotune"] = tune
