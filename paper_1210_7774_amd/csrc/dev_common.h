@@ -7,6 +7,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "mg.h"
 #include "mg_internal.h"
 
 namespace mgx {
@@ -192,21 +193,36 @@ __device__ __forceinline__ double lane_value(double x, int lane)
     return *reinterpret_cast<double *>(&r);
 }
 
+// LDS written by one lane, read by another of the same wavefront
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ double wave_sum(double v)
 {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
 
+// ---- cycle types in the register tails: how often one visit of a level visits
+// the next coarser one, and the v-th visit's type (an F visit: an F and then a V
+// visit, the second from the first's result)
+__device__ __forceinline__ int visits_below(int kind) { return kind == MG_CYCLE_V ? 1 : 2; }
+__device__ __forceinline__ int visit_kind(int v, int kind) { return v > 0 && kind == MG_CYCLE_F ? MG_CYCLE_V : kind; }
+
 // ---- deterministic norm reduction + stop test ------------------------------
 // Work items write their partial sums (rr = sum r^2, ff = sum f^2) to
 // partials[2 slot + {0, 1}] with plain stores; the next kernel on the stream
-// (k_norm_finish, one wavefront per system) reduces a system's slots in a
-// fixed order -- lane l adds slots l, l+64, ..., then a fixed butterfly
-// across the lanes -- so the total does not depend on scheduling, and applies
-// the stop test:
-//   rel = sqrt(rr / ff); hist[nres] = rel; done = 1 if rel <= tol,
-//   2 if not finite, 3 if nres reached the cycle limit.
+// (k_norm_finish, 256 threads per system) reduces a system's slots in a fixed
+// order -- thread t adds slots t, t + 256, ..., then a fixed butterfly across
+// the lanes of each wavefront, then the four wavefronts' sums in order -- so
+// the total does not depend on scheduling, and applies the stop test:
+//   rel = sqrt(rr / ff); hist[nres] = rel; done = 1 if rel <= tol, 2 if not
+//   finite, 3 if nres reached the cycle limit, 4 to 6 by the rules on the
+//   history (SolveState::done).
 // `first` marks the norm before the first cycle: it also fixes ff = ||f||^2.
 __device__ inline void put_partial(double *partials, int slot, double rr, double ff)
 {

@@ -21,7 +21,6 @@
 // and a stop-test kernel per cycle), so a solve is one launch: 1023 points FP64
 // 71 -> 23 us (11.2 us of it the kernel), 2047 75 -> 26, 31 55 -> 17.
 #include "dev_common.h"
-#include "mg.h"
 
 namespace mgx {
 
@@ -143,14 +142,13 @@ struct Tail1 {
         }
     }
 
-    // The visits of a level by one visit of its parent: one (V), two W visits,
-    // or an F and then a V visit, the second from the first's result.
+    // The visits of a level by one visit of its parent.
     template <int K, bool MULTI>
     __device__ __forceinline__ void below(C (&u)[per(K)], const C (&f)[per(K)], int kind)
     {
         if constexpr (MULTI && K > 1) {
-            const int visits = kind == MG_CYCLE_V ? 1 : 2;
-            for (int v = 0; v < visits; ++v) visit<K, true>(u, f, v > 0 && kind == MG_CYCLE_F ? MG_CYCLE_V : kind);
+            const int visits = visits_below(kind);
+            for (int v = 0; v < visits; ++v) visit<K, true>(u, f, visit_kind(v, kind));
         } else {
             visit<K, MULTI>(u, f, kind);
         }

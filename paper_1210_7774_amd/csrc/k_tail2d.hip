@@ -27,7 +27,6 @@
 // 255^2 FP64 W 2455 -> 945 us, F 811 -> 512, of 63^2 FP32 diffusion F 732 -> 298
 // (FP64 from 63 spills 54 registers there and is still the faster form).
 #include "dev_common.h"
-#include "mg.h"
 
 namespace mgx {
 
@@ -51,13 +50,6 @@ template <class C>
 __device__ __forceinline__ C t2harm(C a, C b)
 {
     return (C)2 * a * b / (a + b);
-}
-
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // LDS of one level: the four points' arrays by block with a zero row above and
@@ -197,10 +189,6 @@ struct Tail2 {
     // state: a V-cycle visit from zero, the visits of a W or F cycle (MULTI: two
     // W visits, or an F and then a V visit, the second from the first's
     // result), or full multigrid.
-    static __device__ __forceinline__ int next_kind(int v, int kind)
-    {
-        return v > 0 && kind == MG_CYCLE_F ? MG_CYCLE_V : kind;
-    }
     template <int K, bool FMG>
     __device__ __forceinline__ void below(TLds<C, K> &lds, int kind)
     {
@@ -224,9 +212,9 @@ struct Tail2 {
         if constexpr (FMG) {
             fmg<K - 1>(lds.below, cu, cf, kind);
         } else if constexpr (MULTI) {
-            const int visits = kind == MG_CYCLE_V ? 1 : 2;
+            const int visits = visits_below(kind);
             for (int v = 0; v < visits; ++v)
-                visit<K - 1>(lds.below, cu, cf, v == visits - 1, next_kind(v, kind));
+                visit<K - 1>(lds.below, cu, cf, v == visits - 1, visit_kind(v, kind));
         } else {
             visit<K - 1>(lds.below, cu, cf, true, kind);
         }
@@ -431,7 +419,7 @@ __global__ __launch_bounds__(K == 6 ? 1024 : K == 5 ? 256 : 64) void k_tail2d(Ta
         t.template fmg<K>(lds, u, f, args.cycle);
     } else if constexpr (MULTI) {
         for (int v = 0; v < args.visits; ++v)
-            t.template visit<K>(lds, u, f, v == args.visits - 1, t.next_kind(v, args.cycle));
+            t.template visit<K>(lds, u, f, v == args.visits - 1, visit_kind(v, args.cycle));
     } else {
         t.template visit<K>(lds, u, f, true, MG_CYCLE_V);
     }

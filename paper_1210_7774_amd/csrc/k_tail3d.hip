@@ -17,24 +17,10 @@
 // 14.1 us.  W and F cycles repeat the visits of the levels below (solves of 7
 // cycles: 63^3 FP32 W 1897 -> 810 us, FP64 F 1262 -> 813, 127^3 FP32 F 1879 -> 1477).
 #include "dev_common.h"
-#include "mg.h"
 
 namespace mgx {
 
 namespace {
-
-// the cycle type of a level's v-th visit in one visit of its parent
-__device__ __forceinline__ int t3_next_kind(int v, int kind)
-{
-    return v > 0 && kind == MG_CYCLE_F ? MG_CYCLE_V : kind;
-}
-
-__device__ __forceinline__ void t3_wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 template <class C, int K>
 struct T3Level {
@@ -69,7 +55,7 @@ struct Tail3 {
     static __device__ __forceinline__ void sync()
     {
         if constexpr (K >= 4) __syncthreads();
-        else t3_wave_sync();
+        else wave_sync();
     }
 
     // the neighbour of point d outside its block along each axis
@@ -190,11 +176,11 @@ struct Tail3 {
                 cu[d] = (C)0;
                 B.v[d][(cz + 1) * B.ZS + (cy + 1) * B.YS + cx] = (C)0;
             }
-            t3_wave_sync();
+            wave_sync();
             if constexpr (MULTI) {
-                const int visits = kind == MG_CYCLE_V ? 1 : 2;
+                const int visits = visits_below(kind);
                 for (int v = 0; v < visits; ++v)
-                    visit<K - 1, true>(lds.below, cu, cf, v == visits - 1, t3_next_kind(v, kind));
+                    visit<K - 1, true>(lds.below, cu, cf, v == visits - 1, visit_kind(v, kind));
             } else {
                 visit<K - 1, false>(lds.below, cu, cf, true, kind);
             }
@@ -290,7 +276,7 @@ __global__ __launch_bounds__(K == 4 ? 512 : 64) void k_tail3d(TailArgs args, Lev
     Tail3<S> t{tid, args.nu1, args.nu2, cinv};
     if constexpr (MULTI) {
         for (int v = 0; v < args.visits; ++v)
-            t.template visit<K, true>(lds, u, f, v == args.visits - 1, t3_next_kind(v, args.cycle));
+            t.template visit<K, true>(lds, u, f, v == args.visits - 1, visit_kind(v, args.cycle));
     } else {
         t.template visit<K, false>(lds, u, f, true, MG_CYCLE_V);
     }
