@@ -220,9 +220,10 @@ __global__ __launch_bounds__((W3Geo<NS, TAIL, T>::NT)) void k_march3dw(M3Args a)
     // p / 2 (p even) or (Pa + Pb) / 2 with Pb that of p / 2 + 1 (p odd) -- the
     // order of the unfused prolongation kernel (x, y, then z); it is computed
     // when the plane enters the registers.  Coarse plane K + 2 is loaded when
-    // fine plane 2K enters and staged when 2K + 1 does, two steps (four
-    // barriers) before fine plane 2K + 3 first reads it and after the last
-    // reader of the slot's previous plane.
+    // fine plane 2K enters and staged when 2K + 1 does: the last reader
+    // of the slot's previous plane (fine plane 2K - 1) entered two steps before,
+    // and fine plane 2K + 3, which first reads it, enters two steps later, with
+    // one barrier a step between them.
     const int ci0 = (i0 - R) >> 1, cj0 = (j0 - R) >> 1;  // floor
     C pk[QC];
     uint32_t co[QC];

@@ -245,7 +245,7 @@ struct TailArgs {
     int faces;                // 2D diffusion: face weights precomputed in LDS (the LDS holds them)
     const int *ops;           // device: a schedule of level operations (W / F cycles, full
     int nops;                 //   multigrid), or null for the V-cycle
-    int cycle, visits;        // k_tail2d: cycle type of the top level's visits (the first of them), and how many
+    int cycle, visits;        // register tails: cycle type of the top level's visits (the first of them), and how many
 };
 // Operations of a tail schedule: op = kind | level << 4 | sweeps << 12 (level
 // relative to the tail's top level)
@@ -257,15 +257,17 @@ enum TailOp {
     TAIL_OP_RESTRICT_RHS = 5,  // f_{l+1} = R f_l, u_{l+1} = 0 (full multigrid)
     TAIL_OP_INTERP = 6,        // u_l = P u_{l+1} (full multigrid)
 };
-// The 2D red-black V-cycle tail (k_tail2d.hip) for the given top level and m
-// coarsest unknowns; L: the top level's descriptor (used when a.nsys == 1).
+// The 2D red-black tail (k_tail2d.hip: V, W and F cycles, FP64 full multigrid)
+// for the given top level and m coarsest unknowns; L: the top level's descriptor
+// (used when a.nsys == 1).
 bool tail2d_supported(int st, bool vc, int n_top, int m);
 hipError_t launch_tail2d(int st, bool vc, bool fmg, const TailArgs &a, const LevelDesc &L, hipStream_t s);
-// The 3D one (k_tail3d.hip).
+// The 3D one (k_tail3d.hip: V, W and F cycles).
 bool tail3d_supported(int n_top, int m);
 hipError_t launch_tail3d(int st, const TailArgs &a, const LevelDesc &L, hipStream_t s);
-// The 1D ones (k_tail1d.hip): one V-cycle of a hierarchy that is all tail, and
-// `cycles` cycles of an FP64 solve with their norms and stop tests.
+// The 1D ones (k_tail1d.hip): one V, W or F cycle or full-multigrid pass (FP64)
+// of a hierarchy that is all tail, and `cycles` V-cycles of an FP64 solve with
+// their norms and stop tests.
 bool tail1d_supported(int n, int m);
 bool solve1d_supported(int n, int m);
 hipError_t launch_tail1d(int st, bool fmg, const TailArgs &a, const LevelDesc &L, hipStream_t s);
