@@ -767,14 +767,17 @@ int norm2_blocks(int n)
     return (int)std::min<long long>((units + 3) / 4, 2048);
 }
 
-// ---- 3D FP64 residual norm: each thread marches one column up a run of 32
+// ---- 3D FP64 residual norm: each thread marches one column up a run of RUN
 // planes keeping u(k - 1), u(k), u(k + 1) in registers, so every array is
 // streamed once (the in-plane neighbours come from the cache); work units of
-// 64 x 4 columns x RUN planes are dealt to the blocks in a fixed order.  32
-// planes a unit, 8 up to 255 points an edge, where longer runs leave the chip
-// waiting on a few columns (127^3 with the FP32 rhs written: 22.8 -> 13.4 us)
+// 64 x 4 columns x RUN planes are dealt to the blocks in a fixed order.  8
+// planes a unit up to 127 points an edge, where longer runs leave the chip
+// waiting on a few columns (127^3 with the FP32 rhs written: 22.8 -> 13.4 us), 32
+// above.  Those run with four wavefronts a SIMD: more of them push the rows that
+// a neighbouring unit reads next out of the caches (511^3: 635 us with eight, 600
+// with six, 569 with four; 255^3 72 / 69 / 66.5, and 74.5 in runs of 8).
 template <int RUN, bool HASU>
-__global__ __launch_bounds__(256) void k_norm3(NormArgs g)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, RUN == 32 ? 4 : 8))) void k_norm3(NormArgs g)
 {
     if (!g.first && g.state->done) return;
     Idx<3> x{g.n, g.pitch, g.ppitch};
@@ -1225,7 +1228,7 @@ hipError_t launch_norm(const NormArgs &a, hipStream_t s)
         }
         break;
     case 3:
-        if (a.n <= 255) {
+        if (a.n <= 127) {
             if (a.u) hipLaunchKernelGGL((k_norm3<8, true>), dim3(grid), dim3(256), 0, s, a);
             else hipLaunchKernelGGL((k_norm3<8, false>), dim3(grid), dim3(256), 0, s, a);
         } else {
