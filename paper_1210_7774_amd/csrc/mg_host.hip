@@ -902,11 +902,11 @@ void await_published(const mg_handle_s *h)
 // level operation (of that many launches), which is then left out.  kAhead
 // launches go out behind the norm unseen, so that the GPU has work while the
 // host looks.  A solve whose guess already meets the tolerance (1023^2 FP64
-// diffusion, W cycles of 80 launches): 35 us, 421 with two cycles enqueued
-// unseen; 255^2 FP64 28, 65 unseen.  Solves with cycles take 0 to 15 us longer
-// than unseen with kAhead = 2 (the most where the launches bound them), 6 to 25
-// with 0; four launches cost an ended solve 5 to 7 us more.
-constexpr int kAhead = 2;
+// diffusion, W cycles of 80 launches): 32 us, 421 with two cycles enqueued
+// unseen; 255^2 FP64 26, 65 unseen.  Solves with cycles take 0 to 3 us longer
+// than unseen (more only by what processes differ); with kAhead = 2 an ended
+// solve takes 2 to 3 us more, with 4 7 to 10.
+constexpr int kAhead = 1;
 bool ended_at_first_norm(mg_handle_s *h, int launches)
 {
     if (h->ahead < 0) return h->ended;
@@ -995,6 +995,9 @@ bool use_m3w(const mg_handle_s *h, int n)
     return ((h->opt.nu1 + 1) / 2 - (h->opt.nu2 + 1) / 2) % 2 == 0;
 }
 
+// launches of a level's PRE (nu1) or POST (nu2)
+int m3_passes(const mg_handle_s *h, int n, int nu) { return use_m3w(h, n) ? (nu + 1) / 2 : nu; }
+
 mg_status enqueue_m3(mg_handle_s *h, int s, int l, bool post, hipStream_t st, bool keep = false)
 {
     Sys &S = h->sys[s];
@@ -1023,7 +1026,7 @@ mg_status enqueue_m3(mg_handle_s *h, int s, int l, bool post, hipStream_t st, bo
     const int nu = post ? h->opt.nu2 : h->opt.nu1;
     // passes and their sweeps: one sweep each, or two (wavefront passes)
     const bool wf = use_m3w(h, L.n);
-    const int npass = wf ? (nu + 1) / 2 : nu;
+    const int npass = m3_passes(h, L.n, nu);
     const int npre = wf ? (h->opt.nu1 + 1) / 2 : h->opt.nu1;
     // PRE starts in B; POST starts where PRE ended (A after an odd count)
     bool inA = post ? (npre % 2 == 1) : false;
@@ -1101,7 +1104,8 @@ mg_status enqueue_m3(mg_handle_s *h, int s, int l, bool post, hipStream_t st, bo
 
 mg_status enqueue_generic_down(mg_handle_s *h, int s, int l, hipStream_t st, bool keep = false)
 {
-    if (ended_at_first_norm(h, h->m3 ? 1 : kAhead + 1)) return MG_OK;  // (a generic level: several launches)
+    // (a generic level: several launches)
+    if (ended_at_first_norm(h, h->m3 ? m3_passes(h, h->sys[s].lv[l].n, h->opt.nu1) : kAhead + 1)) return MG_OK;
     if (h->m3) return enqueue_m3(h, s, l, false, st, keep);
     Sys &S = h->sys[s];
     GenArgs g = gen_args(h, s, l);
@@ -1125,7 +1129,7 @@ mg_status enqueue_generic_down(mg_handle_s *h, int s, int l, hipStream_t st, boo
 
 mg_status enqueue_generic_up(mg_handle_s *h, int s, int l, hipStream_t st)
 {
-    if (ended_at_first_norm(h, h->m3 ? 1 : kAhead + 1)) return MG_OK;
+    if (ended_at_first_norm(h, h->m3 ? m3_passes(h, h->sys[s].lv[l].n, h->opt.nu2) : kAhead + 1)) return MG_OK;
     if (h->m3) return enqueue_m3(h, s, l, true, st);
     Sys &S = h->sys[s];
     GenArgs g = gen_args(h, s, l);
