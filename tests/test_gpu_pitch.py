@@ -91,3 +91,83 @@ def test_padded_zero_start(dim, n, row, plane, fmg):
             assert float(uv.abs().max()) == 0.0
         uv.fill_(FILL)
         assert bool((ut == FILL).all())
+
+
+def handle(n, row, opts):
+    L = _abi.lib()
+    g, o, op = _abi.Grid(), _abi.Options(), _abi.Operator(_abi.MG_OP_POISSON, None)
+    L.mg_options_default(ctypes.byref(o))
+    g.dim, g.n[0], g.n[1], g.n[2], g.pitch[1] = 2, n, n, 1, row
+    for k, v in opts.items():
+        setattr(o, k, v)
+    nbytes, h = ctypes.c_size_t(0), ctypes.c_void_p(0)
+    assert L.mg_workspace_size(ctypes.byref(g), ctypes.byref(op), ctypes.byref(o), ctypes.byref(nbytes)) == 0
+    ws = torch.empty(nbytes.value, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    assert L.mg_setup(ctypes.byref(g), ctypes.byref(op), ctypes.byref(o), ctypes.c_void_p(ws.data_ptr()), nbytes,
+                      ctypes.byref(h)) == 0
+    return h, ws
+
+
+@pytest.mark.parametrize("n,row,opts", [(255, 260, {}), (2047, 2049, {}), (127, 130, JAC)])
+def test_padded_level_operations(n, row, opts):
+    print("padded level operations", n, row, opts, flush=True)
+    L, nc = _abi.lib(), (n - 1) // 2
+    u, f, uc = (torch.from_numpy(np.ascontiguousarray(I.normal_rhs(m, 2, 60 + m % 7))).to("cuda") for m in (n, n, nc))
+    f = f.flip(0).contiguous()
+    outs = []
+    for p in (n, row):
+        h, ws = handle(n, p, opts)
+        (ut, uv), (ft, fv), (ot, ov), (qt, qv) = (padded(n, 2, p, 0) for _ in range(4))
+        uv.copy_(u)
+        fv.copy_(f)
+        fc, r, s = torch.empty_like(uc), torch.empty_like(u), torch.empty_like(u)
+        ptr = [ctypes.c_void_p(t.data_ptr()) for t in (ut, ft, ot, fc, uc, qt, r, s)]
+        assert L.mg_smooth_restrict(h, ptr[0], ptr[1], ptr[2], ptr[3]) == 0
+        assert L.mg_correct_smooth(h, ptr[0], ptr[4], ptr[1], ptr[5]) == 0
+        assert L.mg_residual(h, ptr[0], ptr[1], ptr[6]) == 0
+        assert L.mg_scaled_residual(h, ptr[0], ptr[1], ptr[7]) == 0
+        L.mg_destroy(h)
+        outs.append([t.clone() for t in (ov, fc, qv, r, s)])
+        for t, v in ((ot, ov), (qt, qv)):
+            v.fill_(FILL)
+            assert bool((t == FILL).all())
+    for x, y in zip(*outs):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("prec", [_abi.MG_P_F64, _abi.MG_P_F32_IR])
+def test_padded_batch(prec):
+    print("padded batch", prec, flush=True)
+    L, ns, rows = _abi.lib(), [127, 255, 511], [130, 255, 600]
+    fs = [torch.from_numpy(np.ascontiguousarray(I.normal_rhs(n, 2, 66 + n))).to("cuda") for n in ns]
+    outs = []
+    for pitches in (ns, rows):
+        g, ops, o = (_abi.Grid * 3)(), (_abi.Operator * 3)(), _abi.Options()
+        L.mg_options_default(ctypes.byref(o))
+        o.precision = prec
+        us, ft = [], []
+        for k, (n, p) in enumerate(zip(ns, pitches)):
+            g[k].dim, g[k].n[0], g[k].n[1], g[k].n[2], g[k].pitch[1] = 2, n, n, 1, p
+            ops[k] = _abi.Operator(_abi.MG_OP_POISSON, None)
+            us.append(padded(n, 2, p, 0))
+            us[-1][1].zero_()
+            ft.append(padded(n, 2, p, 0))
+            ft[-1][1].copy_(fs[k])
+        nbytes, h = ctypes.c_size_t(0), ctypes.c_void_p(0)
+        assert L.mg_workspace_size_batch(3, g, ops, ctypes.byref(o), ctypes.byref(nbytes)) == 0
+        ws = torch.empty(nbytes.value, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        assert L.mg_setup_batch(3, g, ops, ctypes.byref(o), ctypes.c_void_p(ws.data_ptr()), nbytes, ctypes.byref(h)) == 0
+        st = (_abi.Stats * 3)()
+        up = (ctypes.c_void_p * 3)(*[t.data_ptr() for t, _ in us])
+        fp = (ctypes.c_void_p * 3)(*[t.data_ptr() for t, _ in ft])
+        assert L.mg_solve_batch(h, up, fp, 1e-8, st) == 0
+        L.mg_destroy(h)
+        outs.append(([s.cycles for s in st], [v.clone() for _, v in us]))
+        for t, v in us:
+            v.fill_(FILL)
+            assert bool((t == FILL).all())
+    assert outs[0][0] == outs[1][0]
+    for x, y in zip(outs[0][1], outs[1][1]):
+        assert torch.equal(x, y)
