@@ -775,9 +775,10 @@ int norm2_blocks(int n)
 // waiting on a few columns (127^3 with the FP32 rhs written: 22.8 -> 13.4 us), 32
 // above.  Those run with four wavefronts a SIMD: more of them push the rows that
 // a neighbouring unit reads next out of the caches (511^3: 635 us with eight, 600
-// with six, 569 with four; 255^3 72 / 69 / 66.5, and 74.5 in runs of 8).
+// with six, 569 with four; 255^3 72 / 69 / 66.5, and 74.5 in runs of 8).  The zero
+// iterate reads f alone and keeps eight (511^3 212 us, 315 with four).
 template <int RUN, bool HASU>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, RUN == 32 ? 4 : 8))) void k_norm3(NormArgs g)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, RUN == 32 && HASU ? 4 : 8))) void k_norm3(NormArgs g)
 {
     if (!g.first && g.state->done) return;
     Idx<3> x{g.n, g.pitch, g.ppitch};
