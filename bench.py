@@ -29,7 +29,6 @@ Prints ONE JSON line (rank 0 only; the solver runs on one GPU).
 from __future__ import annotations
 
 import argparse
-import hashlib
 import json
 import os
 import platform
@@ -66,17 +65,14 @@ def cpu_model():
     return platform.processor() or "unknown"
 
 
-def measured_traffic(kernel, record="traffic.json",
-                     sources=("k_march2d.inc", "k_march2d_f64.hip", "dev_common.h", "mg_internal.h")):
+def measured_traffic(kernel, record="traffic.json"):
     """HBM bytes per launch of `kernel` from a committed rocprofv3 counter
-    summary, or None when the kernel sources changed since it was taken."""
+    summary, or None when the kernels' code changed since it was taken."""
+    from paper_1210_7774_amd import profile_summary as P
     try:
-        rec = json.load(open(os.path.join(ROOT, "profiles", record)))
-        csrc = os.path.join(ROOT, "paper_1210_7774_amd", "csrc")
-        h = hashlib.sha256()
-        for fn in sources:
-            h.update(open(os.path.join(csrc, fn), "rb").read())
-        if h.hexdigest()[:16] != rec["source_hash"] or kernel not in rec["kernels"]:
+        with open(os.path.join(ROOT, "profiles", record)) as fh:
+            rec = json.load(fh)
+        if P.code_hash(P.RECORDS[record]) != rec["source_hash"] or kernel not in rec["kernels"]:
             return None
         k = rec["kernels"][kernel]
         return k["read_bytes"] + k["write_bytes"]
@@ -160,18 +156,14 @@ LEARNED_FLOP_PER_PX = 2 * 9 * (16 + 16 * 16 + 16 * 16 + 16)  # 9792: the network
 MFMA_BF16_PEAK_TFLOPS = 2500.0
 
 
-# committed counter records (profiles/) per kernel family, with the sources
-# whose hash they were taken on
-TRAFFIC_2D = ("traffic.json", ("k_march2d.inc", "k_march2d_f64.hip", "dev_common.h", "mg_internal.h"))
-TRAFFIC_3D = ("traffic_c3.json", ("k_march3d.hip", "k_march3dw.hip", "mg_m3.h", "dev_common.h", "mg_internal.h"))
 M3_CLASSES = ("pre_rr", "pre_sweep", "post_corr", "post_norm", "post_sweep", "post_acc", "pre_zero_rr",
               "pre_zero_sweep")
 
 
 def traffic_of(name):
     cls = name.split(" ")[0]
-    rec = TRAFFIC_3D if cls in M3_CLASSES or (cls[:1] == "w" and cls[2:] in M3_CLASSES) else TRAFFIC_2D
-    return measured_traffic(name, rec[0], rec[1])
+    m3 = cls in M3_CLASSES or (cls[:1] == "w" and cls[2:] in M3_CLASSES)
+    return measured_traffic(name, "traffic_c3.json" if m3 else "traffic.json")
 
 
 def roofline_of(rows, learned_px_per_launch=0):
@@ -463,8 +455,7 @@ def run_jacobi(args):
     b = 16.0 * n * n  # read the array once, write it once
     achieved = b / (avg * 1e-3) / 1e9
     res["roofline"] = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                       "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic("jacobi5 n=%d" % n, "traffic_jacobi5.json",
-                                                                  ("k_jacobi5.hip", "dev_common.h")),
+                       "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic("jacobi5 n=%d" % n, "traffic_jacobi5.json"),
                        "kernel": "k_jacobi5", "bytes_per_launch": b, "avg_ms": round(avg, 5), "launches": K}
     res["cpu_baseline"] = None
     want = None

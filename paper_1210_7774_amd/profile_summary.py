@@ -4,13 +4,13 @@ the same counters on a plain device copy of known size).
 
     python -m paper_1210_7774_amd.profile_summary trace <run_kernel_stats.csv>
     python -m paper_1210_7774_amd.profile_summary traffic <fetch dir> <write dir> <cal fetch dir> <cal write dir>
-        <out.json> <n> <kernel sources...>
+        profiles/<record> <n>
 
 The traffic record keeps, per timing class of the library ("pre_rr n=511",
 "post n=4095", ...), the calibrated read and write bytes of one launch at the
 finest level (the dispatches of each kernel that move the most data), and
-the hash of the kernel sources they were taken on; bench.py reports them only
-while the sources are unchanged.
+the hash of the code (without comments) they were taken on; bench.py reports
+them only while that is unchanged.
 """
 from __future__ import annotations
 
@@ -28,13 +28,31 @@ M3_CLASS = {("0", "0"): "pre_sweep", ("1", "0"): "pre_sweep", ("0", "1"): "pre_r
             ("2", "0"): "post_corr", ("2", "2"): "post_norm", ("0", "2"): "post_norm"}
 
 
+# the committed records and the kernel sources that each was taken on
+RECORDS = {
+    "traffic.json": ("k_march2d.inc", "k_march2d_f64.hip", "dev_common.h", "mg_internal.h"),
+    "traffic_c3.json": ("k_march3d.hip", "k_march3dw.hip", "mg_m3.h", "dev_common.h", "mg_internal.h"),
+    "traffic_jacobi5.json": ("k_jacobi5.hip", "dev_common.h"),
+}
+
+
+def code_hash(sources):
+    """Hash of the sources' code: comments and white space left out."""
+    h = hashlib.sha256()
+    for fn in sources:
+        with open(os.path.join(CSRC, fn)) as fh:
+            text = re.sub(r"//[^\n]*|/\*.*?\*/", "", fh.read(), flags=re.S)
+        h.update("".join(text.split()).encode())
+    return h.hexdigest()[:16]
+
+
 def short(name):
     m = re.search(r"k_march3d<(\w+), (\w+), (\d), (\d),", name)
     if m:
         return "k_march3d<%s,%s,head %s,tail %s>" % m.groups()
-    m = re.search(r"k_march3dw<(\w+), (\w+), (\d), (\d), (\d)>", name)
+    m = re.search(r"k_march3dw<(\w+), (\w+), (\d), (\d), (\d), (\d+), \w+>", name)
     if m:
-        return "k_march3dw<%s,%s,%s sweeps,head %s,tail %s>" % m.groups()
+        return "k_march3dw<%s,%s,%s sweeps,head %s,tail %s,edge %s>" % m.groups()
     return re.sub(r"\(.*", "", name)[:90]
 
 
@@ -72,7 +90,7 @@ def copy_kib(d, counter):
     return max(finest(x) for k, x in per_kernel(d, counter).items() if "elementwise" in k or "copy" in k.lower())
 
 
-def traffic(fdir, wdir, cfdir, cwdir, out, n, sources):
+def traffic(fdir, wdir, cfdir, cwdir, out, n):
     # 256 MiB copy: read and written once
     fs = 262144.0 / copy_kib(cfdir, "FETCH_SIZE")
     ws = 262144.0 / copy_kib(cwdir, "WRITE_SIZE")
@@ -80,7 +98,8 @@ def traffic(fdir, wdir, cfdir, cwdir, out, n, sources):
     kernels = {}
     for name in sorted(fk):
         m = re.search(r"k_march3d<\w+, \w+, (\d), (\d),", name)
-        mw = re.search(r"k_march3dw<\w+, \w+, (\d), (\d), (\d)>", name)
+        mw = re.search(r"k_march3dw<\w+, \w+, (\d), (\d), (\d), \d+, \w+>", name)
+        mj = "k_jacobi5" in name
         m2 = re.search(r"k_march2d<double, double, \d+, \d+, \d+, \d+, \w+, (\d), 1,", name)
         if m and m.groups() in M3_CLASS:
             cls = "%s n=%d" % (M3_CLASS[m.groups()], n)
@@ -88,6 +107,8 @@ def traffic(fdir, wdir, cfdir, cwdir, out, n, sources):
             cls = "w%s%s n=%d" % (mw.group(1), M3_CLASS[mw.groups()[1:]], n)
         elif m2:
             cls = "%s n=%d" % ("pre" if m2.group(1) == "0" else "post", n)  # the finest FP64 march kernels
+        elif mj:
+            cls = "jacobi5 n=%d" % n
         else:
             continue
         rd = finest(fk[name]) * fs * 1024
@@ -102,13 +123,12 @@ def traffic(fdir, wdir, cfdir, cwdir, out, n, sources):
     for cls, k in sorted(kernels.items()):
         print("%-16s read %8.1f MB  write %8.1f MB  (%s)" % (cls, k["read_bytes"] / 1e6, k["write_bytes"] / 1e6,
                                                           k["kernel"]))
-    h = hashlib.sha256()
-    for fn in sources:
-        h.update(open(os.path.join(CSRC, fn), "rb").read())
-    rec = {"source_hash": h.hexdigest()[:16], "kernels": kernels, "fetch_scale": fs, "write_scale": ws,
-           "note": "per-dispatch FETCH_SIZE / WRITE_SIZE (KiB) of the finest-level kernels, scaled by a 256 MiB "
-                   "device copy"}
-    json.dump(rec, open(out, "w"), indent=1)
+    rec = {"source_hash": code_hash(RECORDS[os.path.basename(out)]), "kernels": kernels, "fetch_scale": fs,
+           "write_scale": ws, "note": "per-dispatch FETCH_SIZE / WRITE_SIZE (KiB) of the finest-level kernels, scaled by a 256 MiB "
+           "device copy"}
+    with open(out, "w") as fh:
+        json.dump(rec, fh, indent=1)
+        fh.write("\n")
     print("scale: fetch %.3f write %.3f; source hash %s" % (fs, ws, rec["source_hash"]))
 
 
@@ -116,4 +136,4 @@ if __name__ == "__main__":
     if sys.argv[1] == "trace":
         trace(sys.argv[2])
     else:
-        traffic(*sys.argv[2:7], int(sys.argv[7]), sys.argv[8:])
+        traffic(*sys.argv[2:7], int(sys.argv[7]))
