@@ -843,10 +843,12 @@ hipError_t launch_norm_batch(const NormItem *items, int nitems, const NormSys *s
     return hipGetLastError();
 }
 
-// (the host may poll this flag while the stream runs on)
-__device__ __forceinline__ void publish_done(SolveState *pub, int done)
+// (the host may poll `done` while the stream runs on; one store with nres)
+__device__ __forceinline__ void publish_done(SolveState *pub, int done, int nres)
 {
-    __hip_atomic_store(&pub->done, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    static_assert(offsetof(SolveState, done) == 0 && offsetof(SolveState, nres) == 4, "one word");
+    const unsigned long long w = (unsigned long long)(unsigned)nres << 32 | (unsigned)done;
+    __hip_atomic_store(reinterpret_cast<unsigned long long *>(pub), w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---- reduction of the partial sums + stop test: one workgroup per system ----
@@ -890,9 +892,8 @@ __global__ __launch_bounds__(256) void k_norm_finish(SolveState *states, const d
         if (pub) {
             if (tid < k && tid <= 200) pub[sys].hist[tid] = h;
             if (tid == 0) {
-                pub[sys].nres = k;
                 pub[sys].rel = rel0;
-                publish_done(pub + sys, done0);
+                publish_done(pub + sys, done0, k);
             }
         }
         return;
@@ -942,9 +943,8 @@ __global__ __launch_bounds__(256) void k_norm_finish(SolveState *states, const d
     }
     if (pub) {
         if (k <= 200) pub[sys].hist[k] = rel;
-        pub[sys].nres = k + 1;
         pub[sys].rel = rel;
-        publish_done(pub + sys, done);
+        publish_done(pub + sys, done, k + 1);
     }
 }
 
