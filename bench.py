@@ -229,10 +229,9 @@ def autotune(args, solver, us, fs, default):
     else:
         choice = solver.autotune(us, fs, reps=5)
     torch.cuda.synchronize()
-    log("autotune (%.2f s): %s" % (time.time() - t0, " ".join(
-        "n=%d:%s" % (n, "tile" if t else "hb%d" % hb) for n, (hb, t) in sorted(choice.items()))))
-    return {"seconds": round(time.time() - t0, 2),
-            "choices": {str(n): ("tile32" if t else "march hb=%d" % hb) for n, (hb, t) in sorted(choice.items())}}
+    shapes = {str(n): ("march hb=%d" if t is False else "tile%d") % hb for n, (hb, t) in sorted(choice.items())}
+    log("autotune (%.2f s): %s" % (time.time() - t0, " ".join("n=%s:%s" % c for c in shapes.items())))
+    return {"seconds": round(time.time() - t0, 2), "choices": shapes}
 
 
 def run_single(args, cfg):
