@@ -265,7 +265,8 @@ mg_status mg_jacobi5_static(const double *in, double *out, int rows, int cols, i
  * the fused PRE/POST kernels, mg_autotune times the PRE launch with block
  * heights 4 .. 256 and with LDS tiles on the bound arrays (u[s], f[s]: nsys
  * device pointers, as for a solve), `reps` (1 .. 50) timed launches per
- * candidate, and keeps the fastest; the choice lasts for the handle's life.
+ * candidate, and keeps the fastest (tiles of a finest level unless a height is
+ * 5 % faster); the choice lasts for the handle's life.
  * A size that holds a system's finest level runs tiles by itself when all its
  * levels together are at most 3072 tiles of 32 x 32 points (a single system
  * up to 1023 points an edge), and only then has them as a candidate.  The

@@ -220,7 +220,7 @@ __global__ __launch_bounds__(256) void k_resid_restrict1(GenArgs g)
 // and residuals come from the next lanes, so each residual and each face is
 // computed once or twice instead of 2.25 times (a coarse point by itself takes
 // nine residuals of five points and their 36 faces: 1023^2 variable-coefficient
-// FP32 13.2 us -> 7.3).  The sums and their order are those of the 1D kernel
+// FP32 13.2 us -> 6.4).  The sums and their order are those of the 1D kernel
 // above, rows from below, west to east.
 constexpr int kRRows = 4;
 template <class S, class F, bool VC>
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(256) void k_prolong_correct1(GenArgs g)
 
 // 2D (ADD), and interpolation alone, B = P Bc: a wavefront takes 64 columns of
 // 8 rows, all loads in flight at once; each coarse row is interpolated along x
-// once (1023^2 FP32 8.2 us -> 6.3, the index arithmetic of a point by itself
+// once (1023^2 FP32 8.2 us -> 6.1, the index arithmetic of a point by itself
 // being most of it; 2047^2 FP64 without the sum 19.4 -> 9.0).  Same order: x,
 // then y.
 template <class S, bool ADD>
