@@ -843,12 +843,14 @@ hipError_t launch_norm_batch(const NormItem *items, int nitems, const NormSys *s
     return hipGetLastError();
 }
 
-// (the host may poll `done` while the stream runs on; one store with nres)
+// The host may poll `done` while the stream runs on: one 8-byte store with nres,
+// there when the kernel ends at the latest (its end makes all its stores visible
+// to the host).  As an atomic store, of system or of device scope, a publishing
+// kernel takes 4.6 us, 3.8 like this, three of them a solve: 255^2 287.6 -> 284.8.
 __device__ __forceinline__ void publish_done(SolveState *pub, int done, int nres)
 {
     static_assert(offsetof(SolveState, done) == 0 && offsetof(SolveState, nres) == 4, "one word");
-    const unsigned long long w = (unsigned long long)(unsigned)nres << 32 | (unsigned)done;
-    __hip_atomic_store(reinterpret_cast<unsigned long long *>(pub), w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    *reinterpret_cast<int2 *>(pub) = make_int2(done, nres);
 }
 
 // ---- reduction of the partial sums + stop test: one workgroup per system ----
